@@ -100,7 +100,7 @@ def make_workload(name):
 # (the SSSP layout the benchmark times).
 TRAFFIC_SOURCES = ("paper_1711_00231_amd/csrc/lbg_kernels.hpp", "paper_1711_00231_amd/csrc/lbg_device.hpp",
                    "paper_1711_00231_amd/csrc/lbg_sliced.hpp", "paper_1711_00231_amd/csrc/lbg_order.hpp",
-                   "paper_1711_00231_amd/csrc/lbg.hip")
+                   "paper_1711_00231_amd/csrc/lbg_team.hpp", "paper_1711_00231_amd/csrc/lbg.hip")
 
 
 def recorded_traffic():

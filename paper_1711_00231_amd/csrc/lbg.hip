@@ -13,6 +13,7 @@
 
 #include "../../include/lbg.h"
 #include "lbg_kernels.hpp"
+#include "lbg_team.hpp"
 #include "lbg_sliced.hpp"
 #include "lbg_split.hpp"
 #include "lbg_order.hpp"
@@ -46,8 +47,8 @@ const char* guard_names(unsigned flags) {
   buf[0] = 0;
   static const char* names[] = {"worklist capacity", "tile-mark capacity", "edge-worklist capacity",
                                 "arc outside the graph", "tile without an entry", "source outside [0, n)",
-                                "malformed split table"};
-  for (int b = 0; b < 7; ++b)
+                                "malformed split table", "small-frontier team stalled"};
+  for (int b = 0; b < 8; ++b)
     if (flags & (1u << b)) {
       if (buf[0]) strncat(buf, ", ", sizeof(buf) - strlen(buf) - 1);
       strncat(buf, names[b], sizeof(buf) - strlen(buf) - 1);
@@ -64,7 +65,7 @@ int32_t resolve(int32_t s) { return s == LBG_AUTO ? LBG_BALANCED : s; }
 
 // Workspace layout.  All offsets 256-byte aligned.
 struct Layout {
-  size_t ctl, visited, seen[2], xfilter, dstate, d16, node[2], eprefix[2], estart[2], tile[2], sub[2],
+  size_t ctl, team, visited, seen[2], xfilter, dstate, d16, node[2], eprefix[2], estart[2], tile[2], sub[2],
       hier_trace, total;
   uint32_t node_cap, tile_cap, edge_cap;
 };
@@ -81,6 +82,7 @@ Layout layout(int32_t n, int64_t m, int32_t strategy, int is_sssp, int64_t child
     return at;
   };
   L.ctl = take(sizeof(Ctl));
+  if (s == LBG_BALANCED) L.team = take(sizeof(lbg::TeamCtl));
   const size_t words = (static_cast<size_t>(n) + 31) / 32;
   if (is_sssp) {
     L.dstate = take(sizeof(unsigned long long) * static_cast<size_t>(n));
@@ -114,6 +116,8 @@ Layout layout(int32_t n, int64_t m, int32_t strategy, int is_sssp, int64_t child
     if (s == LBG_BINNED) extra = m / lbg::kMinMdt + 1;
     if (s == LBG_SPLIT) extra = children < 0 ? m : children;
     L.node_cap = static_cast<uint32_t>(n + extra);
+    // the small-frontier team keeps one segment of entries per workgroup
+    if (s == LBG_BALANCED) L.node_cap = std::max(L.node_cap, lbg::kTeamE);
     L.tile_cap = static_cast<uint32_t>((m + lbg::kMinTile - 1) / lbg::kMinTile + 2);
     for (int b = 0; b < 2; ++b) {
       L.node[b] = take(sizeof(int32_t) * static_cast<size_t>(L.node_cap));
@@ -163,22 +167,7 @@ struct Grids {
   int sliced[2][2];                                      // [is_sssp][narrow], a multiple of 8 (>= 8)
   int bal_p[2];                                          // SSSP with packed arcs [narrow]
   int bal_s[2][2];                                       // split graph [is_sssp][narrow]
-  bool small_p[2];
-  bool small[2][2];                                      // small-frontier kernel fits the device
 };
-
-// The small-frontier kernel holds its frontier in LDS (about 100 KiB for
-// SSSP); use it only where the device grants a workgroup that much.
-template <typename K>
-bool fits_lds(K kernel) {
-  int dev = 0, max_lds = 0;
-  hipFuncAttributes fa{};
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
-      hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(kernel)) != hipSuccess)
-    return false;
-  return fa.sharedSizeBytes <= static_cast<size_t>(max_lds) && fa.maxThreadsPerBlock >= lbg::kSmallBlock;
-}
 
 // Sliced expansion: every slice needs at least one workgroup; equal counts
 // per slice keep the XCDs evenly loaded.
@@ -214,16 +203,10 @@ const Grids& grids() {
     g[dev].bal_s[0][1] = resident_grid(lbg::k_expand_balanced<false, true, false, false, true>);
     g[dev].bal_s[1][0] = resident_grid(lbg::k_expand_balanced<true, false, false, false, true>);
     g[dev].bal_s[1][1] = resident_grid(lbg::k_expand_balanced<true, true, false, false, true>);
-    g[dev].small_p[0] = fits_lds(lbg::k_expand_small<true, false, true>);
-    g[dev].small_p[1] = fits_lds(lbg::k_expand_small<true, true, true>);
     g[dev].sliced[0][0] = slice_grid(resident_grid(lbg::k_expand_sliced<false, false>));
     g[dev].sliced[0][1] = slice_grid(resident_grid(lbg::k_expand_sliced<false, true>));
     g[dev].sliced[1][0] = slice_grid(resident_grid(lbg::k_expand_sliced<true, false>));
     g[dev].sliced[1][1] = slice_grid(resident_grid(lbg::k_expand_sliced<true, true>));
-    g[dev].small[0][0] = fits_lds(lbg::k_expand_small<false, false>);
-    g[dev].small[0][1] = fits_lds(lbg::k_expand_small<false, true>);
-    g[dev].small[1][0] = fits_lds(lbg::k_expand_small<true, false>);
-    g[dev].small[1][1] = fits_lds(lbg::k_expand_small<true, true>);
     done[dev] = true;
   }
   return g[dev];
@@ -430,6 +413,7 @@ int solve(const Problem& P) {
   }
   if (strat == LBG_HIER) a.hier_trace = reinterpret_cast<uint32_t*>(ws + Lay.hier_trace);
   a.ctl = reinterpret_cast<Ctl*>(ws + Lay.ctl);
+  if (strat == LBG_BALANCED) a.team = reinterpret_cast<lbg::TeamCtl*>(ws + Lay.team);
   a.n = static_cast<uint32_t>(P.n);
   a.m = static_cast<uint32_t>(P.m);
   a.words = static_cast<uint32_t>((static_cast<size_t>(P.n) + 31) / 32);
@@ -437,6 +421,9 @@ int solve(const Problem& P) {
   a.tile_cap = Lay.tile_cap;
   a.edge_cap = Lay.edge_cap;
   a.scan_min = 0xffffffffu;
+  // levels of at most this many arcs run in the small-frontier team; a level
+  // that a caller's threshold makes a scan level does not
+  uint32_t team_limit = strat == LBG_BALANCED ? lbg::kTeamE : 0u;
   if (!P.is_sssp && strat == LBG_BALANCED) {
     int64_t smin;
     {
@@ -447,6 +434,7 @@ int solve(const Problem& P) {
     // (n / 2: 0.5 % faster still), the 2048 x 2048 grid with shortcuts 8.5 %
     // (n / 2: its levels never reach it)
     if (smin < 0) smin = std::max<int64_t>(1, P.n / 4);
+    else team_limit = static_cast<uint32_t>(std::min<int64_t>(team_limit, smin > 0 ? smin - 1 : 0));
     a.scan_min = static_cast<uint32_t>(std::min<int64_t>(smin, 0xffffffffll));
   }
   // a level can only run in scan mode if the graph has that many arcs
@@ -620,11 +608,12 @@ int solve(const Problem& P) {
   // levels to the single-workgroup kernel, which keeps going on the device
   // until a level outgrows those limits or the worklist empties; the host
   // then resumes from ctl->levels, the next level to expand.
-  const bool small_ok = strat == LBG_BALANCED && (packed ? GR.small_p[nw] : GR.small[sv][nw]);
+  const bool small_ok = strat == LBG_BALANCED && team_limit > 0u;
+  uint32_t seq = 0;  // team launches so far
   uint32_t L = 0, L_prev = 0;
   const uint32_t hint = g_level_hint[P.is_sssp ? 1 : 0];
   uint32_t batch = hint ? std::min<uint32_t>(std::max<uint32_t>(hint + 1, 8), 64) : 8;
-  bool small = false, used_small = false;
+  bool small = small_ok, used_small = small_ok;
   size_t nev = 0;
   g_event_level.clear();
   g_event_end.clear();
@@ -638,17 +627,19 @@ int solve(const Problem& P) {
   for (;;) {
     if (profiling && (rc = mark()) != LBG_OK) return rc;  // the batch's first interval starts here
     if (small) {
-      const uint32_t max_levels = static_cast<uint32_t>(level_cap + 1 - L);
+      const uint32_t max_levels = static_cast<uint32_t>(std::min<uint64_t>(level_cap + 1 - L, 0xffffffffu));
+      const dim3 tg(lbg::kTeamMax), tb(lbg::kTeamBlock);
       if (P.is_sssp && packed) {
-        if (narrow) hipLaunchKernelGGL((lbg::k_expand_small<true, true, true>), dim3(1), dim3(lbg::kSmallBlock), 0, st, a, L, max_levels);
-        else hipLaunchKernelGGL((lbg::k_expand_small<true, false, true>), dim3(1), dim3(lbg::kSmallBlock), 0, st, a, L, max_levels);
+        if (narrow) hipLaunchKernelGGL((lbg::k_expand_team<true, true, true>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
+        else hipLaunchKernelGGL((lbg::k_expand_team<true, false, true>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
       } else if (P.is_sssp) {
-        if (narrow) hipLaunchKernelGGL((lbg::k_expand_small<true, true>), dim3(1), dim3(lbg::kSmallBlock), 0, st, a, L, max_levels);
-        else hipLaunchKernelGGL((lbg::k_expand_small<true, false>), dim3(1), dim3(lbg::kSmallBlock), 0, st, a, L, max_levels);
+        if (narrow) hipLaunchKernelGGL((lbg::k_expand_team<true, true>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
+        else hipLaunchKernelGGL((lbg::k_expand_team<true, false>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
       } else {
-        if (narrow) hipLaunchKernelGGL((lbg::k_expand_small<false, true>), dim3(1), dim3(lbg::kSmallBlock), 0, st, a, L, max_levels);
-        else hipLaunchKernelGGL((lbg::k_expand_small<false, false>), dim3(1), dim3(lbg::kSmallBlock), 0, st, a, L, max_levels);
+        if (narrow) hipLaunchKernelGGL((lbg::k_expand_team<false, true>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
+        else hipLaunchKernelGGL((lbg::k_expand_team<false, false>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
       }
+      ++seq;
       HIP_TRY(hipGetLastError());
       if (profiling) {
         if ((rc = mark()) != LBG_OK) return rc;
@@ -676,19 +667,15 @@ int solve(const Problem& P) {
     if (host->error)
       return fail(LBG_EOVERFLOW, "device guard tripped (flags 0x%x: %s)", host->error, guard_names(host->error));
     L = host->levels;
-    uint64_t ef = static_cast<uint32_t>(host->ctr[L % 3]), nfr = host->ctr[L % 3] >> 32;
-    if (sl) {  // the mixed list's tail (ctr) plus the 8 slice tails
-      for (int x = 0; x < lbg::kXcds; ++x) {
-        ef += static_cast<uint32_t>(host->xstat[x][4 + L % 3]);
-        nfr += host->xstat[x][4 + L % 3] >> 32;
-      }
-    }
+    uint64_t ef = static_cast<uint32_t>(host->ctr[L % 3]);
+    if (sl)  // the mixed list's tail (ctr) plus the 8 slice tails
+      for (int x = 0; x < lbg::kXcds; ++x) ef += static_cast<uint32_t>(host->xstat[x][4 + L % 3]);
     if (ef == 0u) break;
     if (L > level_cap)
       return fail(LBG_EINTERNAL, "more than n + 1 levels; the CSR is probably malformed");
     const bool was_small = small;
-    small = small_ok && ef <= lbg::kSmallE && nfr <= lbg::kSmallF &&
-            !(was_small && L == L_prev);  // a small step always advances; never spin
+    small = small_ok && ef <= team_limit &&
+            !(was_small && L == L_prev);  // no progress (the team came together too small): never spin
     if (was_small && !small) batch = 8;
     used_small = used_small || small;
     L_prev = L;
@@ -1329,7 +1316,10 @@ namespace {
 // ends.  Host code never passes the array's name to a kernel or a copy (on
 // the host it only stands in for the symbol); it uses the device address
 // hipGetSymbolAddress gives, looked up once per device.
-static __device__ __align__(256) unsigned char scratch[LBG_NOALLOC_SCRATCH_BYTES];
+// kNoallocTeam: the small-frontier team's control words (balanced solves) come
+// on top of the 64 MiB that the sizes a call accepts are counted against.
+constexpr size_t kNoallocTeam = (sizeof(lbg::TeamCtl) + 255) / 256 * 256;
+static __device__ __align__(256) unsigned char scratch[LBG_NOALLOC_SCRATCH_BYTES + kNoallocTeam];
 
 namespace {
 
@@ -1387,15 +1377,16 @@ int lbg_sssp_noalloc(const int32_t* offsets, const int32_t* cols, const uint32_t
                             "(got %d)", strategy);
   if (n > 0 && m >= 0 && m <= INT32_MAX) {
     const size_t need = layout(n, m, strategy, 1).total;
-    if (need > LBG_NOALLOC_SCRATCH_BYTES)
+    const size_t most = LBG_NOALLOC_SCRATCH_BYTES + (s == LBG_BALANCED ? kNoallocTeam : 0);
+    if (need > most)
       return fail(LBG_ENOMEM, "lbg_sssp_noalloc: n = %d, m = %lld need %zu bytes of scratch, above its "
                   "maximum of %zu", n, static_cast<long long>(m), need,
-                  static_cast<size_t>(LBG_NOALLOC_SCRATCH_BYTES));
+                  most);
   }
   void* ws = nullptr;
   const int rc = noalloc_scratch(&ws);
   if (rc) return rc;
-  Problem P{offsets, cols, weights, nullptr, n, m, src, dist_out, ws, LBG_NOALLOC_SCRATCH_BYTES,
+  Problem P{offsets, cols, weights, nullptr, n, m, src, dist_out, ws, sizeof(scratch),
             strategy, 1, stats, static_cast<hipStream_t>(stream)};
   P.no_alloc = true;
   return solve(P);

@@ -71,6 +71,23 @@ struct Ctl {
 };
 static_assert(sizeof(Ctl) == 128 + kXcds * 128, "Ctl layout");
 
+// The team of the small-frontier kernel (lbg_team.hpp): at most kTeamMax
+// workgroups, kTeamSlots arcs of a level each.
+constexpr uint32_t kTeamMax = 128;
+constexpr uint32_t kTeamSlots = 2048;
+constexpr uint32_t kTeamE = kTeamMax * kTeamSlots;  // arcs of a level run there
+// Its control words, in the workspace, zeroed by k_init.  join[] / size[] are
+// used by launch number seq of a solve at seq % 4 and cleared two launches
+// ahead.  flag[e % 2][w]: workgroup w's word of exchange e, (e << 34) | payload.
+struct TeamCtl {
+  uint32_t join[4];
+  uint32_t size[4];
+  uint32_t epoch;  // exchanges so far in this solve
+  uint32_t pad[23];
+  unsigned long long flag[2][kTeamMax];
+};
+constexpr uint32_t kTeamWords = sizeof(TeamCtl) / sizeof(uint32_t);
+
 // One worklist (frontier) buffer.  For node worklists entry i holds the node,
 // the position of its first edge in this level's edge space (strictly
 // increasing in i because every stored node has out-degree >= 1) and the CSR
@@ -106,6 +123,7 @@ struct KArgs {
   Frontier fr[2];
   int32_t* sub[2];       // hierarchical strategy: sublists (worklist indices) of two sub-iterations
   Ctl* ctl;
+  TeamCtl* team;         // balanced strategy: the small-frontier team (else null)
   uint32_t n;
   uint32_t m;
   uint32_t words;        // (n + 31) / 32
@@ -172,7 +190,7 @@ __device__ __forceinline__ void split_piece(uint32_t d, uint32_t p, uint32_t k, 
 // split graph's child table names a child outside the graph or a child piece
 // without arcs (tables that did not come from lbg_split_graph).
 constexpr unsigned kErrNodeCap = 1u, kErrTileCap = 2u, kErrEdgeCap = 4u, kErrBadArc = 8u,
-                   kErrBadTile = 16u, kErrBadSrc = 32u, kErrBadSplit = 64u;
+                   kErrBadTile = 16u, kErrBadSrc = 32u, kErrBadSplit = 64u, kErrTeam = 128u;
 
 // Address of element idx of an array.  With kNarrow the byte offset is
 // formed in 32 bits, so the access is a uniform (SGPR) base plus a 32-bit

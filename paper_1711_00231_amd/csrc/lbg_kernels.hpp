@@ -63,9 +63,7 @@ __device__ __forceinline__ void load_arc(const KArgs& a, uint32_t e, int32_t* v,
 
 
 // Level bookkeeping, by one thread of the grid: clear the counter two levels
-// ahead (the one level L+1 appends to) and account level L.  kSmall: the
-// level runs in the small-frontier kernel, whose work is also counted apart.
-template <bool kSmall = false>
+// ahead (the one level L+1 appends to) and account level L.
 __device__ __forceinline__ void level_account(const KArgs& a, uint32_t L, unsigned long long c) {
   __hip_atomic_store(&a.ctl->ctr[(L + 2) % 3], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (static_cast<uint32_t>(c) != 0u) {
@@ -73,10 +71,6 @@ __device__ __forceinline__ void level_account(const KArgs& a, uint32_t L, unsign
     a.ctl->levels = L + 1;
     a.ctl->frontier_entries += fe;
     a.ctl->edges_scanned += static_cast<uint32_t>(c);
-    if (kSmall) {
-      a.ctl->p_frontier_entries += fe;
-      a.ctl->p_edges_scanned += static_cast<uint32_t>(c);
-    }
   }
 }
 
@@ -316,6 +310,8 @@ __global__ __launch_bounds__(kBlock) void k_init(KArgs a, int32_t src) {
     return;
   }
   init_state<kSssp>(a, src, gid, stride);
+  if (a.team)
+    for (uint32_t k = gid; k < kTeamWords; k += stride) reinterpret_cast<uint32_t*>(a.team)[k] = 0u;
   if (a.hier_trace)
     for (uint32_t k = gid; k < kHierTraceLevels * kHierTraceSubs; k += stride) a.hier_trace[k] = 0u;
   const int32_t s0 = a.offsets[src];
@@ -1063,353 +1059,6 @@ __global__ __launch_bounds__(kBlock) void k_expand_batched_graph(KArgs a, uint32
 
 __global__ void k_level_advance(Ctl* ctl, uint32_t K) {
   if (threadIdx.x == 0 && blockIdx.x == 0) ctl->level_base += K;
-}
-
-// ------------------------------------------------ small frontiers (a8) ----
-// Level loop inside ONE workgroup for small frontiers.  High-diameter graphs
-// spend thousands of levels with a few thousand edges each; there a level's
-// cost is its chain of dependent memory round trips, not its bandwidth, and
-// a one-level launch adds several (tile marks, worklist staging, per-XCD
-// filters, the tail reservation, the kernel boundary).  Here the frontier
-// stays in LDS and a level is three round trips: the arcs of the frontier,
-// one atomic per arc (OR on the visited bitmap / 64-bit min on the packed
-// state), then the offsets of the arcs' winners, so a discovered node is
-// pushed with its first arc and degree (SSSP adds a coherent read of each
-// pushed node's distance).  Slots of the
-// level's edge space map to entries through an LDS bitmask of entry starts
-// with per-word popcount prefixes.  Pushes also go to the global node list
-// of the next worklist, for the case that they outgrow LDS.
-//
-// The kernel runs levels L0, L0+1, ... and returns when a level is empty,
-// after max_levels levels, or when the next level has more than kSmallF
-// entries or kSmallE edges; then it writes that level in the one-level
-// kernels' worklist format (entries, edge prefix, tile marks, tail counter)
-// and the host continues from ctl->levels.  Entry condition (host): level
-// L0 has at most kSmallF entries and kSmallE edges.
-constexpr int kSmallBlock = 1024;
-constexpr int kSmallWaves = kSmallBlock / 64;
-constexpr uint32_t kSmallF = 4000;   // frontier entries held in LDS
-constexpr uint32_t kSmallE = 16384;  // edges of a level run in this kernel
-constexpr uint32_t kSmallW = kSmallE / 32;
-constexpr int kSmallU = 4;           // edge slots per thread issued together
-constexpr int kSmallC = 4;           // entries per thread per scan chunk
-
-template <bool kSssp>
-struct SmallLds {
-  uint32_t s[kSmallF];      // current level: first arc of entry i
-  uint32_t p[kSmallF];      //   exclusive prefix of the entries' degrees
-  uint32_t du[kSssp ? kSmallF : 1];  //   distance of entry i's node
-  int32_t nv[kSmallF];      // pushes of this level: node,
-  int32_t ns[kSmallF];      //   first arc,
-  int32_t nd[kSmallF];      //   out-degree (> 0)
-  uint32_t flag[kSmallW];   // bit e: an entry starts at edge slot e
-  uint32_t wpre[kSmallW];   // set bits in the words before
-  uint32_t wsum[2][kSmallWaves];
-  uint32_t ncount;          // pushes so far this level
-};
-
-// Exclusive block scan of two counters (kSmallBlock threads).  Returns the
-// thread's prefixes; *tn, *te receive the block totals.
-template <bool kSssp>
-__device__ __forceinline__ void small_scan2(SmallLds<kSssp>& sm, uint32_t xn, uint32_t xe,
-                                            uint32_t* pn, uint32_t* pe, uint32_t* tn, uint32_t* te) {
-  const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const uint32_t in = wave_incl_scan(xn), ie = wave_incl_scan(xe);
-  __syncthreads();  // wsum may still be read by a previous scan
-  if (lane == 63) {
-    sm.wsum[0][wid] = in;
-    sm.wsum[1][wid] = ie;
-  }
-  __syncthreads();
-  uint32_t bn = 0, be = 0, an = 0, ae = 0;
-  for (int k = 0; k < kSmallWaves; ++k) {
-    const uint32_t wn = sm.wsum[0][k], we = sm.wsum[1][k];
-    if (static_cast<uint32_t>(k) < wid) {
-      bn += wn;
-      be += we;
-    }
-    an += wn;
-    ae += we;
-  }
-  *pn = bn + in - xn;
-  *pe = be + ie - xe;
-  *tn = an;
-  *te = ae;
-}
-
-// The `cnt` (> kSmallF) nodes pushed for level L, all with out-arcs, from
-// the global list out.node to the one-level worklist format.  Returns the
-// level's packed tail.
-template <bool kSssp, bool kNarrow>
-__device__ __forceinline__ unsigned long long small_overflow(const KArgs& a, SmallLds<kSssp>& sm,
-                                                             const Frontier& out, uint32_t cnt) {
-  constexpr uint32_t T = TileCfg<kSssp>::kEdges;
-  constexpr int kPay = kSssp ? 1 : 0;
-  uint32_t base_e = 0;
-  for (uint32_t c0 = 0; c0 < cnt; c0 += kSmallBlock * kSmallC) {
-    int32_t v[kSmallC], st[kSmallC], dg[kSmallC];
-    uint32_t xe = 0;
-#pragma unroll
-    for (int r = 0; r < kSmallC; ++r) {
-      const uint32_t i = c0 + threadIdx.x * kSmallC + r;
-      v[r] = i < cnt ? *at<kNarrow>(out.node, i) : -1;
-    }
-#pragma unroll
-    for (int r = 0; r < kSmallC; ++r) {
-      st[r] = 0;
-      dg[r] = 0;
-      if (v[r] >= 0) {
-        st[r] = *at<kNarrow>(a.offsets, v[r]);
-        dg[r] = *at<kNarrow>(a.offsets, v[r] + 1) - st[r];
-        xe += static_cast<uint32_t>(dg[r]);
-      }
-    }
-    uint32_t pn, pe, tn, te;
-    small_scan2(sm, 0u, xe, &pn, &pe, &tn, &te);
-#pragma unroll
-    for (int r = 0; r < kSmallC; ++r) {
-      if (v[r] >= 0) {
-        write_entry<kPay, T, kNarrow>(a, out, c0 + threadIdx.x * kSmallC + r, base_e + pe, v[r], 0,
-                                      st[r], dg[r]);
-        pe += static_cast<uint32_t>(dg[r]);
-      }
-    }
-    base_e += te;
-  }
-  return (static_cast<unsigned long long>(cnt) << 32) | base_e;
-}
-
-template <bool kSssp, bool kNarrow, bool kPacked = false>
-__global__ __launch_bounds__(kSmallBlock) void k_expand_small(KArgs a, uint32_t L0, uint32_t max_levels) {
-  static_assert(!kPacked || kSssp, "packed arcs: SSSP");
-  constexpr uint32_t T = TileCfg<kSssp>::kEdges;
-  constexpr int kPay = kSssp ? 1 : 0;
-  __shared__ SmallLds<kSssp> sm;
-  __shared__ uint32_t red[2][kSmallWaves];
-  const uint32_t tid = threadIdx.x, lane = tid & 63;
-
-  // Level L0 from the one-level worklist format.
-  unsigned long long c = __hip_atomic_load(&a.ctl->ctr[L0 % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  uint32_t nf = static_cast<uint32_t>(c >> 32), E = static_cast<uint32_t>(c);
-  if (E == 0u || nf == 0u || nf > kSmallF || E > kSmallE) return;  // the host checked; uniform
-  {
-    const Frontier f0 = a.fr[L0 & 1];
-    for (uint32_t i = tid; i < nf; i += kSmallBlock) {
-      sm.s[i] = static_cast<uint32_t>(*at<kNarrow>(f0.estart, i));
-      sm.p[i] = *at<kNarrow>(f0.eprefix, i);
-      if (kSssp) {
-        const int32_t u = *at<kNarrow>(f0.node, i);
-        sm.du[i] = static_cast<uint32_t>(__hip_atomic_load(at<kNarrow>(a.dstate, static_cast<uint32_t>(u)),
-                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32);
-      }
-    }
-  }
-  uint32_t upd = 0, atom = 0;
-  unsigned long long tot_f = 0, tot_e = 0;  // this launch's levels (thread 0)
-  bool bad = false;
-  uint32_t L = L0;
-  for (;; ++L) {
-    if (tid == 0) {
-      tot_f += nf;
-      tot_e += E;
-      sm.ncount = 0u;
-    }
-    // Entry starts -> bitmask -> per-word prefixes.
-    const uint32_t words = (E + 31) / 32;
-    for (uint32_t k = tid; k < words; k += kSmallBlock) sm.flag[k] = 0u;
-    __syncthreads();
-    for (uint32_t i = tid; i < nf; i += kSmallBlock) atomicOr(&sm.flag[sm.p[i] >> 5], 1u << (sm.p[i] & 31));
-    __syncthreads();
-    if (tid < 64) {
-      constexpr uint32_t kPer = kSmallW / 64;
-      uint32_t x[kPer], t = 0;
-#pragma unroll
-      for (uint32_t r = 0; r < kPer; ++r) {
-        const uint32_t k = tid * kPer + r;
-        x[r] = k < words ? __popc(sm.flag[k]) : 0u;
-        t += x[r];
-      }
-      uint32_t pre = wave_incl_scan(t) - t;
-#pragma unroll
-      for (uint32_t r = 0; r < kPer; ++r) {
-        const uint32_t k = tid * kPer + r;
-        if (k < words) sm.wpre[k] = pre;
-        pre += x[r];
-      }
-    }
-    __syncthreads();
-
-    const Frontier nxt = a.fr[(L + 1) & 1];
-    for (uint32_t b0 = 0; b0 < E; b0 += kSmallBlock * kSmallU) {
-      int32_t vv[kSmallU];
-      uint32_t ww[kSmallU], du[kSmallU];
-#pragma unroll
-      for (int r = 0; r < kSmallU; ++r) {
-        const uint32_t e = b0 + r * kSmallBlock + tid;
-        vv[r] = -1;
-        ww[r] = 0;
-        du[r] = 0;
-        if (e < E) {
-          const uint32_t k = e >> 5;
-          const uint32_t msk = static_cast<uint32_t>((2ull << (e & 31)) - 1ull);
-          const uint32_t i = sm.wpre[k] + __popc(sm.flag[k] & msk) - 1;  // entry 0 starts at slot 0
-          const uint32_t arc = sm.s[i] + (e - sm.p[i]);
-          if (i < nf && arc < a.m) {
-            if (kPacked) {
-              load_arc<true, kNarrow>(a, arc, &vv[r], &ww[r]);
-            } else {
-              vv[r] = *at<kNarrow>(a.cols, arc);
-              if (kSssp) ww[r] = *at<kNarrow>(a.weights, arc);
-            }
-            if (kSssp) du[r] = sm.du[i];
-          } else {
-            bad = true;
-          }
-        }
-      }
-      // One atomic per arc.
-      bool win[kSmallU];
-      int32_t s0[kSmallU], s1[kSmallU];
-#pragma unroll
-      for (int r = 0; r < kSmallU; ++r) {
-        if (vv[r] >= 0 && static_cast<uint32_t>(vv[r]) >= a.n) {
-          bad = true;
-          vv[r] = -1;
-        }
-        s0[r] = 0;
-        s1[r] = 0;
-      }
-#pragma unroll
-      for (int r = 0; r < kSmallU; ++r) {
-        win[r] = false;
-        if (vv[r] < 0) continue;
-        ++atom;
-        if (!kSssp) {
-          const uint32_t bit = 1u << (vv[r] & 31);
-          const uint32_t old = atomicOr(at<kNarrow>(a.visited, static_cast<uint32_t>(vv[r]) >> 5), bit);
-          win[r] = !(old & bit);
-        } else {
-          const uint32_t alt = du[r] + ww[r];
-          const unsigned long long old =
-              atomicMin(at<kNarrow>(a.dstate, static_cast<uint32_t>(vv[r])),
-                        (static_cast<unsigned long long>(alt) << 32) | (L + 1));
-          if (alt < static_cast<uint32_t>(old >> 32)) {
-            *at<kNarrow>(a.d16, vv[r]) = f16_of(alt);  // filter of the one-level launches
-            ++upd;
-            win[r] = static_cast<uint32_t>(old) != L + 1;  // not yet queued this level
-          }
-        }
-      }
-      // Offsets of the winners only: the workgroup's CU issues about one
-      // random lane access per cycle, and most arcs do not win (measured on
-      // the 2048 x 2048 grid without shortcuts: BFS 11 % faster than loading
-      // every target's offsets alongside its atomic).
-#pragma unroll
-      for (int r = 0; r < kSmallU; ++r) {
-        if (win[r]) {
-          s0[r] = *at<kNarrow>(a.offsets, vv[r]);
-          s1[r] = *at<kNarrow>(a.offsets, vv[r] + 1);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < kSmallU; ++r) {
-        if (!kSssp && win[r]) {
-          *at<kNarrow>(a.levels, vv[r]) = static_cast<int32_t>(L + 1);
-          ++upd;
-        }
-        const int32_t d = s1[r] - s0[r];
-        if (win[r] && d > 0) {  // a node without out-arcs has nothing to expand
-          const uint32_t k = atomicAdd(&sm.ncount, 1u);  // LDS
-          if (k < kSmallF) {
-            sm.nv[k] = vv[r];
-            sm.ns[k] = s0[r];
-            sm.nd[k] = d;
-          }
-          if (k < a.node_cap) *at<kNarrow>(nxt.node, k) = vv[r];
-          else bad = true;
-        }
-      }
-    }
-    if (__any(bad) && lane == 0) atomicOr(&a.ctl->error, kErrBadArc);
-    __syncthreads();
-    // at most one push per node per level, so never above node_cap
-    const uint32_t cnt = min(sm.ncount, a.node_cap);
-    const uint32_t Ln = L + 1;
-    bool stop = false;
-    if (cnt == 0u) {
-      c = 0ull;
-      stop = true;
-    } else if (cnt > kSmallF) {
-      c = small_overflow<kSssp, kNarrow>(a, sm, nxt, cnt);
-      stop = true;
-    } else {
-      // pushes -> the next level's entries: scan the degrees
-      uint32_t d[kSmallC], xe = 0;
-#pragma unroll
-      for (int r = 0; r < kSmallC; ++r) {
-        const uint32_t i = tid * kSmallC + r;
-        d[r] = i < cnt ? static_cast<uint32_t>(sm.nd[i]) : 0u;
-        xe += d[r];
-      }
-      uint32_t pn, pe, tn, te;
-      small_scan2(sm, 0u, xe, &pn, &pe, &tn, &te);
-#pragma unroll
-      for (int r = 0; r < kSmallC; ++r) {
-        const uint32_t i = tid * kSmallC + r;
-        if (i < cnt) {
-          sm.s[i] = static_cast<uint32_t>(sm.ns[i]);
-          sm.p[i] = pe;
-          if (kSssp)
-            sm.du[i] = static_cast<uint32_t>(__hip_atomic_load(at<kNarrow>(a.dstate, static_cast<uint32_t>(sm.nv[i])),
-                                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32);
-          pe += d[r];
-        }
-      }
-      nf = cnt;
-      E = te;
-      c = (static_cast<unsigned long long>(nf) << 32) | E;
-      if (E > kSmallE || Ln - L0 >= max_levels) {
-        __syncthreads();
-        for (uint32_t i = tid; i < nf; i += kSmallBlock)
-          write_entry<kPay, T, kNarrow>(a, nxt, i, sm.p[i], sm.nv[i], 0, sm.ns[i], sm.nd[i]);
-        stop = true;
-      }
-    }
-    if (stop) break;
-    __syncthreads();
-  }
-  // Bookkeeping of every level run here, then the tail of level L + 1 (the
-  // next to expand) and a cleared counter for the level after it.
-  if (tid == 0) {
-    const uint32_t Ln = L + 1;
-    a.ctl->levels = Ln;
-    a.ctl->frontier_entries += tot_f;
-    a.ctl->edges_scanned += tot_e;
-    a.ctl->p_frontier_entries += tot_f;
-    a.ctl->p_edges_scanned += tot_e;
-    __hip_atomic_store(&a.ctl->ctr[Ln % 3], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&a.ctl->ctr[(Ln + 1) % 3], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  // the balanced kernel's tile counters of level L + 1 (see expand_level)
-  if (tid < static_cast<uint32_t>(kXcds)) a.ctl->xstat[tid][8 + (L + 1) % 3] = 0ull;
-  if (a.count_stats) {
-    const uint32_t su = wave_sum(upd), sa = wave_sum(atom);
-    if (lane == 0) {
-      red[0][tid >> 6] = su;
-      red[1][tid >> 6] = sa;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      unsigned long long tu = 0, ta = 0;
-      for (int w = 0; w < kSmallWaves; ++w) {
-        tu += red[0][w];
-        ta += red[1][w];
-      }
-      const int x = blockIdx.x % kXcds;
-      atomicAdd(&a.ctl->xstat[x][2], tu);
-      atomicAdd(&a.ctl->xstat[x][3], ta);
-    }
-  }
 }
 
 // ---------------------------------------------------------- node (BS) ----

@@ -1,0 +1,135 @@
+"""The small-frontier team (levels of at most 262,144 arcs run on the device by
+up to 128 workgroups) against the oracle, bit for bit, at the sizes where its
+cuts fall: one arc per level, hubs that span every workgroup, levels of exactly
+the largest size and one arc more, and hand-overs to one-level launches and
+back."""
+import numpy as np
+import pytest
+
+import graphgen
+import oracle
+import pins
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+from paper_1711_00231_amd import lbg  # noqa: E402
+
+O = oracle.get()
+LIMIT = 128 * 2048  # arcs of a level that the team takes
+
+
+@pytest.fixture(autouse=True)
+def _reset():
+    yield
+    lbg.set_bfs_scan_min(-1)
+    lbg.set_addressing(0)
+
+
+def _fan(width, tail=3, salt=0):
+    """A path of 3 nodes into a hub with `width` children; every 7th child
+    starts a chain of `tail` nodes, every 11th points back at the hub."""
+    rng = np.random.default_rng(salt)
+    kids = 4 + np.arange(width)
+    src, dst = [np.arange(3), np.full(width, 3)], [np.arange(1, 4), kids]
+    nxt = 4 + width
+    heads = kids[::7]
+    for _ in range(tail):
+        new = nxt + np.arange(heads.size)
+        src.append(heads)
+        dst.append(new)
+        heads, nxt = new, nxt + heads.size
+    src.append(kids[::11])
+    dst.append(np.full(kids[::11].size, 3))
+    s, d = np.concatenate(src), np.concatenate(dst)
+    perm = rng.permutation(nxt)  # ids in no order
+    g = graphgen.from_edges(nxt, perm[s], perm[d], rng.integers(1, 90, s.size), f"fan{width}")
+    return g, int(perm[0])
+
+
+def _cases():
+    yield "path", pins.path_graph(300, np.arange(1, 300) % 9), 0
+    for width in (1, 63, 64, 2047, 2048, 2049, 128 * 64, LIMIT - 1, LIMIT, LIMIT + 1):
+        yield (f"fan{width}", *_fan(width, salt=width))
+    for n, k in ((7, 1), (129, 3), (5000, 8), (40000, 5), (90001, 11)):
+        yield f"uniform{n}x{k}", graphgen.uniform(n=n, k=k, salt=n), 1
+    yield "grid150", graphgen.grid(150, 97, shortcut_frac=0), 60
+    yield "rmat14", graphgen.rmat(14), int(graphgen.sources(graphgen.rmat(14), 1, graphgen.FAMILY_RMAT)[0])
+
+
+CASES = list(_cases())
+
+
+@pytest.mark.parametrize("limit", [-1, 2, 700, 33000])
+@pytest.mark.parametrize("wide", [0, 1])
+def test_team_levels(limit, wide):
+    """limit: levels of at least so many arcs leave the team (-1: the
+    default, LIMIT + 1); 33000 lies just above the size up to which every
+    arc issues its atomic without reading first."""
+    lbg.set_bfs_scan_min(limit)
+    lbg.set_addressing(wide)
+    ws = lbg.Workspace()
+    for name, g, s in CASES:
+        dg = lbg.DeviceGraph.from_numpy(g.offsets, g.cols, g.weights)
+        exp_l = O.bfs(g.offsets, g.cols, s)
+        exp_d = O.dijkstra(g.offsets, g.cols, g.weights, s)
+        got, st = lbg.bfs(dg, s, workspace=ws, stats=True)
+        assert np.array_equal(got.cpu().numpy(), exp_l), (name, "bfs")
+        reached = exp_l != pins.BFS_INF
+        assert st["updates"] == int(reached.sum()) - 1, (name, st)
+        assert st["edges_scanned"] == g.reached_arcs(reached), (name, st)
+        for kw in ({}, {"packed": True}, {"ordered": True}):
+            d = lbg.sssp(dg, s, workspace=ws, **kw).cpu().numpy().view(np.uint32)
+            assert np.array_equal(d, exp_d), (name, "sssp", kw)
+
+
+def test_team_limit_boundary():
+    """A level of exactly LIMIT arcs runs in the team, one arc more does not."""
+    for width, one_level in ((LIMIT, 0), (LIMIT + 1, 1)):
+        g, s = _fan(width, tail=0)
+        dg = lbg.DeviceGraph.from_numpy(g.offsets, g.cols, g.weights)
+        lbg.profile_enable(True, reset=True)
+        lv = lbg.bfs(dg, s)
+        lbg.profile_enable(False, reset=False)
+        assert np.array_equal(lv.cpu().numpy(), O.bfs(g.offsets, g.cols, s))
+        assert lbg.profile_read("bfs_small")["launches"] >= 1
+        assert (lbg.profile_read("bfs")["launches"] > 0) == bool(one_level), width
+
+
+def test_teams_side_by_side():
+    """Solves from several threads and streams at once: teams come together
+    with whatever workgroups are scheduled, and every result is exact."""
+    import threading
+
+    g = graphgen.grid(400, 300, shortcut_frac=0)
+    h = graphgen.uniform(15)
+    jobs = [(g, 5), (h, 9), (g, 70000), (h, 1)]
+    exp = [(O.bfs(x.offsets, x.cols, s), O.dijkstra(x.offsets, x.cols, x.weights, s)) for x, s in jobs]
+    dgs = {id(x): lbg.DeviceGraph.from_numpy(x.offsets, x.cols, x.weights) for x in (g, h)}
+    bad = []
+
+    def work(k):
+        try:
+            x, s = jobs[k]
+            st = torch.cuda.Stream()
+            ws = lbg.Workspace()
+            for _ in range(4):
+                lv = lbg.bfs(dgs[id(x)], s, workspace=ws, stream=st)
+                d = lbg.sssp(dgs[id(x)], s, workspace=ws, stream=st)
+                st.synchronize()
+                if not np.array_equal(lv.cpu().numpy(), exp[k][0]):
+                    bad.append((k, "bfs"))
+                if not np.array_equal(d.cpu().numpy().view(np.uint32), exp[k][1]):
+                    bad.append((k, "sssp"))
+        except Exception as e:  # reported below
+            bad.append(repr(e))
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(len(jobs))]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join(100)
+    assert not any(t.is_alive() for t in ts)
+    assert not bad, bad
