@@ -65,7 +65,7 @@ int32_t resolve(int32_t s) { return s == LBG_AUTO ? LBG_BALANCED : s; }
 
 // Workspace layout.  All offsets 256-byte aligned.
 struct Layout {
-  size_t ctl, team, visited, seen[2], xfilter, dstate, d16, node[2], eprefix[2], estart[2], tile[2], sub[2],
+  size_t ctl, visited, seen[2], xfilter, dstate, d16, node[2], eprefix[2], estart[2], tile[2], sub[2],
       hier_trace, total;
   uint32_t node_cap, tile_cap, edge_cap;
 };
@@ -82,7 +82,6 @@ Layout layout(int32_t n, int64_t m, int32_t strategy, int is_sssp, int64_t child
     return at;
   };
   L.ctl = take(sizeof(Ctl));
-  if (s == LBG_BALANCED) L.team = take(sizeof(lbg::TeamCtl));
   const size_t words = (static_cast<size_t>(n) + 31) / 32;
   if (is_sssp) {
     L.dstate = take(sizeof(unsigned long long) * static_cast<size_t>(n));
@@ -116,8 +115,6 @@ Layout layout(int32_t n, int64_t m, int32_t strategy, int is_sssp, int64_t child
     if (s == LBG_BINNED) extra = m / lbg::kMinMdt + 1;
     if (s == LBG_SPLIT) extra = children < 0 ? m : children;
     L.node_cap = static_cast<uint32_t>(n + extra);
-    // the small-frontier team keeps one segment of entries per workgroup
-    if (s == LBG_BALANCED) L.node_cap = std::max(L.node_cap, lbg::kTeamE);
     L.tile_cap = static_cast<uint32_t>((m + lbg::kMinTile - 1) / lbg::kMinTile + 2);
     for (int b = 0; b < 2; ++b) {
       L.node[b] = take(sizeof(int32_t) * static_cast<size_t>(L.node_cap));
@@ -413,7 +410,17 @@ int solve(const Problem& P) {
   }
   if (strat == LBG_HIER) a.hier_trace = reinterpret_cast<uint32_t*>(ws + Lay.hier_trace);
   a.ctl = reinterpret_cast<Ctl*>(ws + Lay.ctl);
-  if (strat == LBG_BALANCED) a.team = reinterpret_cast<lbg::TeamCtl*>(ws + Lay.team);
+  if (strat == LBG_BALANCED) {
+    // the team's control words follow the control block; its flags lie in an
+    // array that levels run by the team leave alone (BFS worklists store no
+    // node ids, SSSP results are written at the end; results need not be
+    // 8-byte aligned)
+    a.team = reinterpret_cast<lbg::TeamCtl*>(ws + Lay.ctl + sizeof(Ctl));
+    a.tblocks = std::clamp<uint32_t>(static_cast<uint32_t>(P.n) / lbg::kTeamNodes, 1u, lbg::kTeamMax);
+    if (a.tblocks <= lbg::kTeamFew) a.tflag = a.team->flag;
+    else a.tflag = reinterpret_cast<unsigned long long*>(
+        P.is_sssp ? (reinterpret_cast<uintptr_t>(P.out) + 7) / 8 * 8 : reinterpret_cast<uintptr_t>(ws + Lay.node[0]));
+  }
   a.n = static_cast<uint32_t>(P.n);
   a.m = static_cast<uint32_t>(P.m);
   a.words = static_cast<uint32_t>((static_cast<size_t>(P.n) + 31) / 32);
@@ -423,7 +430,7 @@ int solve(const Problem& P) {
   a.scan_min = 0xffffffffu;
   // levels of at most this many arcs run in the small-frontier team; a level
   // that a caller's threshold makes a scan level does not
-  uint32_t team_limit = strat == LBG_BALANCED ? lbg::kTeamE : 0u;
+  uint32_t team_limit = strat == LBG_BALANCED ? a.tblocks * lbg::kTeamSlots : 0u;
   if (!P.is_sssp && strat == LBG_BALANCED) {
     int64_t smin;
     {
@@ -628,7 +635,7 @@ int solve(const Problem& P) {
     if (profiling && (rc = mark()) != LBG_OK) return rc;  // the batch's first interval starts here
     if (small) {
       const uint32_t max_levels = static_cast<uint32_t>(std::min<uint64_t>(level_cap + 1 - L, 0xffffffffu));
-      const dim3 tg(lbg::kTeamMax), tb(lbg::kTeamBlock);
+      const dim3 tg(a.tblocks), tb(lbg::kTeamBlock);
       if (P.is_sssp && packed) {
         if (narrow) hipLaunchKernelGGL((lbg::k_expand_team<true, true, true>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
         else hipLaunchKernelGGL((lbg::k_expand_team<true, false, true>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
@@ -1316,10 +1323,7 @@ namespace {
 // ends.  Host code never passes the array's name to a kernel or a copy (on
 // the host it only stands in for the symbol); it uses the device address
 // hipGetSymbolAddress gives, looked up once per device.
-// kNoallocTeam: the small-frontier team's control words (balanced solves) come
-// on top of the 64 MiB that the sizes a call accepts are counted against.
-constexpr size_t kNoallocTeam = (sizeof(lbg::TeamCtl) + 255) / 256 * 256;
-static __device__ __align__(256) unsigned char scratch[LBG_NOALLOC_SCRATCH_BYTES + kNoallocTeam];
+static __device__ __align__(256) unsigned char scratch[LBG_NOALLOC_SCRATCH_BYTES];
 
 namespace {
 
@@ -1377,16 +1381,15 @@ int lbg_sssp_noalloc(const int32_t* offsets, const int32_t* cols, const uint32_t
                             "(got %d)", strategy);
   if (n > 0 && m >= 0 && m <= INT32_MAX) {
     const size_t need = layout(n, m, strategy, 1).total;
-    const size_t most = LBG_NOALLOC_SCRATCH_BYTES + (s == LBG_BALANCED ? kNoallocTeam : 0);
-    if (need > most)
+    if (need > LBG_NOALLOC_SCRATCH_BYTES)
       return fail(LBG_ENOMEM, "lbg_sssp_noalloc: n = %d, m = %lld need %zu bytes of scratch, above its "
                   "maximum of %zu", n, static_cast<long long>(m), need,
-                  most);
+                  static_cast<size_t>(LBG_NOALLOC_SCRATCH_BYTES));
   }
   void* ws = nullptr;
   const int rc = noalloc_scratch(&ws);
   if (rc) return rc;
-  Problem P{offsets, cols, weights, nullptr, n, m, src, dist_out, ws, sizeof(scratch),
+  Problem P{offsets, cols, weights, nullptr, n, m, src, dist_out, ws, LBG_NOALLOC_SCRATCH_BYTES,
             strategy, 1, stats, static_cast<hipStream_t>(stream)};
   P.no_alloc = true;
   return solve(P);

@@ -72,21 +72,27 @@ struct Ctl {
 static_assert(sizeof(Ctl) == 128 + kXcds * 128, "Ctl layout");
 
 // The team of the small-frontier kernel (lbg_team.hpp): at most kTeamMax
-// workgroups, kTeamSlots arcs of a level each.
+// workgroups, kTeamSlots arcs of a level each, one workgroup per kTeamNodes
+// nodes of the graph.
 constexpr uint32_t kTeamMax = 128;
 constexpr uint32_t kTeamSlots = 2048;
+constexpr uint32_t kTeamNodes = 256;
 constexpr uint32_t kTeamE = kTeamMax * kTeamSlots;  // arcs of a level run there
-// Its control words, in the workspace, zeroed by k_init.  join[] / size[] are
-// used by launch number seq of a solve at seq % 4 and cleared two launches
-// ahead.  flag[e % 2][w]: workgroup w's word of exchange e, (e << 34) | payload.
+// Its control words, zeroed by k_init, in the bytes between the control block
+// and the next 256-byte boundary.  join[] / size[] are used by launch number
+// seq of a solve at seq % 4 and cleared two launches ahead.  The workgroups'
+// flags (KArgs::tflag) are here for up to kTeamFew of them, else in an array
+// the solve does not use meanwhile: workgroup w's word of exchange e is
+// tflag[(e % 2) * workgroups + w] = (e << 34) | payload.
+constexpr uint32_t kTeamFew = 4;
 struct TeamCtl {
   uint32_t join[4];
   uint32_t size[4];
   uint32_t epoch;  // exchanges so far in this solve
-  uint32_t pad[23];
-  unsigned long long flag[2][kTeamMax];
+  uint32_t pad;
+  unsigned long long flag[2 * kTeamFew];
 };
-constexpr uint32_t kTeamWords = sizeof(TeamCtl) / sizeof(uint32_t);
+static_assert(sizeof(TeamCtl) <= 128 && sizeof(Ctl) + 128 <= 1280, "fits between the control block and 1280");
 
 // One worklist (frontier) buffer.  For node worklists entry i holds the node,
 // the position of its first edge in this level's edge space (strictly
@@ -124,6 +130,8 @@ struct KArgs {
   int32_t* sub[2];       // hierarchical strategy: sublists (worklist indices) of two sub-iterations
   Ctl* ctl;
   TeamCtl* team;         // balanced strategy: the small-frontier team (else null)
+  unsigned long long* tflag;  // its flags, 2 x tblocks
+  uint32_t tblocks;      // workgroups it is launched with
   uint32_t n;
   uint32_t m;
   uint32_t words;        // (n + 31) / 32

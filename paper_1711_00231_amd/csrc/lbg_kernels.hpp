@@ -265,7 +265,9 @@ __device__ __forceinline__ void init_state(const KArgs& a, int32_t src, uint32_t
     if (kSssp) {
       a.dstate[v] = (v == static_cast<uint32_t>(src)) ? 0ull
                                                       : (static_cast<unsigned long long>(kSsspInf) << 32);
-      a.dist[v] = (v == static_cast<uint32_t>(src)) ? 0u : kSsspInf;
+      // the balanced strategy keeps the team's flags in the output until
+      // k_sssp_finish writes it
+      if (!a.team) a.dist[v] = (v == static_cast<uint32_t>(src)) ? 0u : kSsspInf;
       a.d16[v] = (v == static_cast<uint32_t>(src)) ? 0 : static_cast<uint16_t>(kF16None);
     } else {
       a.levels[v] = (v == static_cast<uint32_t>(src)) ? 0 : static_cast<int32_t>(kBfsInf);
@@ -310,8 +312,10 @@ __global__ __launch_bounds__(kBlock) void k_init(KArgs a, int32_t src) {
     return;
   }
   init_state<kSssp>(a, src, gid, stride);
-  if (a.team)
-    for (uint32_t k = gid; k < kTeamWords; k += stride) reinterpret_cast<uint32_t*>(a.team)[k] = 0u;
+  if (a.team) {
+    if (gid < sizeof(TeamCtl) / 4) reinterpret_cast<uint32_t*>(a.team)[gid] = 0u;
+    for (uint32_t k = gid; k < 2 * a.tblocks; k += stride) a.tflag[k] = 0ull;
+  }
   if (a.hier_trace)
     for (uint32_t k = gid; k < kHierTraceLevels * kHierTraceSubs; k += stride) a.hier_trace[k] = 0u;
   const int32_t s0 = a.offsets[src];

@@ -16,8 +16,8 @@
 // whole L2s and cost about 30 us per level (measured), which is as slow as
 // one launch per level.  Against one workgroup with the frontier in its LDS
 // (levels of at most 16 K arcs) and one-level launches for the rest: a solve
-// of a 16 K-node uniform graph went from 194 to 98 us (BFS) and from 309 to
-// 164 us (SSSP), BFS of the 2048 x 2048 grid with shortcuts from 1.71 to
+// of a 16 K-node uniform graph went from 194 to 92 us (BFS) and from 311 to
+// 179 us (SSSP), BFS of the 2048 x 2048 grid with shortcuts from 1.71 to
 // 1.24 ms.
 //
 // Membership: a workgroup joins by an atomic on join[]; the first one closes
@@ -93,21 +93,26 @@ struct TeamLds {
   int32_t node[kSssp ? 2 * kTeamSlots : 1];      // entry i's node
   uint32_t flag[kTeamSlots / 32];                // bit s: an entry starts at slot s
   uint32_t lead;                                 // the entry that holds slot 0
+  uint32_t ppre[kTeamSlots];                     // pushes: arcs of the pushes before,
+  int32_t pst[kTeamSlots];                       //   first arc,
+  int32_t pnode[kSssp ? kTeamSlots : 1];         //   node
   unsigned long long push;                       // (entries << 32) | arcs pushed so far
   uint32_t me, size, ok;
+  uint32_t over;                                 // some workgroup's pushes outgrew its segment
 };
 
 // Exchange number e: wave 0 raises this workgroup's flag, waits for every
 // member's and leaves the prefix sums of their payloads in segn / sege:
-// (entries << 21 | arcs) or, kArcsOnly, arcs alone (segn is kept).  Must be
-// reached by the whole workgroup after its stores have been waited for and
-// a barrier; ends with one.
+// (entries << 21 | arcs) or, kArcsOnly, arcs alone (segn is kept); over says
+// whether a workgroup has more than seg entries.  Must be reached by the
+// whole workgroup after its stores have been waited for and a barrier; ends
+// with one.
 template <bool kSssp, bool kArcsOnly>
 __device__ __forceinline__ bool team_exchange(const KArgs& a, TeamLds<kSssp>& sm, uint32_t e, uint32_t me,
-                                              uint32_t size, unsigned long long payload) {
+                                              uint32_t size, uint32_t seg, unsigned long long payload) {
   if (threadIdx.x < 64) {
     const uint32_t lane = threadIdx.x;
-    unsigned long long* f = a.team->flag[e & 1];
+    unsigned long long* f = a.tflag + (e & 1) * a.tblocks;
     if (lane == 0) st_agent(&f[me], (static_cast<unsigned long long>(e) << 34) | payload);
     const unsigned long long t0 = wall_clock64();
     unsigned long long v[2];
@@ -124,6 +129,7 @@ __device__ __forceinline__ bool team_exchange(const KArgs& a, TeamLds<kSssp>& sm
       if (!ok && (spin & 1023u) == 0u && wall_clock64() - t0 > kTeamPatience) break;
     }
     uint32_t cn = 0, ce = 0;
+    bool over = false;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const uint32_t q = h * 64 + lane;
@@ -133,12 +139,15 @@ __device__ __forceinline__ bool team_exchange(const KArgs& a, TeamLds<kSssp>& sm
       ce += __shfl(ie, 63, 64);
       if (!kArcsOnly) {
         const uint32_t xn = static_cast<uint32_t>(v[h] >> 21) & 0x1fffu;
+        over = over || xn > seg;
         const uint32_t in = wave_incl_scan(xn);
         sm.segn[q + 1] = cn + in;
         cn += __shfl(in, 63, 64);
       }
     }
+    over = __any(over);
     if (lane == 0) {
+      if (!kArcsOnly) sm.over = over ? 1u : 0u;
       sm.sege[0] = 0u;
       if (!kArcsOnly) sm.segn[0] = 0u;
       sm.ok = ok ? 1u : 0u;
@@ -154,11 +163,15 @@ __device__ __forceinline__ bool team_exchange(const KArgs& a, TeamLds<kSssp>& sm
 // in the one-level kernels' worklist format and the host continues from
 // ctl->levels.  Level L0 comes in that format (at most `limit` arcs and
 // kTeamE entries, or nothing is done); later levels live as one segment of
-// entries per workgroup, segment q of level L at q * kTeamSlots of the
-// arrays of buffer (L + 1) & 1 (estart, node; eprefix counts from the
-// segment's start), with the segments' sizes exchanged in the flags.  A
-// level's arcs are cut evenly: workgroup w takes arcs [w C, (w + 1) C), so a
-// hub is shared by many workgroups and no segment outgrows C <= kTeamSlots.
+// entries per workgroup, segment q of level L at q * seg of the arrays of
+// buffer (L + 1) & 1 (estart, node; eprefix counts from the segment's start),
+// with the segments' sizes exchanged in the flags.  A level's arcs are cut
+// evenly: workgroup w takes arcs [w C, (w + 1) C), so a hub is shared by many
+// workgroups and none pushes more than C <= kTeamSlots entries; they are kept
+// in LDS as well.  The arrays hold n entries in all, so with fewer than
+// kTeamE nodes a workgroup's pushes may outgrow its segment; then the level
+// is written in the one-level format from the LDS copies, once the counts
+// are known (one more exchange).
 template <bool kSssp, bool kNarrow, bool kPacked = false>
 __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t L0, uint32_t seq, uint32_t limit,
                                                             uint32_t max_levels) {
@@ -178,6 +191,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t L0
   const uint32_t me = sm.me, P = min(sm.size, kTeamMax);
   if (me >= P) return;
   limit = min(limit, P * kTeamSlots);
+  const uint32_t seg = min(kTeamSlots, a.node_cap / gridDim.x);  // entries of a segment
   if (E > limit) return;  // a small team: the host goes on with one-level launches
 
   uint32_t e = a.team->epoch;
@@ -187,7 +201,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t L0
   if (tid <= P) {
     const uint32_t i = min(tid * stride, nf);
     sm.segn[tid] = i;
-    sm.sege[tid] = i < nf ? *at<kNarrow>(a.fr[L0 & 1].eprefix, i) : E;
+    sm.sege[tid] = i < nf ? ld_agent(at<kNarrow>(a.fr[L0 & 1].eprefix, i)) : E;
   }
   if (tid < kTeamSlots / 32) sm.flag[tid] = 0u;
   if (tid == 0) sm.push = 0ull;
@@ -246,7 +260,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t L0
     if (contiguous) {
       // pushes reuse this level's arrays: everyone has to have read them
       ++e;
-      alive = team_exchange<kSssp, false>(a, sm, e, me, P, 0ull);
+      alive = team_exchange<kSssp, false>(a, sm, e, me, P, seg, 0ull);
       if (!alive) break;
     }
     if (lo < hi) {
@@ -377,13 +391,19 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t L0
         b = bcast64(b, 63);
         if (put) {
           const uint32_t k = static_cast<uint32_t>(b >> 32) + lane_rank(mask);
+          const uint32_t p = static_cast<uint32_t>(b) + inc - static_cast<uint32_t>(d);
           if (k < kTeamSlots) {
-            const uint32_t to = me * kTeamSlots + k;
-            st_agent(at<kNarrow>(nxt.eprefix, to), static_cast<uint32_t>(b) + inc - static_cast<uint32_t>(d));
-            st_agent(at<kNarrow>(nxt.estart, to), s0[r]);
-            if (kSssp) st_agent(at<kNarrow>(nxt.node, to), vv[r]);
+            sm.ppre[k] = p;
+            sm.pst[k] = s0[r];
+            if (kSssp) sm.pnode[k] = vv[r];
           } else {
             bad = true;
+          }
+          if (k < seg) {
+            const uint32_t to = me * seg + k;
+            st_agent(at<kNarrow>(nxt.eprefix, to), p);
+            st_agent(at<kNarrow>(nxt.estart, to), s0[r]);
+            if (kSssp) st_agent(at<kNarrow>(nxt.node, to), vv[r]);
           }
         }
       }
@@ -394,34 +414,57 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t L0
     if (tid < kTeamSlots / 32) sm.flag[tid] = 0u;
     ++e;
     alive = team_exchange<kSssp, false>(
-        a, sm, e, me, P,
+        a, sm, e, me, P, seg,
         (min(pushed >> 32, 0x1fffull) << 21) | min(pushed & 0xffffffffull, 0x1fffffull));
     if (!alive) break;
     if (tid == 0) sm.push = 0ull;  // everyone has read it; the next pushes follow a barrier
     contiguous = false;
-    stride = kTeamSlots;
+    stride = seg;
     ++L;
     nf = sm.segn[P];
     E = sm.sege[P];
     if (E == 0u) break;
-    if (E > limit || L - L0 >= max_levels) {
-      // hand level L over: exact arc counts, then entries, prefixes, marks
+    const bool leave = E > limit || L - L0 >= max_levels;
+    if (!leave && !sm.over) continue;
+    // Level L in the one-level format, to go on there (exact arc counts
+    // first, then entries, prefixes and marks) or here.
+    if (leave) {
+      __syncthreads();  // the prefixes are read before the next exchange writes them
       ++e;
-      alive = team_exchange<kSssp, true>(a, sm, e, me, P, pushed & 0xffffffffull);
+      alive = team_exchange<kSssp, true>(a, sm, e, me, P, seg, pushed & 0xffffffffull);
       if (!alive) break;
       E = sm.sege[P];
-      const Frontier seg = a.fr[(L + 1) & 1], out = a.fr[L & 1];
-      const uint32_t cnt = sm.segn[me + 1] - sm.segn[me], eb = sm.sege[me];
-      for (uint32_t k = tid; k < cnt; k += kTeamBlock) {
-        const uint32_t from = me * kTeamSlots + k;
-        const uint32_t p = ld_agent(at<kNarrow>(seg.eprefix, from));
-        const uint32_t pn = k + 1 < cnt ? ld_agent(at<kNarrow>(seg.eprefix, from + 1)) : sm.sege[me + 1] - eb;
-        write_entry<kPay, T, kNarrow>(a, out, sm.segn[me] + k, eb + p,
-                                      kSssp ? ld_agent(at<kNarrow>(seg.node, from)) : 0, 0,
-                                      ld_agent(at<kNarrow>(seg.estart, from)), static_cast<int32_t>(pn - p));
-      }
-      break;
     }
+    const Frontier out = a.fr[L & 1];
+    const uint32_t cnt = static_cast<uint32_t>(pushed >> 32), nb = sm.segn[me], eb = sm.sege[me];
+    for (uint32_t k = tid; k < min(cnt, kTeamSlots); k += kTeamBlock) {
+      const uint32_t p = sm.ppre[k];
+      if (leave) {
+        const uint32_t pn = k + 1 < cnt ? sm.ppre[k + 1] : static_cast<uint32_t>(pushed);
+        write_entry<kPay, T, kNarrow>(a, out, nb + k, eb + p, kSssp ? sm.pnode[k] : 0, 0, sm.pst[k],
+                                      static_cast<int32_t>(pn - p));
+      } else if (nb + k < a.node_cap) {
+        st_agent(at<kNarrow>(out.eprefix, nb + k), eb + p);
+        st_agent(at<kNarrow>(out.estart, nb + k), sm.pst[k]);
+        if (kSssp) st_agent(at<kNarrow>(out.node, nb + k), sm.pnode[k]);
+      } else {
+        bad = true;
+      }
+    }
+    if (leave) break;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    ++e;
+    alive = team_exchange<kSssp, false>(a, sm, e, me, P, seg, 0ull);
+    if (!alive) break;
+    contiguous = true;
+    stride = (nf + P - 1) / P;
+    if (tid <= P) {
+      const uint32_t i = min(tid * stride, nf);
+      sm.segn[tid] = i;
+      sm.sege[tid] = i < nf ? ld_agent(at<kNarrow>(out.eprefix, i)) : E;
+    }
+    __syncthreads();
   }
   if (__any(bad) && lane == 0) atomicOr(&a.ctl->error, kErrBadArc);
   // Bookkeeping of every level run here, then the tail of level L (the next
