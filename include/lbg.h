@@ -161,7 +161,7 @@ int lbg_bfs(const int32_t* offsets, const int32_t* cols, int32_t n, int64_t m, i
  * levels array builds the next worklist from the nodes of the new level, in
  * node order.  Smaller levels claim and push as before.  Results are the
  * same either way.  arcs < 0 (the default): n / 4 for a graph of n nodes,
- * of the levels too large for the small-frontier kernel (more than 262144
+ * of the levels too large for the small-frontier kernel (more than 524288
  * arcs); 0: every level; >= 2^32: never.  Process-wide, read when a solve starts;
  * lbg_get_bfs_scan_min returns the setting (-1 for the default).  Always
  * LBG_OK. */
@@ -485,7 +485,7 @@ typedef struct {
  * (which = 0), SSSP solves (1) or batched solves (2), and of the
  * small-frontier launches of BFS (3) and SSSP (4) solves (the level loop
  * on the device that balanced solves start in and return to while a level
- * has at most 262144 arcs; `launches` counts launches, the work counters
+ * has at most 524288 arcs; `launches` counts launches, the work counters
  * cover every level they ran, empty_* stay 0). */
 void lbg_profile_read(int32_t which, lbg_profile* out);
 

@@ -163,6 +163,7 @@ struct Grids {
   int bal[2][2], node[2], edge[2], edge_nc[2], multi[2], binned[2], hier[2];  // bal[is_sssp][narrow], multi[narrow]
   int sliced[2][2];                                      // [is_sssp][narrow], a multiple of 8 (>= 8)
   int bal_p[2];                                          // SSSP with packed arcs [narrow]
+  int far[2][2];                                         // near-far SSSP [packed][narrow]
   int bal_s[2][2];                                       // split graph [is_sssp][narrow]
 };
 
@@ -196,6 +197,10 @@ const Grids& grids() {
     g[dev].multi[1] = resident_grid(lbg::k_expand_balanced<true, true, true>);
     g[dev].bal_p[0] = resident_grid(lbg::k_expand_balanced<true, false, false, true>);
     g[dev].bal_p[1] = resident_grid(lbg::k_expand_balanced<true, true, false, true>);
+    g[dev].far[0][0] = resident_grid(lbg::k_expand_balanced<true, false, false, false, false, true>);
+    g[dev].far[0][1] = resident_grid(lbg::k_expand_balanced<true, true, false, false, false, true>);
+    g[dev].far[1][0] = resident_grid(lbg::k_expand_balanced<true, false, false, true, false, true>);
+    g[dev].far[1][1] = resident_grid(lbg::k_expand_balanced<true, true, false, true, false, true>);
     g[dev].bal_s[0][0] = resident_grid(lbg::k_expand_balanced<false, false, false, false, true>);
     g[dev].bal_s[0][1] = resident_grid(lbg::k_expand_balanced<false, true, false, false, true>);
     g[dev].bal_s[1][0] = resident_grid(lbg::k_expand_balanced<true, false, false, false, true>);
@@ -238,20 +243,25 @@ struct PinnedCtl {
   }
 };
 thread_local PinnedCtl g_pinned;
-// Level count of this thread's previous single solve, per kind (BFS, SSSP),
-// or 0 when it used the small-frontier kernel: repeated solves on one graph
-// enqueue that many levels in the first batch, so a typical solve needs one
-// read-back and few empty launches.
-thread_local uint32_t g_level_hint[2] = {0u, 0u};
+// One-level launches that had work in the first submission of this thread's
+// previous balanced solve, plus one, per kind (BFS, SSSP): the next solve
+// enqueues that many, so a typical solve needs one read-back and few empty
+// launches.
+thread_local uint32_t g_big_hint[2] = {0u, 0u};
+// Balanced solves of graphs of at most this many arcs read back after their
+// first team launch instead of enqueueing one-level launches behind it: most
+// are done by then (an empty launch costs 2 us, a read-back about 15).
+constexpr uint32_t kTeamDense = 512;  // arcs per team workgroup, see solve()
+constexpr int64_t kSmallGraph = int64_t{2} << 20;
 
-// Balanced BFS: the levels that ran in scan mode in this thread's solves of
+// Balanced BFS: the launches that ran in scan mode in this thread's solves of
 // a graph (keyed by offsets pointer, n, m), accumulated since the last
-// re-check.  A later solve lets only those levels and their neighbours scan,
+// re-check.  A later solve lets only those launches and their neighbours scan,
 // and launches the compaction kernel only after them, so graphs whose levels
 // never reach the threshold stop paying for compaction launches that would
 // find nothing to do (~2 us each).  A graph not in the table, and every 16th
 // solve of one that is (the re-check, which restarts the record), may scan
-// at any level.  Sources whose big levels lie elsewhere only lose speed: a
+// in any launch.  Sources whose big levels lie elsewhere only lose speed: a
 // level that may not scan claims and pushes.
 struct ScanHint {
   const void* off = nullptr;
@@ -373,6 +383,16 @@ int check_common(const Problem& P) {
   return LBG_OK;
 }
 
+// Whether an SSSP solve defers nodes beyond a threshold (near_far_init).  Not
+// above 16 arcs per node: the skewed graphs measured there lose as much to
+// the extra iterations as they gain (R-MAT scale 20, 30 arcs per node, host
+// emulation with the measured rates: 1.55 ms at best against 1.76 ms, before
+// the one-level kernel's own skipping of improved entries, which saves more).
+// Not below 2^20 arcs: there every level is latency and a level saved is worth
+// more than the arcs (uniform graph of 2^14 nodes: 20 iterations, 24 with the
+// best step).
+bool near_far(int32_t n, int64_t m) { return m >= (int64_t{1} << 20) && m <= 16 * static_cast<int64_t>(n); }
+
 int solve(const Problem& P) {
   int rc = check_common(P);
   if (rc) return rc;
@@ -424,6 +444,8 @@ int solve(const Problem& P) {
   a.n = static_cast<uint32_t>(P.n);
   a.m = static_cast<uint32_t>(P.m);
   a.words = static_cast<uint32_t>((static_cast<size_t>(P.n) + 31) / 32);
+  if (P.is_sssp && strat == LBG_BALANCED && near_far(P.n, P.m))
+    a.far = reinterpret_cast<uint32_t*>(a.tflag + 2 * a.tblocks);  // n / 32 of the output's n words
   a.node_cap = Lay.node_cap;
   a.tile_cap = Lay.tile_cap;
   a.edge_cap = Lay.edge_cap;
@@ -444,6 +466,11 @@ int solve(const Problem& P) {
     else team_limit = static_cast<uint32_t>(std::min<int64_t>(team_limit, smin > 0 ? smin - 1 : 0));
     a.scan_min = static_cast<uint32_t>(std::min<int64_t>(smin, 0xffffffffll));
   }
+  // SSSP of dense graphs (skewed ones, mostly): the one-level kernel passes over
+  // entries that improve again while they are expanded, which saves more than
+  // the team's shorter steps from 64 K arcs on (R-MAT 15: 0.296 against
+  // 0.315 ms with the full limit)
+  if (P.is_sssp && P.m > 16 * static_cast<int64_t>(P.n)) team_limit = std::min(team_limit, a.tblocks * kTeamDense);
   // a level can only run in scan mode if the graph has that many arcs
   const bool scan_possible = static_cast<int64_t>(a.scan_min) <= P.m;
   ScanHint* shint = nullptr;
@@ -457,8 +484,8 @@ int solve(const Problem& P) {
   }
   const bool scan_any = scan_possible && shint->uses % 16u == 0u;  // unknown, or a periodic re-check
   const uint64_t scan_near = scan_possible ? (shint->mask | (shint->mask << 1) | (shint->mask >> 1)) : 0ull;
-  auto scan_at = [&](uint32_t L) {
-    return scan_possible && (scan_any || (L < 64u && ((scan_near >> L) & 1ull)));
+  auto scan_at = [&](uint32_t k) {
+    return scan_possible && (scan_any || (k < 64u && ((scan_near >> k) & 1ull)));
   };
   const int compact_blocks = static_cast<int>(
       std::max<int64_t>(1, std::min<int64_t>((static_cast<int64_t>(P.n) + lbg::kCompactChunk - 1) / lbg::kCompactChunk,
@@ -560,7 +587,16 @@ int solve(const Problem& P) {
           else hipLaunchKernelGGL((lbg::k_expand_balanced<true, false, false, false, true>), dim3(GR.bal_s[sv][nw]), dim3(lbg::kBlock), 0, st, a, L);
           break;
         default:
-          if (packed) {
+          if (a.far) {
+            const dim3 fg(GR.far[packed ? 1 : 0][nw]), fb(lbg::kBlock);
+            if (packed) {
+              if (narrow) hipLaunchKernelGGL((lbg::k_expand_balanced<true, true, false, true, false, true>), fg, fb, 0, st, a, L);
+              else hipLaunchKernelGGL((lbg::k_expand_balanced<true, false, false, true, false, true>), fg, fb, 0, st, a, L);
+            } else {
+              if (narrow) hipLaunchKernelGGL((lbg::k_expand_balanced<true, true, false, false, false, true>), fg, fb, 0, st, a, L);
+              else hipLaunchKernelGGL((lbg::k_expand_balanced<true, false, false, false, false, true>), fg, fb, 0, st, a, L);
+            }
+          } else if (packed) {
             if (narrow) hipLaunchKernelGGL((lbg::k_expand_balanced<true, true, false, true>), dim3(GR.bal_p[nw]), dim3(lbg::kBlock), 0, st, a, L);
             else hipLaunchKernelGGL((lbg::k_expand_balanced<true, false, false, true>), dim3(GR.bal_p[nw]), dim3(lbg::kBlock), 0, st, a, L);
           } else if (narrow) {
@@ -608,62 +644,90 @@ int solve(const Problem& P) {
     }
   };
 
-  // Level loop.  One-level launches are enqueued in batches (each launch
-  // reads its own work size on the device) and the host reads the control
-  // block once per batch.  When the next level is small (at most kSmallF
-  // entries and kSmallE edges) the balanced strategy hands the following
-  // levels to the single-workgroup kernel, which keeps going on the device
-  // until a level outgrows those limits or the worklist empties; the host
-  // then resumes from ctl->levels, the next level to expand.
+  // Level loop.  Launches are enqueued in submissions (each reads its own work
+  // size on the device) and the host reads the control block once per
+  // submission.  The balanced strategy's levels of at most team_limit arcs run
+  // in the small-frontier team, which keeps going on the device until a level
+  // outgrows it or the worklist empties; one-level launches run the others
+  // and leave a level to the team launched behind them once it is small
+  // enough.  So a solve of a skewed graph (small levels, a few big ones,
+  // small levels) is one submission.
   const bool small_ok = strat == LBG_BALANCED && team_limit > 0u;
-  uint32_t seq = 0;  // team launches so far
-  uint32_t L = 0, L_prev = 0;
-  const uint32_t hint = g_level_hint[P.is_sssp ? 1 : 0];
-  uint32_t batch = hint ? std::min<uint32_t>(std::max<uint32_t>(hint + 1, 8), 64) : 8;
-  bool small = small_ok, used_small = small_ok;
+  uint32_t L = 0, L_prev = 0;  // next level, known at a read-back
+  uint32_t k = 0;              // launches so far
+  uint32_t seq = 0;            // team launches among them
+  const int kind = P.is_sssp ? 1 : 0;
+  uint32_t batch = small_ok && g_big_hint[kind] ? std::min<uint32_t>(g_big_hint[kind], 16) : 8;
+  bool first = true, alone = false;
+  uint64_t ef = 1;
   size_t nev = 0;
   g_event_level.clear();
   g_event_end.clear();
-  const uint64_t level_cap = static_cast<uint64_t>(P.n) + 2;
+  // near-far: every level may be followed by a split, and thresholds that
+  // double find an empty far set at most 31 times more
+  const uint64_t level_cap = (static_cast<uint64_t>(P.n) + 2) * (a.far ? 2 : 1) + (a.far ? 64 : 0);
   auto mark = [&]() -> int {
     hipEvent_t e = event_at(nev++);
     if (!e) return fail(LBG_EHIP, "hipEventCreate failed");
     HIP_TRY(hipEventRecord(e, st));
     return LBG_OK;
   };
-  for (;;) {
-    if (profiling && (rc = mark()) != LBG_OK) return rc;  // the batch's first interval starts here
-    if (small) {
-      const uint32_t max_levels = static_cast<uint32_t>(std::min<uint64_t>(level_cap + 1 - L, 0xffffffffu));
-      const dim3 tg(a.tblocks), tb(lbg::kTeamBlock);
-      if (P.is_sssp && packed) {
-        if (narrow) hipLaunchKernelGGL((lbg::k_expand_team<true, true, true>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
-        else hipLaunchKernelGGL((lbg::k_expand_team<true, false, true>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
-      } else if (P.is_sssp) {
-        if (narrow) hipLaunchKernelGGL((lbg::k_expand_team<true, true>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
-        else hipLaunchKernelGGL((lbg::k_expand_team<true, false>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
-      } else {
-        if (narrow) hipLaunchKernelGGL((lbg::k_expand_team<false, true>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
-        else hipLaunchKernelGGL((lbg::k_expand_team<false, false>), tg, tb, 0, st, a, L, seq, team_limit, max_levels);
-      }
-      ++seq;
-      HIP_TRY(hipGetLastError());
-      if (profiling) {
-        if ((rc = mark()) != LBG_OK) return rc;
-        g_event_level.push_back(-1);
-        g_event_end.push_back(nev - 1);
-      }
+  auto launched = [&](int64_t what) -> int {  // ends this launch's interval and starts the next one's
+    HIP_TRY(hipGetLastError());
+    if (profiling) {
+      int r = mark();
+      if (r != LBG_OK) return r;
+      g_event_level.push_back(what);
+      g_event_end.push_back(nev - 1);
+    }
+    ++k;
+    return LBG_OK;
+  };
+  auto team = [&]() -> int {
+    const uint32_t max_levels = static_cast<uint32_t>(std::min<uint64_t>(level_cap + 1 - L, 0xffffffffu));
+    const dim3 tg(a.tblocks), tb(lbg::kTeamBlock);
+    if (P.is_sssp && packed) {
+      if (narrow) hipLaunchKernelGGL((lbg::k_expand_team<true, true, true>), tg, tb, 0, st, a, k, seq, team_limit, max_levels);
+      else hipLaunchKernelGGL((lbg::k_expand_team<true, false, true>), tg, tb, 0, st, a, k, seq, team_limit, max_levels);
+    } else if (P.is_sssp) {
+      if (narrow) hipLaunchKernelGGL((lbg::k_expand_team<true, true>), tg, tb, 0, st, a, k, seq, team_limit, max_levels);
+      else hipLaunchKernelGGL((lbg::k_expand_team<true, false>), tg, tb, 0, st, a, k, seq, team_limit, max_levels);
     } else {
-      for (uint32_t k = 0; k < batch; ++k, ++L) {
-        launch(L);
-        HIP_TRY(hipGetLastError());
-        if (profiling) {  // ends this launch's interval and starts the next one's
-          if ((rc = mark()) != LBG_OK) return rc;
-          g_event_level.push_back(L);
-          g_event_end.push_back(nev - 1);
+      if (narrow) hipLaunchKernelGGL((lbg::k_expand_team<false, true>), tg, tb, 0, st, a, k, seq, team_limit, max_levels);
+      else hipLaunchKernelGGL((lbg::k_expand_team<false, false>), tg, tb, 0, st, a, k, seq, team_limit, max_levels);
+    }
+    ++seq;
+    return launched(-1);
+  };
+  uint64_t ones = 0;  // the submission's one-level launches, by k % 64
+  auto one_level = [&](uint32_t count) -> int {
+    for (uint32_t i = 0; i < count; ++i) {
+      ones |= 1ull << (k & 63);
+      launch(k);
+      const int r = launched(k);
+      if (r != LBG_OK) return r;
+    }
+    return LBG_OK;
+  };
+  for (;;) {
+    const uint32_t k_first = k;
+    ones = 0;
+    if (profiling && (rc = mark()) != LBG_OK) return rc;  // the submission's first interval starts here
+    if (!small_ok || alone) {
+      a.min_arcs = 0u;
+      if ((rc = one_level(batch)) != LBG_OK) return rc;
+      batch = std::min<uint32_t>(batch * 2, 64);
+    } else {
+      a.min_arcs = team_limit;
+      if (ef <= team_limit && (rc = team()) != LBG_OK) return rc;
+      // A graph of up to kSmallGraph arcs is mostly done by now: read back
+      // first.  Near-far solves come back to big levels after each split.
+      if (first ? P.m > kSmallGraph : ef > team_limit) {
+        for (int i = 0; i < (a.far ? 3 : 1); ++i) {
+          if ((rc = one_level(a.far ? 6 : batch)) != LBG_OK) return rc;
+          if ((rc = team()) != LBG_OK) return rc;
         }
       }
-      batch = std::min<uint32_t>(batch * 2, 64);
     }
     if (P.is_sssp) {
       hipLaunchKernelGGL(lbg::k_sssp_finish, dim3(init_blocks), dim3(lbg::kBlock), 0, st, a);
@@ -673,22 +737,27 @@ int solve(const Problem& P) {
     HIP_TRY(hipStreamSynchronize(st));
     if (host->error)
       return fail(LBG_EOVERFLOW, "device guard tripped (flags 0x%x: %s)", host->error, guard_names(host->error));
-    L = host->levels;
-    uint64_t ef = static_cast<uint32_t>(host->ctr[L % 3]);
+    L = a.team ? host->next : host->levels;
+    ef = static_cast<uint32_t>(host->ctr[L % 3]);
     if (sl)  // the mixed list's tail (ctr) plus the 8 slice tails
       for (int x = 0; x < lbg::kXcds; ++x) ef += static_cast<uint32_t>(host->xstat[x][4 + L % 3]);
-    if (ef == 0u) break;
+    if (a.team) {  // which of the submission's launches had work
+      if (first && ones) g_big_hint[kind] = 1u + static_cast<uint32_t>(__builtin_popcountll(host->worked & ones));
+      for (size_t j = 0; profiling && j < g_event_level.size(); ++j) {
+        const int64_t q = g_event_level[j];
+        if (q >= k_first) g_event_level[j] = (host->worked >> (q & 63)) & 1ull ? 0 : -2;
+      }
+    }
+    // near-far: done once a split has found the far set empty
+    if (ef == 0u && (!a.far || (host->split_at == L && host->far_seen != L))) break;
     if (L > level_cap)
       return fail(LBG_EINTERNAL, "more than n + 1 levels; the CSR is probably malformed");
-    const bool was_small = small;
-    small = small_ok && ef <= team_limit &&
-            !(was_small && L == L_prev);  // no progress (the team came together too small): never spin
-    if (was_small && !small) batch = 8;
-    used_small = used_small || small;
+    // no progress (the team came together too small): one-level launches alone
+    alone = small_ok && !alone && L == L_prev && !first;
+    if (alone) batch = 8;
+    first = false;
     L_prev = L;
   }
-
-  g_level_hint[P.is_sssp ? 1 : 0] = used_small ? 0u : host->levels;
   if (shint) {
     shint->mask = scan_any ? host->scan_levels : (shint->mask | host->scan_levels);
     ++shint->uses;
@@ -710,10 +779,10 @@ int solve(const Problem& P) {
       float ms = 0.f;
       HIP_TRY(hipEventElapsedTime(&ms, g_events[g_event_end[j] - 1], g_events[g_event_end[j]]));
       const int64_t lv = g_event_level[j];
-      if (lv < 0) {
+      if (lv == -1) {
         pp.launches += 1;
         pp.kernel_ms += ms;
-      } else if (lv < static_cast<int64_t>(host->levels)) {
+      } else if (a.team ? lv >= 0 : lv < static_cast<int64_t>(host->levels)) {
         gp.launches += 1;
         gp.kernel_ms += ms;
       } else {

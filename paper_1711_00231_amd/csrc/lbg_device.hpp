@@ -53,15 +53,18 @@ struct Ctl {
   unsigned long long frontier_entries;
   unsigned long long edges_scanned;
   unsigned int csr_flags;     // lbg_validate_csr findings
-  unsigned int pad0;
+  unsigned int next;          // balanced: the next step (levels counts the ones with work)
   unsigned long long p_frontier_entries;  // the part of the two totals above
   unsigned long long p_edges_scanned;     // done by the small-frontier kernel
   unsigned int deg_max;       // lbg_degree_mdt
   unsigned int level_base;    // graph-launched batches: first level of the next replay
   unsigned int sub_cnt[3];    // hierarchical strategy: sublist sizes of three sub-iterations
-  unsigned int pad3;
-  unsigned long long scan_levels;  // BFS: bit L set when level L (< 64) ran in scan mode
-  unsigned long long pad1[3];
+  unsigned int split_at;      // near-far SSSP: 1 + the last step that split the far set,
+  unsigned long long scan_levels;  // BFS: bit k set when launch k (< 64) ran in scan mode
+  unsigned int far_seen;      //   and 1 + the last one that found a node in it
+  unsigned int pad0;
+  unsigned long long worked;  // balanced: bit k % 64 set when launch k found work
+  unsigned long long pad1;
   // [x][0] updates, [x][1] global atomics issued; [x][2], [x][3] the same for
   // levels run by the small-frontier kernel; [x][4 + L % 3] the packed tail
   // (nodes << 32 | edges) of slice x's worklist of level L (destination-
@@ -75,8 +78,8 @@ static_assert(sizeof(Ctl) == 128 + kXcds * 128, "Ctl layout");
 // workgroups, kTeamSlots arcs of a level each, one workgroup per kTeamNodes
 // nodes of the graph.
 constexpr uint32_t kTeamMax = 128;
-constexpr uint32_t kTeamSlots = 2048;
-constexpr uint32_t kTeamNodes = 256;
+constexpr uint32_t kTeamSlots = 4096;
+constexpr uint32_t kTeamNodes = 128;
 constexpr uint32_t kTeamE = kTeamMax * kTeamSlots;  // arcs of a level run there
 // Its control words, zeroed by k_init, in the bytes between the control block
 // and the next 256-byte boundary.  join[] / size[] are used by launch number
@@ -84,11 +87,18 @@ constexpr uint32_t kTeamE = kTeamMax * kTeamSlots;  // arcs of a level run there
 // flags (KArgs::tflag) are here for up to kTeamFew of them, else in an array
 // the solve does not use meanwhile: workgroup w's word of exchange e is
 // tflag[(e % 2) * workgroups + w] = (e << 34) | payload.
-constexpr uint32_t kTeamFew = 4;
+// The rest is the near-far state (k_expand_balanced, far_split): step L reads
+// entry L % 3 and leaves entry (L + 1) % 3.
+constexpr uint32_t kTeamFew = 2;
 struct TeamCtl {
   uint32_t join[4];
   uint32_t size[4];
-  uint32_t epoch;  // exchanges so far in this solve
+  uint32_t epoch;     // exchanges so far in this solve
+  uint32_t delta0;    // the smallest threshold step
+  uint32_t thr[3];    // nodes with a larger distance wait in the far set
+  uint32_t delta[3];  // the last step of the threshold
+  uint32_t most[3];   // arcs of the largest level since the last split
+  uint32_t at[2];     // the level that launch number k of a solve finds (k % 2)
   uint32_t pad;
   unsigned long long flag[2 * kTeamFew];
 };
@@ -132,6 +142,7 @@ struct KArgs {
   TeamCtl* team;         // balanced strategy: the small-frontier team (else null)
   unsigned long long* tflag;  // its flags, 2 x tblocks
   uint32_t tblocks;      // workgroups it is launched with
+  uint32_t* far;         // near-far SSSP: one bit per node of the far set (else null)
   uint32_t n;
   uint32_t m;
   uint32_t words;        // (n + 31) / 32
@@ -143,6 +154,9 @@ struct KArgs {
   // arcs runs in scan mode (no claim atomics, no pushes; k_bfs_compact
   // builds the next worklist from the levels array).  UINT32_MAX: never.
   uint32_t scan_min;
+  // Balanced one-level launches leave levels of at most min_arcs arcs (and
+  // near-far splits) to the team launched behind them.  0: none.
+  uint32_t min_arcs;
   const QInfo* qtab;     // batched solves
   uint32_t num_queries;
   uint32_t rows;         // batched solves: total elements of node state

@@ -62,13 +62,27 @@ __device__ __forceinline__ void load_arc(const KArgs& a, uint32_t e, int32_t* v,
 }
 
 
+template <typename T>
+__device__ __forceinline__ T ld_agent(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void st_agent(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Level bookkeeping, by one thread of the grid: clear the counter two levels
 // ahead (the one level L+1 appends to) and account level L.
 __device__ __forceinline__ void level_account(const KArgs& a, uint32_t L, unsigned long long c) {
   __hip_atomic_store(&a.ctl->ctr[(L + 2) % 3], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (static_cast<uint32_t>(c) != 0u) {
     const unsigned long long fe = (c >> 32) ? (c >> 32) : static_cast<uint32_t>(c);
-    a.ctl->levels = L + 1;
+    if (a.team) {
+      a.ctl->levels += 1;
+      a.ctl->next = L + 1;
+    } else {
+      a.ctl->levels = L + 1;
+    }
     a.ctl->frontier_entries += fe;
     a.ctl->edges_scanned += static_cast<uint32_t>(c);
   }
@@ -294,7 +308,84 @@ __device__ __forceinline__ void init_state(const KArgs& a, int32_t src, uint32_t
     a.ctl->p_frontier_entries = 0ull;
     a.ctl->p_edges_scanned = 0ull;
     a.ctl->scan_levels = 0ull;
+    a.ctl->next = 0u;
+    a.ctl->worked = 0ull;
+    a.ctl->split_at = 0u;
+    a.ctl->far_seen = 0u;
   }
+}
+
+// Near-far SSSP.  Plain Bellman-Ford expands every improved node in the next
+// iteration, whatever its distance, and on graphs of long shortest paths most
+// of that work is done again with better distances later: 96 x the arcs of the
+// 2048 x 2048 grid without shortcuts, 4.3 x with 1 % shortcuts, 3.7 x those of
+// a uniform graph of 2^20 nodes (measured with the weights of those
+// workloads).  So a node whose distance exceeds a threshold T is not queued
+// but put in the far set, one bit per node; once the worklist is empty T grows
+// by delta and a split moves the nodes of the far set with distances up to T
+// to the worklist (the deferral of delta-stepping, Meyer and Sanders 2003, and
+// of the near-far worklists of Davidson et al. 2014, here with a bitmap, so a
+// node is held once and any order of updates is right).  Invariant: a reached
+// node that has not been expanded with its present distance is in the
+// worklist or in the far set.  A bit may outlive its node's move to the
+// worklist (its clearing may overtake its setting); then the node is expanded
+// once more.
+//
+// The step: 16 x the mean weight / the mean out-degree, i.e. about 16 arcs
+// of a node's share of weight.  Smaller steps relax fewer arcs in more
+// iterations.  Counted on the host emulation, arcs relaxed / iterations: grid
+// with shortcuts, 1 x mean weight 1.12 / 189, 4 x (this rule) 1.38 / 119,
+// 8 x 1.72 / 105; uniform 2^20, 1 x 1.27 / 41, 2 x (this rule) 1.33 / 35, 4 x
+// 3.66 / 30.  While even the largest level of a step is a fraction of what
+// the chip takes in one round of latency the step doubles (the grid without
+// shortcuts: 4587 iterations at 4 x, 3560 with doubling).
+constexpr uint32_t kFarIdle = 16384;  // arcs of a level that latency hides
+constexpr uint32_t kFarSample = 4096;
+
+// One workgroup: the first threshold from a sample of the weights, then the
+// other words of the team's control block.
+__device__ __forceinline__ void near_far_init(const KArgs& a) {
+  __shared__ unsigned long long sum;
+  if (threadIdx.x == 0) sum = 0ull;
+  __syncthreads();
+  unsigned long long x = 0;
+  for (uint32_t k = threadIdx.x; k < kFarSample; k += kBlock) {
+    const uint32_t e = static_cast<uint32_t>(static_cast<unsigned long long>(k) * a.m / kFarSample);
+    x += a.arcs ? a.arcs[e] & ((1u << a.wbits) - 1u) : a.weights[e];
+  }
+  atomicAdd(&sum, x);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    TeamCtl* t = a.team;
+    for (int k = 0; k < 4; ++k) t->join[k] = t->size[k] = 0u;
+    t->epoch = 0u;
+    const double step = 16.0 * static_cast<double>(sum) / kFarSample * a.n / a.m;
+    t->delta0 = static_cast<uint32_t>(step < 1.0 ? 1.0 : (step > 1e9 ? 1e9 : step));
+    t->thr[0] = t->delta[0] = t->delta0;
+    t->at[0] = 0u;
+    t->most[0] = 0u;
+    for (uint32_t k = 0; k < 2 * kTeamFew; ++k) t->flag[k] = 0ull;
+  }
+}
+
+// A node whose distance was `was` (> T) has improved: out of the far set if
+// it is queued now, into it if this is the first time it is reached.
+template <bool kNarrow>
+__device__ __forceinline__ void far_move(const KArgs& a, uint32_t v, uint32_t was, bool queued) {
+  if (queued) {
+    if (was != kSsspInf) atomicAnd(at<kNarrow>(a.far, v >> 5), ~(1u << (v & 31)));
+  } else if (was == kSsspInf) {
+    atomicOr(at<kNarrow>(a.far, v >> 5), 1u << (v & 31));
+  }
+}
+
+// The threshold and step of a split, from those of the steps before.
+__device__ __forceinline__ void far_raise(uint32_t delta0, uint32_t most, uint32_t* thr, uint32_t* delta) {
+  uint32_t d = *delta;
+  if (most < kFarIdle && (most == 0u || d / 4 < delta0)) d = d < 0x40000000u ? 2 * d : d;
+  else if (most > 8 * kFarIdle && d > delta0) d = max(delta0, d / 2);
+  *delta = d;
+  *thr = *thr < kSsspInf - d ? *thr + d : kSsspInf;
 }
 
 template <bool kSssp, bool kEdgeWl>
@@ -313,7 +404,12 @@ __global__ __launch_bounds__(kBlock) void k_init(KArgs a, int32_t src) {
   }
   init_state<kSssp>(a, src, gid, stride);
   if (a.team) {
-    if (gid < sizeof(TeamCtl) / 4) reinterpret_cast<uint32_t*>(a.team)[gid] = 0u;
+    if (a.far) {
+      for (uint32_t k = gid; k < a.words; k += stride) a.far[k] = 0u;
+      if (blockIdx.x == 0) near_far_init(a);
+    } else if (gid < sizeof(TeamCtl) / 4) {
+      reinterpret_cast<uint32_t*>(a.team)[gid] = 0u;
+    }
     for (uint32_t k = gid; k < 2 * a.tblocks; k += stride) a.tflag[k] = 0ull;
   }
   if (a.hier_trace)
@@ -410,14 +506,17 @@ __global__ __launch_bounds__(kBlock) void k_init(KArgs a, int32_t src) {
 }
 
 // SSSP epilogue: once the worklist of the next level to expand (ctl->levels:
-// the last non-empty level + 1) is empty, copy the distances out of the
-// packed state.  Launched after every step of the level loop; exits at once
-// while work remains, so the host needs no extra synchronisation.
+// the last non-empty level + 1; balanced: ctl->next) is empty, and the far set
+// too, copy the distances out of the packed state.  Launched after every step
+// of the level loop; exits at once while work remains, so the host needs no
+// extra synchronisation.
 __global__ __launch_bounds__(kBlock) void k_sssp_finish(KArgs a) {
-  const uint32_t L = __hip_atomic_load(&a.ctl->levels, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint32_t L = __hip_atomic_load(a.team ? &a.ctl->next : &a.ctl->levels, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
   const unsigned long long c = __hip_atomic_load(&a.ctl->ctr[L % 3], __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
   if (static_cast<uint32_t>(c) != 0u) return;
+  if (a.far && !(a.ctl->split_at == L && a.ctl->far_seen != L)) return;  // the far set may hold nodes
   if (a.sliced) {  // and the 8 slice lists
     for (int x = 0; x < kXcds; ++x)
       if (static_cast<uint32_t>(__hip_atomic_load(&a.ctl->xstat[x][4 + L % 3], __ATOMIC_RELAXED,
@@ -490,7 +589,7 @@ __device__ __forceinline__ bool level_fits(const KArgs& a, unsigned long long c)
 // One level of the balanced expansion by the whole grid (all threads of
 // every block must call it).  c = the level's packed tail, non-empty and
 // within capacity.
-template <bool kSssp, bool kNarrow, bool kMulti, bool kPacked = false, bool kSplit = false>
+template <bool kSssp, bool kNarrow, bool kMulti, bool kPacked = false, bool kSplit = false, bool kFar = false>
 __device__ __forceinline__ void expand_level(const KArgs& a, uint32_t L, unsigned long long c) {
   static_assert(!kMulti || kSssp, "batched solves use the SSSP relaxation");
   static_assert(!kPacked || (kSssp && !kMulti), "packed arcs: single SSSP solves");
@@ -522,6 +621,26 @@ __device__ __forceinline__ void expand_level(const KArgs& a, uint32_t L, unsigne
   const bool scan = !kSssp && !kMulti && !kSplit && Ef >= a.scan_min;
   if (!kSssp && !scan) refresh_seen(a, L);
 
+  // Near-far SSSP (above): a split step when the worklist is empty.
+  static_assert(!kFar || (kSssp && !kMulti && !kSplit), "near-far: single SSSP solves");
+  uint32_t thr = kSsspInf;
+  const bool split = kFar && Ef == 0u;
+  if constexpr (kFar) {
+    uint32_t delta = a.team->delta[L % 3], most = a.team->most[L % 3];
+    thr = a.team->thr[L % 3];
+    if (split) {
+      far_raise(a.team->delta0, most, &thr, &delta);
+      most = 0u;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      a.team->thr[(L + 1) % 3] = thr;
+      a.team->delta[(L + 1) % 3] = delta;
+      a.team->most[(L + 1) % 3] = max(most, Ef);
+      a.ctl->next = L + 1;
+      if (split) a.ctl->split_at = L + 1;
+    }
+  }
+
   const uint32_t ntiles = (Ef + T - 1) / T;
   const uint32_t W = gridDim.x * kWaves;
   // Tile deal.  Tiles [0, S) go round-robin to the W wavefronts (tile g,
@@ -549,6 +668,47 @@ __device__ __forceinline__ void expand_level(const KArgs& a, uint32_t L, unsigne
     return S + xcd + static_cast<uint32_t>(kXcds) * k;
   };
   uint32_t tile = blockIdx.x * kWaves + wid;
+  if constexpr (kFar) {
+    // Split: the far set's words, one per lane; the nodes within the
+    // threshold leave it for worklist L + 1.
+    if (split) {
+      for (uint32_t k0 = tile * 64; k0 < a.words; k0 += W * 64) {
+        const uint32_t k = k0 + lane;
+        const uint32_t had = k < a.words ? *at<kNarrow>(a.far, k) : 0u;
+        uint32_t left = had, kept = 0u;
+        if (__any(had != 0u) && lane == 0) a.ctl->far_seen = L + 1;  // one value from every writer
+        while (__any(left != 0u)) {
+          constexpr int kB = 4;
+          int32_t v[kB];
+          bool near[kB];
+          uint32_t P = 0;
+#pragma unroll
+          for (int b = 0; b < kB; ++b) {
+            v[b] = left ? static_cast<int32_t>(32 * k + __builtin_ctz(left)) : -1;
+            left &= left - 1u;
+          }
+#pragma unroll
+          for (int b = 0; b < kB; ++b)
+            near[b] = v[b] >= 0 && static_cast<uint32_t>(*at<kNarrow>(a.dstate, static_cast<uint32_t>(v[b])) >> 32) <= thr;
+#pragma unroll
+          for (int b = 0; b < kB; ++b) {
+            if (v[b] >= 0 && !near[b]) kept |= 1u << (v[b] & 31);
+            P += static_cast<uint32_t>(__popcll(__ballot(near[b])));
+          }
+          if (qcount + P > static_cast<uint32_t>(kWQ)) {
+            WaveFlush<kPay, T, kNarrow, kSplit> f;
+            f.flush(a, w.qv, w.qq, qcount, nxt, nctr);
+            qcount = 0;
+            wave_sync();
+          }
+#pragma unroll
+          for (int b = 0; b < kB; ++b)
+            wq_push<kPay, T, kNarrow, kSplit>(a, w.qv, w.qq, qcount, near[b], v[b], 0, nxt, nctr);
+        }
+        if (kept != had) *at<kNarrow>(a.far, k) = kept;
+      }
+    }
+  }
   if (tile >= S) tile = S < ntiles ? take() : ntiles;
   uint32_t i0_next = tile < ntiles ? static_cast<uint32_t>(*at<kNarrow>(cur.tile_node, tile)) : 0u;
   uint32_t tnext = ntiles;
@@ -837,6 +997,13 @@ __device__ __forceinline__ void expand_level(const KArgs& a, uint32_t L, unsigne
           if (better) *at<kNarrow>(a.d16, row[r]) = f16_of(alt);  // filter (see top of file)
           upd += better ? 1u : 0u;
           push[r] = better && static_cast<uint32_t>(old[r]) != L + 1;
+          if constexpr (kFar) {
+            const uint32_t was = static_cast<uint32_t>(old[r] >> 32);
+            if (better && was > thr) {  // it was not queued so far
+              push[r] = alt <= thr;
+              far_move<kNarrow>(a, static_cast<uint32_t>(vv[r]), was, push[r]);
+            }
+          }
         }
       }
     }
@@ -899,20 +1066,37 @@ __device__ __forceinline__ void expand_level(const KArgs& a, uint32_t L, unsigne
   add_stats(a, upd, atom, skip);
 }
 
-template <bool kSssp, bool kNarrow, bool kMulti, bool kPacked = false, bool kSplit = false>
-__device__ __forceinline__ void balanced_level(const KArgs& a, uint32_t L) {
+// Balanced single solves: the level that launch number k of the solve finds
+// is known on the device only (a team launch runs any number of them); one
+// thread leaves it for the next launch and notes whether this one has work.
+__device__ __forceinline__ uint32_t level_of(const KArgs& a, uint32_t k) { return a.team ? a.team->at[k & 1] : k; }
+__device__ __forceinline__ void level_next(const KArgs& a, uint32_t k, uint32_t next, bool work) {
+  a.team->at[(k + 1) & 1] = next;
+  const unsigned long long bit = 1ull << (k & 63);
+  a.ctl->worked = work ? a.ctl->worked | bit : a.ctl->worked & ~bit;
+}
+
+template <bool kSssp, bool kNarrow, bool kMulti, bool kPacked = false, bool kSplit = false, bool kFar = false>
+__device__ __forceinline__ void balanced_level(const KArgs& a, uint32_t k) {
+  const uint32_t L = level_of(a, k);
+  if (a.team) {
+    const uint32_t Ef = static_cast<uint32_t>(ld_agent(&a.ctl->ctr[L % 3]));
+    const bool idle = Ef <= a.min_arcs && !(Ef == 0u && kFar && a.min_arcs == 0u);
+    if (blockIdx.x == 0 && threadIdx.x == 0) level_next(a, k, idle ? L : L + 1, !idle);
+    if (idle) return;
+  }
   const unsigned long long c = level_begin(a, L);
-  if (static_cast<uint32_t>(c) == 0u) return;
+  if (static_cast<uint32_t>(c) == 0u && !kFar) return;
   if (!level_fits<kSssp, kMulti>(a, c)) {
     if (threadIdx.x == 0) atomicOr(&a.ctl->error, kErrNodeCap);
     return;
   }
-  expand_level<kSssp, kNarrow, kMulti, kPacked, kSplit>(a, L, c);
+  expand_level<kSssp, kNarrow, kMulti, kPacked, kSplit, kFar>(a, L, c);
 }
 
-template <bool kSssp, bool kNarrow, bool kMulti = false, bool kPacked = false, bool kSplit = false>
-__global__ __launch_bounds__(kBlock) void k_expand_balanced(KArgs a, uint32_t L) {
-  balanced_level<kSssp, kNarrow, kMulti, kPacked, kSplit>(a, L);
+template <bool kSssp, bool kNarrow, bool kMulti = false, bool kPacked = false, bool kSplit = false, bool kFar = false>
+__global__ __launch_bounds__(kBlock) void k_expand_balanced(KArgs a, uint32_t k) {
+  balanced_level<kSssp, kNarrow, kMulti, kPacked, kSplit, kFar>(a, k);
 }
 
 // BFS scan levels.  A level of at least a.scan_min arcs is expanded without
@@ -939,14 +1123,15 @@ __global__ __launch_bounds__(kBlock) void k_expand_balanced(KArgs a, uint32_t L)
 // expansion needs no read of the node's level (measured: BFS 2.6 % faster
 // on R-MAT 22 than reading it).  Returns at once unless level L scans.
 template <bool kNarrow>
-__global__ __launch_bounds__(kBlock) void k_bfs_prep(KArgs a, uint32_t L) {
+__global__ __launch_bounds__(kBlock) void k_bfs_prep(KArgs a, uint32_t k) {
+  const uint32_t L = level_of(a, k);
   const unsigned long long c = __hip_atomic_load(&a.ctl->ctr[L % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t Ef = static_cast<uint32_t>(c);
-  if (Ef == 0u || Ef < a.scan_min) return;
+  if (Ef <= a.min_arcs || Ef < a.scan_min) return;
   const uint32_t total = a.words * kXcds;
-  for (uint32_t k = blockIdx.x * kBlock + threadIdx.x; k < total; k += gridDim.x * kBlock) {
-    const uint32_t v = *at<kNarrow>(a.visited, k % a.words);
-    if (v) a.xfilter[k] |= v;
+  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < total; i += gridDim.x * kBlock) {
+    const uint32_t v = *at<kNarrow>(a.visited, i % a.words);
+    if (v) a.xfilter[i] |= v;
   }
 }
 
@@ -955,7 +1140,8 @@ constexpr uint32_t kCompactChunk = kBlock * kCompactPer;  // nodes per workgroup
 __device__ __forceinline__ uint32_t compact_slot(uint32_t j) { return j + (j >> 4); }  // one pad word per 16
 
 template <bool kNarrow>
-__global__ __launch_bounds__(kBlock) void k_bfs_compact(KArgs a, uint32_t L) {
+__global__ __launch_bounds__(kBlock) void k_bfs_compact(KArgs a, uint32_t launch) {
+  const uint32_t L = level_of(a, launch);
   constexpr uint32_t T = TileCfg<false>::kEdges;
   constexpr uint32_t kSlots = kCompactChunk + kCompactChunk / 16 + 1;
   __shared__ int32_t lvs[kSlots];
@@ -964,8 +1150,9 @@ __global__ __launch_bounds__(kBlock) void k_bfs_compact(KArgs a, uint32_t L) {
   __shared__ unsigned long long base_sh;
   const unsigned long long c = __hip_atomic_load(&a.ctl->ctr[L % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t Ef = static_cast<uint32_t>(c);
-  if (Ef == 0u || Ef < a.scan_min || !level_fits<false, false>(a, c)) return;  // push-mode level
-  if (blockIdx.x == 0 && threadIdx.x == 0 && L < 64u) atomicOr(&a.ctl->scan_levels, 1ull << L);
+  // push-mode level, or none was run
+  if (Ef <= a.min_arcs || Ef < a.scan_min || !level_fits<false, false>(a, c)) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && launch < 64u) atomicOr(&a.ctl->scan_levels, 1ull << launch);
   Frontier nxt = a.fr[(L + 1) & 1];
   nxt.level = L + 1;
   const int nctr = (L + 1) % 3;

@@ -31,27 +31,25 @@
 
 namespace lbg {
 
-constexpr int kTeamBlock = 512;
+constexpr int kTeamBlock = 1024;
 constexpr int kTeamWaves = kTeamBlock / 64;
-constexpr int kTeamU = kTeamSlots / kTeamBlock;
+constexpr int kTeamU = 2;                             // slots per thread of a pass over the arcs
+constexpr uint32_t kTeamPass = kTeamU * kTeamBlock;
 // Up to this many arcs a level is all latency: every arc issues its atomic,
 // and its target's offsets, at once.  Beyond, the state is read first and
 // only arcs that can still win issue them (one more round trip, but the
 // memory side takes about 27 G atomics/s for the whole chip).
-constexpr uint32_t kTeamEager = 32768;
+constexpr uint32_t kTeamEager = 16384;
+// Arcs a workgroup may hold whatever the others do.  Cutting a level again
+// costs an exchange and a pass through memory (5 us), 8 us for SSSP.
+constexpr uint32_t kTeamOwnBfs = 512, kTeamOwnSssp = 1024;
+constexpr uint32_t kTeamRounds = 16;   // SSSP rounds between exchanges while the frontier is small,
+constexpr uint32_t kTeamCalm = 512;    //   at most so many arcs per workgroup
 constexpr unsigned long long kTeamWait = 1000;               // 10 us of the 100 MHz clock
 constexpr unsigned long long kTeamPatience = 1000000000ull;  // 10 s
 
+constexpr uint32_t kTeamArcs = 0xfffffu;  // largest arc count of a flag (more than any level run here)
 constexpr uint32_t kTeamClosed = 0x80000000u;
-
-template <typename T>
-__device__ __forceinline__ T ld_agent(const T* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
-__device__ __forceinline__ void st_agent(T* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // Joins launch seq's team (one thread).  Returns the workgroup's number and
 // sets *size, or returns kTeamMax when it is not a member.
@@ -86,30 +84,34 @@ __device__ __forceinline__ uint32_t team_join(const KArgs& a, uint32_t seq, uint
 }
 
 template <bool kSssp>
+struct TeamList {  // the entries one workgroup holds, in arc order
+  uint32_t pre[kTeamSlots];                  // arcs of the entries before
+  int32_t st[kTeamSlots];                    // first arc
+  int32_t node[kSssp ? kTeamSlots : 1];      // node
+  uint32_t du[kSssp ? kTeamSlots : 1];       // the distance it was pushed with
+};
+
+template <bool kSssp>
 struct TeamLds {
-  uint32_t segn[kTeamMax + 1];  // entries of the level before segment q
-  uint32_t sege[kTeamMax + 1];  // arcs of the level before segment q
-  uint32_t base[2 * kTeamSlots];                 // arc of slot s of entry i is base[i] + s
-  int32_t node[kSssp ? 2 * kTeamSlots : 1];      // entry i's node
-  uint32_t flag[kTeamSlots / 32];                // bit s: an entry starts at slot s
-  uint32_t lead;                                 // the entry that holds slot 0
-  uint32_t ppre[kTeamSlots];                     // pushes: arcs of the pushes before,
-  int32_t pst[kTeamSlots];                       //   first arc,
-  int32_t pnode[kSssp ? kTeamSlots : 1];         //   node
-  unsigned long long push;                       // (entries << 32) | arcs pushed so far
+  TeamList<kSssp> list[2];      // this level's entries, the next one's
+  uint32_t segn[kTeamMax + 1];  // entries before workgroup q's
+  uint32_t sege[kTeamMax + 1];  // arcs before workgroup q's
+  unsigned long long flag[kTeamSlots / 64];  // bit s: an entry starts at slot s
+  unsigned long long push;      // (entries << 32) | arcs pushed so far
   uint32_t me, size, ok;
-  uint32_t over;                                 // some workgroup's pushes outgrew its segment
+  uint32_t found;               // split: this workgroup found nodes in the far set
+  uint32_t any_found;           //   or some other one did
+  uint32_t most;                // arcs of the workgroup with the most
 };
 
 // Exchange number e: wave 0 raises this workgroup's flag, waits for every
 // member's and leaves the prefix sums of their payloads in segn / sege:
-// (entries << 21 | arcs) or, kArcsOnly, arcs alone (segn is kept); over says
-// whether a workgroup has more than seg entries.  Must be reached by the
-// whole workgroup after its stores have been waited for and a barrier; ends
-// with one.
+// (found << 33 | entries << 20 | arcs) or, kArcsOnly, arcs alone (segn is
+// kept).  Must be reached by the whole workgroup, with a barrier between it
+// and what it publishes or overwrites; ends with one.
 template <bool kSssp, bool kArcsOnly>
 __device__ __forceinline__ bool team_exchange(const KArgs& a, TeamLds<kSssp>& sm, uint32_t e, uint32_t me,
-                                              uint32_t size, uint32_t seg, unsigned long long payload) {
+                                              uint32_t size, unsigned long long payload) {
   if (threadIdx.x < 64) {
     const uint32_t lane = threadIdx.x;
     unsigned long long* f = a.tflag + (e & 1) * a.tblocks;
@@ -128,28 +130,35 @@ __device__ __forceinline__ bool team_exchange(const KArgs& a, TeamLds<kSssp>& sm
       ok = __all(here);
       if (!ok && (spin & 1023u) == 0u && wall_clock64() - t0 > kTeamPatience) break;
     }
-    uint32_t cn = 0, ce = 0;
-    bool over = false;
+    uint32_t cn = 0, ce = 0, most = 0;
+    bool found = false;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const uint32_t q = h * 64 + lane;
-      const uint32_t xe = kArcsOnly ? static_cast<uint32_t>(v[h]) : static_cast<uint32_t>(v[h]) & 0x1fffffu;
+      const uint32_t xe = kArcsOnly ? static_cast<uint32_t>(v[h]) : static_cast<uint32_t>(v[h]) & kTeamArcs;
       const uint32_t ie = wave_incl_scan(xe);
       sm.sege[q + 1] = ce + ie;
       ce += __shfl(ie, 63, 64);
       if (!kArcsOnly) {
-        const uint32_t xn = static_cast<uint32_t>(v[h] >> 21) & 0x1fffu;
-        over = over || xn > seg;
+        const uint32_t xn = static_cast<uint32_t>(v[h] >> 20) & 0x1fffu;
         const uint32_t in = wave_incl_scan(xn);
         sm.segn[q + 1] = cn + in;
         cn += __shfl(in, 63, 64);
+        found = found || ((v[h] >> 33) & 1ull);
+        most = max(most, xe);
       }
     }
-    over = __any(over);
+    if (!kArcsOnly) {
+      found = __any(found);
+      most = static_cast<uint32_t>(wave_max(static_cast<int32_t>(most)));
+    }
     if (lane == 0) {
-      if (!kArcsOnly) sm.over = over ? 1u : 0u;
       sm.sege[0] = 0u;
-      if (!kArcsOnly) sm.segn[0] = 0u;
+      if (!kArcsOnly) {
+        sm.segn[0] = 0u;
+        sm.any_found = found ? 1u : 0u;
+        sm.most = most;
+      }
       sm.ok = ok ? 1u : 0u;
       if (!ok) atomicOr(&a.ctl->error, kErrTeam);
     }
@@ -161,326 +170,494 @@ __device__ __forceinline__ bool team_exchange(const KArgs& a, TeamLds<kSssp>& sm
 // Levels L0, L0 + 1, ... until the worklist is empty, max_levels levels have
 // run or a level has more than `limit` arcs; then the next level is written
 // in the one-level kernels' worklist format and the host continues from
-// ctl->levels.  Level L0 comes in that format (at most `limit` arcs and
-// kTeamE entries, or nothing is done); later levels live as one segment of
-// entries per workgroup, segment q of level L at q * seg of the arrays of
-// buffer (L + 1) & 1 (estart, node; eprefix counts from the segment's start),
-// with the segments' sizes exchanged in the flags.  A level's arcs are cut
-// evenly: workgroup w takes arcs [w C, (w + 1) C), so a hub is shared by many
-// workgroups and none pushes more than C <= kTeamSlots entries; they are kept
-// in LDS as well.  The arrays hold n entries in all, so with fewer than
-// kTeamE nodes a workgroup's pushes may outgrow its segment; then the level
-// is written in the one-level format from the LDS copies, once the counts
-// are known (one more exchange).
+// ctl->next.  Level L0 comes in that format (at most
+// `limit` arcs, or nothing is done) and is cut into equal shares of arcs, so
+// a hub is shared by many workgroups.  From then on a workgroup expands the
+// nodes it pushed itself, from its LDS: no entry passes through memory, and
+// the arcs of a level are loaded while the flags are exchanged.  Where that
+// leaves a workgroup with more than kTeamOwn* arcs and twice the mean (or
+// more than it can hold), the level is written out and cut again.
+//
+// BFS exchanges flags before every level (levels are hop counts).  SSSP runs
+// kTeamRounds rounds between exchanges: distances only fall, so the order of
+// relaxations is free (and L counts exchanges).  Since a node may improve again after a workgroup has
+// expanded it, every improvement is pushed, with its distance, and an entry
+// whose node has a smaller one by then is passed over.
 template <bool kSssp, bool kNarrow, bool kPacked = false>
-__global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t L0, uint32_t seq, uint32_t limit,
+__global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t launch, uint32_t seq, uint32_t limit,
                                                             uint32_t max_levels) {
   static_assert(!kPacked || kSssp, "packed arcs: SSSP");
-  static_assert(kTeamMax == 128 && kTeamSlots == 64 * 32, "two flags per lane, one flag word per lane");
+  static_assert(kTeamMax == 128 && kTeamSlots == 64 * 64, "two flags per lane, one word of entry starts per lane");
   constexpr uint32_t T = TileCfg<kSssp>::kEdges;
   constexpr int kPay = kSssp ? 1 : 0;
   __shared__ TeamLds<kSssp> sm;
   __shared__ uint32_t red[2][kTeamWaves];
   const uint32_t tid = threadIdx.x, lane = tid & 63;
 
+  const uint32_t L0 = level_of(a, launch);
   const unsigned long long c0 = ld_agent(&a.ctl->ctr[L0 % 3]);
   uint32_t nf = static_cast<uint32_t>(c0 >> 32), E = static_cast<uint32_t>(c0);
-  if (E == 0u || nf == 0u || E > min(limit, kTeamE) || nf > a.node_cap) return;  // grid-uniform
-  if (tid == 0) sm.me = team_join(a, seq, &sm.size);
+  const bool far = kSssp && a.far;
+  if ((E == 0u && !far) || E > min(limit, kTeamE) || nf > a.node_cap) {  // grid-uniform
+    if (blockIdx.x == 0 && tid == 0) level_next(a, launch, L0, false);
+    return;
+  }
+  if (tid == 0) {
+    sm.me = team_join(a, seq, &sm.size);
+    sm.push = 0ull;
+    sm.found = 0u;
+  }
+  if (tid < kTeamSlots / 64) sm.flag[tid] = 0ull;
   __syncthreads();
   const uint32_t me = sm.me, P = min(sm.size, kTeamMax);
   if (me >= P) return;
   limit = min(limit, P * kTeamSlots);
-  const uint32_t seg = min(kTeamSlots, a.node_cap / gridDim.x);  // entries of a segment
-  if (E > limit) return;  // a small team: the host goes on with one-level launches
+  if (E > limit) {  // a small team: the host goes on with one-level launches
+    if (me == 0u && tid == 0) level_next(a, launch, L0, false);
+    return;
+  }
 
   uint32_t e = a.team->epoch;
-  // the first level: pseudo-segments of equal entry counts
-  bool contiguous = true;
-  uint32_t stride = (nf + P - 1) / P;
-  if (tid <= P) {
-    const uint32_t i = min(tid * stride, nf);
-    sm.segn[tid] = i;
-    sm.sege[tid] = i < nf ? ld_agent(at<kNarrow>(a.fr[L0 & 1].eprefix, i)) : E;
+  // near-far state (see far_raise); every member keeps the same
+  uint32_t thr = kSsspInf, delta = 0, delta0 = 0, most = 0;
+  if (far) {
+    thr = a.team->thr[L0 % 3];
+    delta = a.team->delta[L0 % 3];
+    most = a.team->most[L0 % 3];
+    delta0 = a.team->delta0;
   }
-  if (tid < kTeamSlots / 32) sm.flag[tid] = 0u;
-  if (tid == 0) sm.push = 0ull;
-  __syncthreads();
-
-  uint32_t upd = 0, atom = 0;
-  unsigned long long tot_f = 0, tot_e = 0;
-  bool bad = false, alive = true;
+  uint32_t upd = 0, atom = 0, levels = 0;
+  unsigned long long tot_f = 0, tot_e = 0;  // this workgroup's share
+  bool bad = false, alive = true, done = false;
+  uint32_t cur = 0;            // the list of this level
+  uint32_t cnt = 0, arcs = 0;  // its size
   uint32_t L = L0;
-  for (;;) {
-    const Frontier cur = a.fr[contiguous ? (L & 1) : ((L + 1) & 1)];
-    const Frontier nxt = a.fr[L & 1];
-    const uint32_t C = (E + P - 1) / P;
-    const uint32_t lo = min(me * C, E), hi = min(lo + C, E);
-    tot_f += nf;
-    tot_e += E;
-    // Stage the entries that overlap [lo, hi).
-    if (lo < hi) {
-      uint32_t q1 = 0, q2 = 0;  // the segments that do: [q1, q2)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const uint32_t q = h * 64 + lane;
-        q1 += static_cast<uint32_t>(__popcll(__ballot(q < P && sm.sege[q < P ? q + 1 : 0] <= lo)));
-        q2 += static_cast<uint32_t>(__popcll(__ballot(q < P && sm.sege[q] < hi)));
-      }
-      const uint32_t first = sm.segn[q1], last = sm.segn[q2];
-      for (uint32_t i = first + tid; i < last; i += kTeamBlock) {
-        uint32_t q = q1, top = q2;  // segn[q] <= i < segn[top]
-        while (top - q > 1) {
-          const uint32_t mid = (q + top) / 2;
-          if (sm.segn[mid] <= i) q = mid;
-          else top = mid;
+
+  bool staged = E > 0u;                  // the lists are an equal cut of level L: nothing to ask the others
+  bool known = false;                    // the others' counts are known
+  uint32_t rounds = 1;                   // until the next exchange
+  uint32_t part = 0;                     // stage() took an entry whose first arc is another workgroup's
+
+  // Adds (per wavefront, convergent) the lanes with `put` to list `to`.
+  auto put_all = [&](uint32_t to, bool put, int32_t v, int32_t s0, int32_t d, uint32_t du) {
+    const uint64_t mask = __ballot(put);
+    if (mask == 0) return;
+    const uint32_t inc = wave_incl_scan(put ? static_cast<uint32_t>(d) : 0u);
+    unsigned long long b = 0;
+    if (lane == 63) b = atomicAdd(&sm.push, (static_cast<unsigned long long>(__popcll(mask)) << 32) | inc);
+    b = bcast64(b, 63);
+    if (put) {
+      const uint32_t k = static_cast<uint32_t>(b >> 32) + lane_rank(mask);
+      if (k < kTeamSlots) {
+        sm.list[to].pre[k] = static_cast<uint32_t>(b) + inc - static_cast<uint32_t>(d);
+        sm.list[to].st[k] = s0;
+        if (kSssp) {
+          sm.list[to].node[k] = v;
+          sm.list[to].du[k] = du;
         }
-        const uint32_t at_ = q * stride + (i - sm.segn[q]);
-        const uint32_t off = contiguous ? 0u : sm.sege[q];
-        const bool more = i + 1 < sm.segn[q + 1];
-        const uint32_t p = off + ld_agent(at<kNarrow>(cur.eprefix, at_));
-        const uint32_t pn = more ? off + ld_agent(at<kNarrow>(cur.eprefix, at_ + 1)) : sm.sege[q + 1];
-        const uint32_t st = static_cast<uint32_t>(ld_agent(at<kNarrow>(cur.estart, at_)));
-        const int32_t u = kSssp ? ld_agent(at<kNarrow>(cur.node, at_)) : 0;
-        if (p < hi && pn > lo) {
-          const uint32_t k = i - first;
-          if (k < 2 * kTeamSlots) {
-            const uint32_t s = (p > lo ? p : lo) - lo;
-            sm.base[k] = st + lo - p;
-            if (kSssp) sm.node[k] = u;
-            if (s == 0u) sm.lead = k;
-            atomicOr(&sm.flag[s >> 5], 1u << (s & 31));
-          } else {
-            bad = true;
-          }
-        }
-      }
-    }
-    __syncthreads();
-    if (contiguous) {
-      // pushes reuse this level's arrays: everyone has to have read them
-      ++e;
-      alive = team_exchange<kSssp, false>(a, sm, e, me, P, seg, 0ull);
-      if (!alive) break;
-    }
-    if (lo < hi) {
-      const uint32_t fw = sm.flag[lane];
-      const uint32_t pre = wave_incl_scan(__popc(fw)) - __popc(fw);
-      const uint32_t lead = sm.lead, len = hi - lo;
-      const bool eager = E <= kTeamEager;
-      int32_t vv[kTeamU];
-      uint32_t ww[kTeamU], du[kTeamU];
-#pragma unroll
-      for (int r = 0; r < kTeamU; ++r) {
-        const uint32_t s = r * kTeamBlock + tid;
-        vv[r] = -1;
-        ww[r] = 0;
-        du[r] = 0;
-        if (r * kTeamBlock < len) {  // workgroup-uniform
-          const uint32_t k = s >> 5;
-          const uint32_t before = __shfl(pre, k, 64);
-          const uint32_t bits = __shfl(fw, k, 64) & static_cast<uint32_t>((2ull << (s & 31)) - 1ull);
-          if (s < len) {
-            const uint32_t i = lead + before + __popc(bits) - 1u;
-            const uint32_t arc = i < 2 * kTeamSlots ? sm.base[i] + s : a.m;
-            if (arc < a.m) {
-              if (kPacked) {
-                load_arc<true, kNarrow>(a, arc, &vv[r], &ww[r]);
-              } else {
-                vv[r] = *at<kNarrow>(a.cols, arc);
-                if (kSssp) ww[r] = *at<kNarrow>(a.weights, arc);
-              }
-              if (kSssp) {
-                // the node's distance, settled for this level by the exchange
-                const uint32_t u = static_cast<uint32_t>(sm.node[i]);
-                if (u < a.n) {
-                  du[r] = static_cast<uint32_t>(ld_agent(at<kNarrow>(a.dstate, u)) >> 32);
-                } else {
-                  bad = true;
-                  vv[r] = -1;
-                }
-              }
-            } else {
-              bad = true;
-            }
-          }
-        }
-      }
-      bool win[kTeamU];
-      int32_t s0[kTeamU], s1[kTeamU];
-#pragma unroll
-      for (int r = 0; r < kTeamU; ++r) {
-        if (vv[r] >= 0 && static_cast<uint32_t>(vv[r]) >= a.n) {  // malformed cols (see lbg_validate_csr)
-          bad = true;
-          vv[r] = -1;
-        }
-        win[r] = vv[r] >= 0;
-        s0[r] = 0;
-        s1[r] = 0;
-      }
-      if (!eager) {
-        unsigned long long x[kTeamU];
-#pragma unroll
-        for (int r = 0; r < kTeamU; ++r) {
-          x[r] = 0ull;
-          if (win[r])
-            x[r] = kSssp ? ld_agent(at<kNarrow>(a.dstate, static_cast<uint32_t>(vv[r])))
-                         : ld_agent(at<kNarrow>(a.visited, static_cast<uint32_t>(vv[r]) >> 5));
-        }
-#pragma unroll
-        for (int r = 0; r < kTeamU; ++r)
-          win[r] = win[r] && (kSssp ? du[r] + ww[r] < static_cast<uint32_t>(x[r] >> 32)
-                                    : !((x[r] >> (vv[r] & 31)) & 1ull));
-      }
-#pragma unroll
-      for (int r = 0; r < kTeamU; ++r) {
-        if (win[r] && eager) {
-          s0[r] = *at<kNarrow>(a.offsets, vv[r]);
-          s1[r] = *at<kNarrow>(a.offsets, vv[r] + 1);
-        }
-      }
-      unsigned long long old[kTeamU];
-#pragma unroll
-      for (int r = 0; r < kTeamU; ++r) {
-        old[r] = 0ull;
-        if (win[r]) {
-          ++atom;
-          if (kSssp)
-            old[r] = atomicMin(at<kNarrow>(a.dstate, static_cast<uint32_t>(vv[r])),
-                               (static_cast<unsigned long long>(du[r] + ww[r]) << 32) | (L + 1));
-          else
-            old[r] = atomicOr(at<kNarrow>(a.visited, static_cast<uint32_t>(vv[r]) >> 5), 1u << (vv[r] & 31));
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < kTeamU; ++r) {
-        if (!win[r]) continue;
-        if (!kSssp) {
-          win[r] = !((old[r] >> (vv[r] & 31)) & 1ull);
-          if (win[r]) {
-            *at<kNarrow>(a.levels, vv[r]) = static_cast<int32_t>(L + 1);
-            ++upd;
-          }
-        } else {
-          const uint32_t alt = du[r] + ww[r];
-          win[r] = alt < static_cast<uint32_t>(old[r] >> 32);
-          if (win[r]) {
-            *at<kNarrow>(a.d16, vv[r]) = f16_of(alt);  // filter of the one-level launches
-            ++upd;
-            win[r] = static_cast<uint32_t>(old[r]) != L + 1;  // not yet queued this level
-          }
-        }
-        if (win[r] && !eager) {
-          s0[r] = *at<kNarrow>(a.offsets, vv[r]);
-          s1[r] = *at<kNarrow>(a.offsets, vv[r] + 1);
-        }
-      }
-      // Push: one LDS atomic per wavefront and round places the winners that
-      // have out-arcs and their arcs in this workgroup's segment.
-#pragma unroll
-      for (int r = 0; r < kTeamU; ++r) {
-        if (r * kTeamBlock >= len) continue;
-        const int32_t d = s1[r] - s0[r];
-        const bool put = win[r] && d > 0;  // a node without out-arcs has nothing to expand
-        const uint64_t mask = __ballot(put);
-        if (mask == 0) continue;
-        const uint32_t inc = wave_incl_scan(put ? static_cast<uint32_t>(d) : 0u);
-        unsigned long long b = 0;
-        if (lane == 63)
-          b = atomicAdd(&sm.push, (static_cast<unsigned long long>(__popcll(mask)) << 32) | inc);
-        b = bcast64(b, 63);
-        if (put) {
-          const uint32_t k = static_cast<uint32_t>(b >> 32) + lane_rank(mask);
-          const uint32_t p = static_cast<uint32_t>(b) + inc - static_cast<uint32_t>(d);
-          if (k < kTeamSlots) {
-            sm.ppre[k] = p;
-            sm.pst[k] = s0[r];
-            if (kSssp) sm.pnode[k] = vv[r];
-          } else {
-            bad = true;
-          }
-          if (k < seg) {
-            const uint32_t to = me * seg + k;
-            st_agent(at<kNarrow>(nxt.eprefix, to), p);
-            st_agent(at<kNarrow>(nxt.estart, to), s0[r]);
-            if (kSssp) st_agent(at<kNarrow>(nxt.node, to), vv[r]);
-          }
-        }
-      }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the entries are out before the flag is raised
-    __syncthreads();
-    const unsigned long long pushed = sm.push;
-    if (tid < kTeamSlots / 32) sm.flag[tid] = 0u;
-    ++e;
-    alive = team_exchange<kSssp, false>(
-        a, sm, e, me, P, seg,
-        (min(pushed >> 32, 0x1fffull) << 21) | min(pushed & 0xffffffffull, 0x1fffffull));
-    if (!alive) break;
-    if (tid == 0) sm.push = 0ull;  // everyone has read it; the next pushes follow a barrier
-    contiguous = false;
-    stride = seg;
-    ++L;
-    nf = sm.segn[P];
-    E = sm.sege[P];
-    if (E == 0u) break;
-    const bool leave = E > limit || L - L0 >= max_levels;
-    if (!leave && !sm.over) continue;
-    // Level L in the one-level format, to go on there (exact arc counts
-    // first, then entries, prefixes and marks) or here.
-    if (leave) {
-      __syncthreads();  // the prefixes are read before the next exchange writes them
-      ++e;
-      alive = team_exchange<kSssp, true>(a, sm, e, me, P, seg, pushed & 0xffffffffull);
-      if (!alive) break;
-      E = sm.sege[P];
-    }
-    const Frontier out = a.fr[L & 1];
-    const uint32_t cnt = static_cast<uint32_t>(pushed >> 32), nb = sm.segn[me], eb = sm.sege[me];
-    for (uint32_t k = tid; k < min(cnt, kTeamSlots); k += kTeamBlock) {
-      const uint32_t p = sm.ppre[k];
-      if (leave) {
-        const uint32_t pn = k + 1 < cnt ? sm.ppre[k + 1] : static_cast<uint32_t>(pushed);
-        write_entry<kPay, T, kNarrow>(a, out, nb + k, eb + p, kSssp ? sm.pnode[k] : 0, 0, sm.pst[k],
-                                      static_cast<int32_t>(pn - p));
-      } else if (nb + k < a.node_cap) {
-        st_agent(at<kNarrow>(out.eprefix, nb + k), eb + p);
-        st_agent(at<kNarrow>(out.estart, nb + k), sm.pst[k]);
-        if (kSssp) st_agent(at<kNarrow>(out.node, nb + k), sm.pnode[k]);
       } else {
         bad = true;
       }
     }
-    if (leave) break;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  };
+  // The list put_all filled becomes this level's.  Barriers on both sides.
+  auto turn = [&]() {
     __syncthreads();
-    ++e;
-    alive = team_exchange<kSssp, false>(a, sm, e, me, P, seg, 0ull);
-    if (!alive) break;
-    contiguous = true;
-    stride = (nf + P - 1) / P;
-    if (tid <= P) {
-      const uint32_t i = min(tid * stride, nf);
-      sm.segn[tid] = i;
-      sm.sege[tid] = i < nf ? ld_agent(at<kNarrow>(out.eprefix, i)) : E;
+    const unsigned long long p = sm.push;
+    cur ^= 1u;
+    cnt = min(static_cast<uint32_t>(p >> 32), kTeamSlots);
+    arcs = static_cast<uint32_t>(p);
+    __syncthreads();
+    if (tid == 0) sm.push = 0ull;
+  };
+  // This workgroup's share of level L from the one-level worklist format
+  // (E arcs, nf entries, in buffer L & 1).
+  auto stage = [&]() {
+    const Frontier f = a.fr[L & 1];
+    const uint32_t C = (E + P - 1) / P;
+    const uint32_t lo = min(me * C, E), hi = min(lo + C, E);
+    // the entry that holds arc lo: by halving steps of the whole workgroup
+    uint32_t i0 = 0, i1 = nf;  // eprefix[i0] <= lo, eprefix[i1] > lo
+    while (lo < hi && i1 - i0 > 1) {
+      const uint32_t step = (i1 - i0 + kTeamBlock - 1) / kTeamBlock;
+      const uint32_t i = i0 + tid * step;
+      const bool le = i < i1 && ld_agent(at<kNarrow>(f.eprefix, i)) <= lo;
+      const uint32_t ranks = static_cast<uint32_t>(__syncthreads_count(le));
+      i0 += (ranks - 1) * step;
+      i1 = min(i1, i0 + step);
     }
+    cnt = 0;
+    arcs = hi - lo;
+    part = lo < hi && ld_agent(at<kNarrow>(f.eprefix, i0)) < lo ? 1u : 0u;
+    if (lo < hi) {
+      for (uint32_t k0 = 0;; k0 += kTeamBlock) {  // at least one arc of every entry taken lies in [lo, hi)
+        const uint32_t i = i0 + k0 + tid;
+        bool mine = false;
+        if (i < nf && k0 + tid < kTeamSlots) {
+          const uint32_t p = ld_agent(at<kNarrow>(f.eprefix, i));
+          const uint32_t st = static_cast<uint32_t>(ld_agent(at<kNarrow>(f.estart, i)));
+          if (p < hi) {
+            mine = true;
+            sm.list[cur].pre[k0 + tid] = p > lo ? p - lo : 0u;
+            sm.list[cur].st[k0 + tid] = static_cast<int32_t>(p > lo ? st : st + (lo - p));
+            if (kSssp) {
+              const uint32_t u = static_cast<uint32_t>(ld_agent(at<kNarrow>(f.node, i)));
+              sm.list[cur].node[k0 + tid] = static_cast<int32_t>(u);
+              sm.list[cur].du[k0 + tid] = u < a.n ? static_cast<uint32_t>(ld_agent(at<kNarrow>(a.dstate, u)) >> 32) : 0u;
+            }
+          }
+        }
+        const uint32_t got = static_cast<uint32_t>(__syncthreads_count(mine));
+        cnt += got;
+        if (got < static_cast<uint32_t>(kTeamBlock)) break;
+      }
+    }
+  };
+  // Level L, held in the members' lists, to the one-level format: kLast for
+  // the next kernel (with tile marks), else for stage().
+  auto spill = [&](bool last) {
+    const Frontier out = a.fr[L & 1];
+    const uint32_t nb = sm.segn[me], eb = sm.sege[me];
+    for (uint32_t k = tid; k < cnt; k += kTeamBlock) {
+      const uint32_t p = sm.list[cur].pre[k];
+      const int32_t v = kSssp ? sm.list[cur].node[k] : 0;
+      if (last) {
+        const uint32_t pn = k + 1 < cnt ? sm.list[cur].pre[k + 1] : arcs;
+        write_entry<kPay, T, kNarrow>(a, out, nb + k, eb + p, v, 0, sm.list[cur].st[k], static_cast<int32_t>(pn - p));
+      } else if (nb + k < a.node_cap) {
+        st_agent(at<kNarrow>(out.eprefix, nb + k), eb + p);
+        st_agent(at<kNarrow>(out.estart, nb + k), sm.list[cur].st[k]);
+        if (kSssp) st_agent(at<kNarrow>(out.node, nb + k), v);
+      } else {
+        bad = true;
+      }
+    }
+  };
+  auto payload = [&]() {
+    return (static_cast<unsigned long long>(cnt) << 20) | min(arcs, kTeamArcs);
+  };
+
+  uint32_t len = 0;            // its arcs, if they fit the slots
+  int32_t vv[kTeamU];
+  uint32_t ww[kTeamU], du[kTeamU];
+  // The arcs of slots [from, from + kTeamPass) of this workgroup's entries.
+  auto load = [&](uint32_t from) {
+    const unsigned long long fw = sm.flag[lane];
+    const uint32_t pre = wave_incl_scan(__popcll(fw)) - __popcll(fw);
+#pragma unroll
+    for (int r = 0; r < kTeamU; ++r) {
+      const uint32_t s = from + r * kTeamBlock + tid;
+      vv[r] = -1;
+      ww[r] = 0;
+      du[r] = 0;
+      if (from + r * kTeamBlock < len) {  // workgroup-uniform
+        // a wavefront's 64 slots are one word's
+        const uint32_t before = __shfl(pre, s >> 6, 64);
+        const unsigned long long bits = bcast64(fw, s >> 6) & (~0ull >> (63 - lane));
+        if (s < len) {
+          const uint32_t i = before + __popcll(bits) - 1u;  // slot 0 starts entry 0
+          const uint32_t arc =
+              i < kTeamSlots ? static_cast<uint32_t>(sm.list[cur].st[i]) + (s - sm.list[cur].pre[i]) : a.m;
+          if (arc < a.m) {
+            if (kPacked) {
+              load_arc<true, kNarrow>(a, arc, &vv[r], &ww[r]);
+            } else {
+              vv[r] = *at<kNarrow>(a.cols, arc);
+              if (kSssp) ww[r] = *at<kNarrow>(a.weights, arc);
+            }
+            if (kSssp) {
+              const uint32_t u = static_cast<uint32_t>(sm.list[cur].node[i]);
+              du[r] = sm.list[cur].du[i];
+              if (u >= a.n) {
+                bad = true;
+                vv[r] = -1;
+              } else if (static_cast<uint32_t>(ld_agent(at<kNarrow>(a.dstate, u)) >> 32) < du[r]) {
+                vv[r] = -1;  // improved since: pushed again by whoever did
+              }
+            }
+          } else {
+            bad = true;
+          }
+        }
+      }
+    }
+  };
+  // Relaxes them; the nodes to expand next go to the other list.
+  auto relax = [&](uint32_t from) {
+    const bool eager = E <= kTeamEager;
+    bool win[kTeamU];
+    int32_t s0[kTeamU], s1[kTeamU];
+#pragma unroll
+    for (int r = 0; r < kTeamU; ++r) {
+      if (vv[r] >= 0 && static_cast<uint32_t>(vv[r]) >= a.n) {  // malformed cols (see lbg_validate_csr)
+        bad = true;
+        vv[r] = -1;
+      }
+      win[r] = vv[r] >= 0;
+      s0[r] = 0;
+      s1[r] = 0;
+    }
+    if (!eager) {
+      unsigned long long x[kTeamU];
+#pragma unroll
+      for (int r = 0; r < kTeamU; ++r) {
+        x[r] = 0ull;
+        if (win[r])
+          x[r] = kSssp ? ld_agent(at<kNarrow>(a.dstate, static_cast<uint32_t>(vv[r])))
+                       : ld_agent(at<kNarrow>(a.visited, static_cast<uint32_t>(vv[r]) >> 5));
+      }
+#pragma unroll
+      for (int r = 0; r < kTeamU; ++r)
+        win[r] = win[r] && (kSssp ? du[r] + ww[r] < static_cast<uint32_t>(x[r] >> 32)
+                                  : !((x[r] >> (vv[r] & 31)) & 1ull));
+    }
+#pragma unroll
+    for (int r = 0; r < kTeamU; ++r) {
+      if (win[r] && eager) {
+        s0[r] = *at<kNarrow>(a.offsets, vv[r]);
+        s1[r] = *at<kNarrow>(a.offsets, vv[r] + 1);
+      }
+    }
+    unsigned long long old[kTeamU];
+#pragma unroll
+    for (int r = 0; r < kTeamU; ++r) {
+      old[r] = 0ull;
+      if (win[r]) {
+        ++atom;
+        if (kSssp)
+          old[r] = atomicMin(at<kNarrow>(a.dstate, static_cast<uint32_t>(vv[r])),
+                             static_cast<unsigned long long>(du[r] + ww[r]) << 32);
+        else
+          old[r] = atomicOr(at<kNarrow>(a.visited, static_cast<uint32_t>(vv[r]) >> 5), 1u << (vv[r] & 31));
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kTeamU; ++r) {
+      if (!win[r]) continue;
+      if (!kSssp) {
+        win[r] = !((old[r] >> (vv[r] & 31)) & 1ull);
+        if (win[r]) {
+          *at<kNarrow>(a.levels, vv[r]) = static_cast<int32_t>(L + 1);
+          ++upd;
+        }
+      } else {
+        const uint32_t alt = du[r] + ww[r];
+        const uint32_t was = static_cast<uint32_t>(old[r] >> 32);
+        win[r] = alt < was;
+        if (win[r]) {
+          *at<kNarrow>(a.d16, vv[r]) = f16_of(alt);  // filter of the one-level launches
+          ++upd;
+          if (was > thr) {  // near-far only: it was not queued so far
+            win[r] = alt <= thr;
+            far_move<kNarrow>(a, static_cast<uint32_t>(vv[r]), was, win[r]);
+          }
+        }
+      }
+      if (win[r] && !eager) {
+        s0[r] = *at<kNarrow>(a.offsets, vv[r]);
+        s1[r] = *at<kNarrow>(a.offsets, vv[r] + 1);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kTeamU; ++r) {
+      if (from + r * kTeamBlock >= len) continue;
+      const int32_t d = s1[r] - s0[r];
+      // a node without out-arcs has nothing to expand
+      put_all(cur ^ 1u, win[r] && d > 0, vv[r], s0[r], d, du[r] + ww[r]);
+    }
+  };
+
+  if (E > 0u) stage();
+  for (;;) {
+    const bool fits = arcs <= kTeamSlots;
+    len = fits ? arcs : 0u;
+    if (fits)
+      for (uint32_t k = tid; k < cnt; k += kTeamBlock) {
+        const uint32_t s = sm.list[cur].pre[k];
+        atomicOr(&sm.flag[s >> 6], 1ull << (s & 63));
+      }
     __syncthreads();
+    load(0u);
+    if (known || (!staged && (rounds == 0u || !fits))) {
+      if (!known) {
+        ++e;
+        alive = team_exchange<kSssp, false>(a, sm, e, me, P, payload());
+        if (!alive) break;
+        if (kSssp) ++L;
+      }
+      known = false;
+      nf = sm.segn[P];
+      // several rounds until the next exchange only while the frontier is
+      // small and steady: else some workgroups' lists grow while others idle
+      rounds = kSssp && sm.sege[P] <= P * kTeamCalm && sm.sege[P] <= 2 * E ? kTeamRounds : 1u;
+      E = sm.sege[P];
+      if (E == 0u) {
+        if (!far) {
+          done = true;
+          break;
+        }
+        // Split the far set (see near_far_init): this workgroup's share of
+        // its words; nodes beyond what it can push stay in it.
+        if (tid < kTeamSlots / 64) sm.flag[tid] = 0ull;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // moves in and out of the far set
+        __syncthreads();
+        ++e;
+        alive = team_exchange<kSssp, false>(a, sm, e, me, P, 0ull);
+        if (!alive) break;
+        if constexpr (kSssp) {
+          far_raise(delta0, most, &thr, &delta);
+          most = 0u;
+          const uint32_t share = (a.words + P - 1) / P;
+          const uint32_t k1 = min((me + 1) * share, a.words);
+          for (uint32_t k0 = me * share; k0 < k1; k0 += kTeamBlock) {
+            const uint32_t k = k0 + tid;
+            const uint32_t had = k < k1 ? ld_agent(at<kNarrow>(a.far, k)) : 0u;
+            if (had) sm.found = 1u;
+            uint32_t left = had, kept = 0u;
+            while (__any(left != 0u)) {
+              constexpr int kB = 4;
+              int32_t v[kB], s0[kB], s1[kB];
+              uint32_t d[kB];
+#pragma unroll
+              for (int b = 0; b < kB; ++b) {
+                v[b] = left ? static_cast<int32_t>(32 * k + __builtin_ctz(left)) : -1;
+                left &= left - 1u;
+              }
+#pragma unroll
+              for (int b = 0; b < kB; ++b) {
+                d[b] = kSsspInf;
+                s0[b] = 0;
+                s1[b] = 0;
+                if (v[b] >= 0) {
+                  d[b] = static_cast<uint32_t>(ld_agent(at<kNarrow>(a.dstate, static_cast<uint32_t>(v[b]))) >> 32);
+                  s0[b] = *at<kNarrow>(a.offsets, v[b]);
+                  s1[b] = *at<kNarrow>(a.offsets, v[b] + 1);
+                }
+              }
+#pragma unroll
+              for (int b = 0; b < kB; ++b) {
+                // room for this push and one in flight of every wavefront
+                const bool room = (sm.push >> 32) + kTeamBlock <= kTeamSlots;
+                const bool go = v[b] >= 0 && d[b] <= thr && __any(room);
+                if (v[b] >= 0 && !go) kept |= 1u << (v[b] & 31);
+                put_all(cur ^ 1u, go && s1[b] > s0[b], v[b], s0[b], s1[b] - s0[b], d[b]);
+              }
+            }
+            if (kept != had) st_agent(at<kNarrow>(a.far, k), kept);
+          }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        turn();
+        const bool found = sm.found != 0u;
+        ++e;
+        alive = team_exchange<kSssp, false>(a, sm, e, me, P, payload() | (found ? 1ull << 33 : 0ull));
+        if (!alive) break;
+        if (tid == 0) sm.found = 0u;
+        ++L;
+        nf = sm.segn[P];
+        E = sm.sege[P];
+        if (E == 0u && !sm.any_found) {
+          done = true;
+          break;
+        }
+        known = true;
+        continue;
+      }
+      const bool leave = E > limit || L - L0 >= max_levels;
+      if (leave || sm.most > max(kSssp ? kTeamOwnSssp : kTeamOwnBfs, 2 * ((E + P - 1) / P)) || sm.most > kTeamSlots) {
+        if (tid < kTeamSlots / 64) sm.flag[tid] = 0ull;
+        if (kSssp && (leave || nf > a.node_cap)) {
+          // only the entry with its node's distance: one per node, so the
+          // worklist holds them
+          __syncthreads();
+          for (uint32_t k0 = 0; k0 < cnt; k0 += kTeamBlock) {
+            const uint32_t k = k0 + tid;
+            int32_t v = 0, s0 = 0, d = 0;
+            uint32_t x = 0;
+            bool keep = false;
+            if (k < cnt) {
+              v = sm.list[cur].node[k];
+              x = sm.list[cur].du[k];
+              s0 = sm.list[cur].st[k];
+              d = static_cast<int32_t>((k + 1 < cnt ? sm.list[cur].pre[k + 1] : arcs) - sm.list[cur].pre[k]);
+              keep = static_cast<uint32_t>(v) < a.n &&
+                     static_cast<uint32_t>(ld_agent(at<kNarrow>(a.dstate, static_cast<uint32_t>(v))) >> 32) == x;
+            }
+            put_all(cur ^ 1u, keep, v, s0, d, x);
+          }
+          turn();
+          ++e;
+          alive = team_exchange<kSssp, false>(a, sm, e, me, P, payload());
+          if (!alive) break;
+          nf = sm.segn[P];
+        }
+        __syncthreads();  // the prefixes are read before the next exchange writes them
+        if (leave || sm.most >= kTeamArcs) {
+          ++e;
+          alive = team_exchange<kSssp, true>(a, sm, e, me, P, arcs);
+          if (!alive) break;
+        }
+        E = sm.sege[P];
+        spill(leave || E > limit);
+        if (leave || E > limit) break;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        ++e;
+        alive = team_exchange<kSssp, false>(a, sm, e, me, P, 0ull);
+        if (!alive) break;
+        if (E > 0u) stage();
+        else cnt = arcs = 0u;
+        staged = true;
+        rounds = 1u;
+        continue;
+      }
+    }
+    staged = false;
+    most = max(most, E);
+    tot_f += tid == 0 ? cnt - part : 0u;
+    part = 0u;
+    tot_e += tid == 0 ? arcs : 0u;
+    --rounds;
+    if (len) relax(0u);  // workgroup-uniform
+    for (uint32_t from = kTeamPass; from < len; from += kTeamPass) {
+      load(from);
+      relax(from);
+    }
+    turn();
+    if (tid < kTeamSlots / 64) sm.flag[tid] = 0ull;
+    __syncthreads();
+    if (!kSssp) ++L;
+    ++levels;
   }
   if (__any(bad) && lane == 0) atomicOr(&a.ctl->error, kErrBadArc);
   // Bookkeeping of every level run here, then the tail of level L (the next
   // to expand) and a cleared counter for the level after it.
   if (me == 0u && tid == 0 && alive) {
     a.team->epoch = e;
-    a.ctl->levels = L;
-    a.ctl->frontier_entries += tot_f;
-    a.ctl->edges_scanned += tot_e;
-    a.ctl->p_frontier_entries += tot_f;
-    a.ctl->p_edges_scanned += tot_e;
+    a.ctl->levels += levels;
+    a.ctl->next = L;
+    level_next(a, launch, L, true);
+    if (far) {
+      a.team->thr[L % 3] = thr;
+      a.team->delta[L % 3] = delta;
+      a.team->most[L % 3] = most;
+      if (done) a.ctl->split_at = L;
+    }
     st_agent(&a.ctl->ctr[L % 3], E ? (static_cast<unsigned long long>(nf) << 32) | E : 0ull);
     st_agent(&a.ctl->ctr[(L + 1) % 3], 0ull);
   }
   // the balanced kernel's tile counters of level L (see expand_level)
   if (me == 0u && tid < static_cast<uint32_t>(kXcds)) a.ctl->xstat[tid][8 + L % 3] = 0ull;
+  if (tid == 0) {
+    if (tot_f) {
+      atomicAdd(&a.ctl->frontier_entries, tot_f);
+      atomicAdd(&a.ctl->p_frontier_entries, tot_f);
+    }
+    if (tot_e) {
+      atomicAdd(&a.ctl->edges_scanned, tot_e);
+      atomicAdd(&a.ctl->p_edges_scanned, tot_e);
+    }
+  }
   if (a.count_stats) {
     const uint32_t su = wave_sum(upd), sa = wave_sum(atom);
     if (lane == 0) {

@@ -1,4 +1,4 @@
-"""The small-frontier team (levels of at most 262,144 arcs run on the device by
+"""The small-frontier team (levels of at most 524,288 arcs run on the device by
 up to 128 workgroups) against the oracle, bit for bit, at the sizes where its
 cuts fall: one arc per level, hubs that span every workgroup, levels of exactly
 the largest size and one arc more, and hand-overs to one-level launches and
@@ -18,7 +18,7 @@ if not torch.cuda.is_available():
 from paper_1711_00231_amd import lbg  # noqa: E402
 
 O = oracle.get()
-LIMIT = 128 * 2048  # arcs of a level that the team takes
+LIMIT = 128 * 4096  # arcs of a level that the team takes
 
 
 @pytest.fixture(autouse=True)
@@ -51,7 +51,7 @@ def _fan(width, tail=3, salt=0):
 
 def _cases():
     yield "path", pins.path_graph(300, np.arange(1, 300) % 9), 0
-    for width in (1, 63, 64, 2047, 2048, 2049, 128 * 64, LIMIT - 1, LIMIT, LIMIT + 1):
+    for width in (1, 63, 64, 2047, 2048, 2049, 4096, 128 * 64, LIMIT - 1, LIMIT, LIMIT + 1):
         yield (f"fan{width}", *_fan(width, salt=width))
     for n, k in ((7, 1), (129, 3), (5000, 8), (40000, 5), (90001, 11)):
         yield f"uniform{n}x{k}", graphgen.uniform(n=n, k=k, salt=n), 1
@@ -133,3 +133,38 @@ def test_teams_side_by_side():
         t.join(100)
     assert not any(t.is_alive() for t in ts)
     assert not bad, bad
+
+
+@pytest.mark.parametrize("layout", ["csr", "packed", "ordered"])
+def test_near_far(layout):
+    """SSSP solves that defer far nodes (at least 2^20 arcs, at most 16 per
+    node): long paths, gaps far beyond the threshold step, all weights zero,
+    equal weights, and one weight that dwarfs the others."""
+    rng = np.random.default_rng(7)
+    road = graphgen.grid(640, 520, shortcut_frac=0)
+    uni = graphgen.uniform(n=140_000, k=8, salt=3)
+    graphs = [(road, 77), (graphgen.grid(600), 4), (uni, 11)]
+    for w in (np.zeros(uni.m), np.full(uni.m, 7), np.where(rng.random(uni.m) < 1e-4, 90_000, 1),
+              np.where(np.arange(uni.m) % 8 == 0, 1, 200)):
+        graphs.append((graphgen.Graph("w", uni.offsets, uni.cols, w.astype(np.uint32)), 11))
+    # two halves joined by one heavy arc: the far set is empty of near nodes
+    # until the threshold has jumped the gap
+    half = graphgen.uniform(n=70_000, k=8, salt=9)
+    off = np.concatenate([half.offsets, half.offsets[1:] + half.m]).astype(np.int32)
+    cols = np.concatenate([half.cols, half.cols + half.n]).astype(np.int32)
+    w = np.concatenate([half.weights, half.weights]).astype(np.uint32)
+    k = int(half.offsets[1234])
+    cols[k], w[k] = half.n + 5, 4_000_000
+    graphs.append((graphgen.Graph("gap", off, cols, w), 3))
+    ws = lbg.Workspace()
+    for g, s in graphs:
+        assert (1 << 20) <= g.m <= 16 * g.n
+        dg = lbg.DeviceGraph.from_numpy(g.offsets, g.cols, g.weights)
+        if layout == "packed" and int(g.weights.max()) > 8191:
+            continue  # ids and weights do not fit one word
+        exp = O.dijkstra(g.offsets, g.cols, g.weights, s)
+        for wide in (0, 1):
+            lbg.set_addressing(wide)
+            d, st = lbg.sssp(dg, s, workspace=ws, packed=layout == "packed", ordered=layout == "ordered", stats=True)
+            assert np.array_equal(d.cpu().numpy().view(np.uint32), exp), (g.name, s, wide)
+            assert st["edges_scanned"] >= g.reached_arcs(exp != 0xFFFFFFFF)
