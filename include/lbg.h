@@ -160,7 +160,7 @@ int lbg_bfs(const int32_t* offsets, const int32_t* cols, int32_t n, int64_t m, i
  * newly reached node gets its level by a plain store, then one pass over the
  * levels array builds the next worklist from the nodes of the new level, in
  * node order.  Smaller levels claim and push as before.  Results are the
- * same either way.  arcs < 0 (the default): n / 4 for a graph of n nodes,
+ * same either way.  arcs < 0 (the default): n / 32 for a graph of n nodes,
  * of the levels too large for the small-frontier kernel (more than 524288
  * arcs); 0: every level; >= 2^32: never.  Process-wide, read when a solve starts;
  * lbg_get_bfs_scan_min returns the setting (-1 for the default).  Always

@@ -220,7 +220,7 @@ int grid_blocks() { return grids().bal[0][1]; }
 std::mutex g_bins_mu;
 lbg_bins g_bins{256, 16, 1024};  // what the autotuner picks on R-MAT scale 22
 int32_t g_slice_min = 512;       // LBG_SLICED: degree from which a node is split by slice
-int64_t g_bfs_scan_min = -1;     // balanced BFS: arcs from which a level runs in scan mode (< 0: n / 4)
+int64_t g_bfs_scan_min = -1;     // balanced BFS: arcs from which a level runs in scan mode (< 0: n / 32)
 std::atomic<int32_t> g_addressing{0};  // 0: 32-bit element offsets when every array fits, 1: always 64-bit
 int32_t g_hier_mdt = 0;          // LBG_HIER: fixed MDT (0 = the histogram rule per solve)
 
@@ -248,30 +248,11 @@ thread_local PinnedCtl g_pinned;
 // enqueues that many, so a typical solve needs one read-back and few empty
 // launches.
 thread_local uint32_t g_big_hint[2] = {0u, 0u};
-// Balanced solves of graphs of at most this many arcs read back after their
-// first team launch instead of enqueueing one-level launches behind it: most
-// are done by then (an empty launch costs 2 us, a read-back about 15).
+// SSSP solves of sparse graphs of at most this many arcs are expected to stay
+// in the team.
 constexpr uint32_t kTeamDense = 512;  // arcs per team workgroup, see solve()
 constexpr int64_t kSmallGraph = int64_t{2} << 20;
 
-// Balanced BFS: the launches that ran in scan mode in this thread's solves of
-// a graph (keyed by offsets pointer, n, m), accumulated since the last
-// re-check.  A later solve lets only those launches and their neighbours scan,
-// and launches the compaction kernel only after them, so graphs whose levels
-// never reach the threshold stop paying for compaction launches that would
-// find nothing to do (~2 us each).  A graph not in the table, and every 16th
-// solve of one that is (the re-check, which restarts the record), may scan
-// in any launch.  Sources whose big levels lie elsewhere only lose speed: a
-// level that may not scan claims and pushes.
-struct ScanHint {
-  const void* off = nullptr;
-  int32_t n = 0;
-  int64_t m = 0;
-  uint64_t mask = 0;
-  uint32_t uses = 0;
-};
-thread_local ScanHint g_scan_hint[4];
-thread_local uint32_t g_scan_hint_next = 0;
 thread_local std::vector<hipEvent_t> g_events;
 // Profiling mode: per timed launch, its level (-1 = small-frontier launch)
 // and the index of the event recorded right after it; the launch's interval
@@ -459,10 +440,11 @@ int solve(const Problem& P) {
       std::lock_guard<std::mutex> lk(g_bins_mu);
       smin = g_bfs_scan_min;
     }
-    // default n / 4, measured: R-MAT 22 BFS 10 % faster than never scanning
-    // (n / 2: 0.5 % faster still), the 2048 x 2048 grid with shortcuts 8.5 %
-    // (n / 2: its levels never reach it)
-    if (smin < 0) smin = std::max<int64_t>(1, P.n / 4);
+    // default n / 32: of the levels beyond the team's limit, a scan level costs
+    // less than claims and pushes unless the graph is far larger than they are
+    // (2048 x 2048 grid, 500 K arcs: 21 + 12 us for the compaction of 4 M
+    // nodes, against 55 us)
+    if (smin < 0) smin = std::max<int64_t>(1, P.n / 32);
     else team_limit = static_cast<uint32_t>(std::min<int64_t>(team_limit, smin > 0 ? smin - 1 : 0));
     a.scan_min = static_cast<uint32_t>(std::min<int64_t>(smin, 0xffffffffll));
   }
@@ -473,23 +455,14 @@ int solve(const Problem& P) {
   if (P.is_sssp && P.m > 16 * static_cast<int64_t>(P.n)) team_limit = std::min(team_limit, a.tblocks * kTeamDense);
   // a level can only run in scan mode if the graph has that many arcs
   const bool scan_possible = static_cast<int64_t>(a.scan_min) <= P.m;
-  ScanHint* shint = nullptr;
-  if (scan_possible) {
-    for (ScanHint& h : g_scan_hint)
-      if (h.off == P.offsets && h.n == P.n && h.m == P.m) shint = &h;
-    if (!shint) {
-      shint = &g_scan_hint[g_scan_hint_next++ % 4];
-      *shint = ScanHint{P.offsets, P.n, P.m, 0ull, 0u};
-    }
-  }
-  const bool scan_any = scan_possible && shint->uses % 16u == 0u;  // unknown, or a periodic re-check
-  const uint64_t scan_near = scan_possible ? (shint->mask | (shint->mask << 1) | (shint->mask >> 1)) : 0ull;
-  auto scan_at = [&](uint32_t k) {
-    return scan_possible && (scan_any || (k < 64u && ((scan_near >> k) & 1ull)));
-  };
-  const int compact_blocks = static_cast<int>(
-      std::max<int64_t>(1, std::min<int64_t>((static_cast<int64_t>(P.n) + lbg::kCompactChunk - 1) / lbg::kCompactChunk,
-                                            grids().bal[0][1])));
+  // Every level that reaches the one-level launches scans (the default on
+  // graphs of up to 2^24 nodes; an `alone` submission aside): then a compaction leaves the filters as the
+  // next level needs them, and only the first launch after a team launch is
+  // preceded by the filter merge.
+  const bool scan_all = scan_possible && a.scan_min <= team_limit + 1u;
+  const bool wide_chunk = P.n >= (1 << 22);
+  const int64_t chunk = lbg::kCompactBlock * (wide_chunk ? 16 : 4);
+  const int compact_blocks = static_cast<int>(std::min<int64_t>((P.n + chunk - 1) / chunk, 2 * cu_count()));
   const bool sl = strat == LBG_SLICED;
   const bool split = strat == LBG_SPLIT;
   a.child_base = P.child_base;
@@ -566,6 +539,7 @@ int solve(const Problem& P) {
   }
   HIP_TRY(hipGetLastError());
 
+  bool merge = true;  // the next launch is the first after a team launch (or of the solve)
   auto launch = [&](uint32_t L) {
     if (P.is_sssp) {
       switch (strat) {
@@ -626,18 +600,24 @@ int solve(const Problem& P) {
           else hipLaunchKernelGGL((lbg::k_expand_balanced<false, false, false, false, true>), dim3(GR.bal_s[sv][nw]), dim3(lbg::kBlock), 0, st, a, L);
           break;
         default:
-          if (scan_at(L)) {  // may scan: the filter merge precedes, the compaction follows
-            if (narrow) hipLaunchKernelGGL((lbg::k_bfs_prep<true>), dim3(GR.bal[sv][nw]), dim3(lbg::kBlock), 0, st, a, L);
-            else hipLaunchKernelGGL((lbg::k_bfs_prep<false>), dim3(GR.bal[sv][nw]), dim3(lbg::kBlock), 0, st, a, L);
+          if (scan_possible) {  // may scan: the filter merge precedes, the compaction follows
+            const dim3 cg(compact_blocks), cb(lbg::kCompactBlock);
+            if (merge || !scan_all) {
+              if (narrow) hipLaunchKernelGGL((lbg::k_bfs_prep<true>), dim3(GR.bal[sv][nw]), dim3(lbg::kBlock), 0, st, a, L);
+              else hipLaunchKernelGGL((lbg::k_bfs_prep<false>), dim3(GR.bal[sv][nw]), dim3(lbg::kBlock), 0, st, a, L);
+            }
             if (narrow) hipLaunchKernelGGL((lbg::k_expand_balanced<false, true>), dim3(GR.bal[sv][nw]), dim3(lbg::kBlock), 0, st, a, L);
             else hipLaunchKernelGGL((lbg::k_expand_balanced<false, false>), dim3(GR.bal[sv][nw]), dim3(lbg::kBlock), 0, st, a, L);
-            if (narrow) hipLaunchKernelGGL((lbg::k_bfs_compact<true>), dim3(compact_blocks), dim3(lbg::kBlock), 0, st, a, L);
-            else hipLaunchKernelGGL((lbg::k_bfs_compact<false>), dim3(compact_blocks), dim3(lbg::kBlock), 0, st, a, L);
+            if (wide_chunk) {
+              if (narrow) hipLaunchKernelGGL((lbg::k_bfs_compact<true, 16>), cg, cb, 0, st, a, L);
+              else hipLaunchKernelGGL((lbg::k_bfs_compact<false, 16>), cg, cb, 0, st, a, L);
+            } else {
+              if (narrow) hipLaunchKernelGGL((lbg::k_bfs_compact<true, 4>), cg, cb, 0, st, a, L);
+              else hipLaunchKernelGGL((lbg::k_bfs_compact<false, 4>), cg, cb, 0, st, a, L);
+            }
           } else {
-            KArgs ap = a;
-            ap.scan_min = 0xffffffffu;  // push mode
-            if (narrow) hipLaunchKernelGGL((lbg::k_expand_balanced<false, true>), dim3(GR.bal[sv][nw]), dim3(lbg::kBlock), 0, st, ap, L);
-            else hipLaunchKernelGGL((lbg::k_expand_balanced<false, false>), dim3(GR.bal[sv][nw]), dim3(lbg::kBlock), 0, st, ap, L);
+            if (narrow) hipLaunchKernelGGL((lbg::k_expand_balanced<false, true>), dim3(GR.bal[sv][nw]), dim3(lbg::kBlock), 0, st, a, L);
+            else hipLaunchKernelGGL((lbg::k_expand_balanced<false, false>), dim3(GR.bal[sv][nw]), dim3(lbg::kBlock), 0, st, a, L);
           }
           break;
       }
@@ -658,6 +638,13 @@ int solve(const Problem& P) {
   uint32_t seq = 0;            // team launches among them
   const int kind = P.is_sssp ? 1 : 0;
   uint32_t batch = small_ok && g_big_hint[kind] ? std::min<uint32_t>(g_big_hint[kind], 16) : 8;
+  // how many one-level launches can find work: a BFS expands every arc once,
+  // so at most m / (team_limit + 1) levels outgrow the team; an SSSP solve of a
+  // graph of few arcs has none, most likely (then it reads back first: an
+  // empty launch costs 2 us, a read-back about 15)
+  const int64_t most_big = !small_ok ? 64 : !P.is_sssp ? P.m / (int64_t{team_limit} + 1)
+                           : P.m > (P.m > 16 * static_cast<int64_t>(P.n) ? int64_t{4} * team_limit : kSmallGraph) ? 64 : 0;
+  if (small_ok && !P.is_sssp) batch = static_cast<uint32_t>(std::clamp<int64_t>(most_big, 1, batch));
   bool first = true, alone = false;
   uint64_t ef = 1;
   size_t nev = 0;
@@ -703,6 +690,7 @@ int solve(const Problem& P) {
   auto one_level = [&](uint32_t count) -> int {
     for (uint32_t i = 0; i < count; ++i) {
       ones |= 1ull << (k & 63);
+      merge = i == 0 || alone;  // alone: levels below the threshold push, which leaves the filters behind
       launch(k);
       const int r = launched(k);
       if (r != LBG_OK) return r;
@@ -720,9 +708,8 @@ int solve(const Problem& P) {
     } else {
       a.min_arcs = team_limit;
       if (ef <= team_limit && (rc = team()) != LBG_OK) return rc;
-      // A graph of up to kSmallGraph arcs is mostly done by now: read back
-      // first.  Near-far solves come back to big levels after each split.
-      if (first ? P.m > kSmallGraph : ef > team_limit) {
+      // near-far solves come back to big levels after each split
+      if (first ? most_big > 0 : ef > team_limit) {
         for (int i = 0; i < (a.far ? 3 : 1); ++i) {
           if ((rc = one_level(a.far ? 6 : batch)) != LBG_OK) return rc;
           if ((rc = team()) != LBG_OK) return rc;
@@ -757,10 +744,6 @@ int solve(const Problem& P) {
     if (alone) batch = 8;
     first = false;
     L_prev = L;
-  }
-  if (shint) {
-    shint->mask = scan_any ? host->scan_levels : (shint->mask | host->scan_levels);
-    ++shint->uses;
   }
   if (strat == LBG_HIER && !P.no_alloc) {
     g_hier_sched.assign(static_cast<size_t>(lbg::kHierTraceLevels) * lbg::kHierTraceSubs, 0u);

@@ -60,11 +60,10 @@ struct Ctl {
   unsigned int level_base;    // graph-launched batches: first level of the next replay
   unsigned int sub_cnt[3];    // hierarchical strategy: sublist sizes of three sub-iterations
   unsigned int split_at;      // near-far SSSP: 1 + the last step that split the far set,
-  unsigned long long scan_levels;  // BFS: bit k set when launch k (< 64) ran in scan mode
   unsigned int far_seen;      //   and 1 + the last one that found a node in it
   unsigned int pad0;
   unsigned long long worked;  // balanced: bit k % 64 set when launch k found work
-  unsigned long long pad1;
+  unsigned long long pad1[2];
   // [x][0] updates, [x][1] global atomics issued; [x][2], [x][3] the same for
   // levels run by the small-frontier kernel; [x][4 + L % 3] the packed tail
   // (nodes << 32 | edges) of slice x's worklist of level L (destination-

@@ -307,7 +307,6 @@ __device__ __forceinline__ void init_state(const KArgs& a, int32_t src, uint32_t
     a.ctl->edges_scanned = 0ull;
     a.ctl->p_frontier_entries = 0ull;
     a.ctl->p_edges_scanned = 0ull;
-    a.ctl->scan_levels = 0ull;
     a.ctl->next = 0u;
     a.ctl->worked = 0ull;
     a.ctl->split_at = 0u;
@@ -1106,12 +1105,18 @@ __global__ __launch_bounds__(kBlock) void k_expand_balanced(KArgs a, uint32_t k)
 // is L + 1 (the worklist of Section II-B, made by a scan of the node states
 // instead of by atomic claims; at R-MAT scale 22 a big level issues ~8 M
 // claim atomics, at a memory-side rate of ~25 G/s).  Each workgroup takes
-// 4096-node chunks: coalesced loads of the chunk's levels and offsets into
-// LDS, then thread t handles nodes 16t .. 16t + 15 of the chunk, so a block
-// scan gives every new node with out-arcs its place in node order and one
-// packed atomic reserves the chunk's entries: the next level reads the CSR
-// in order.  `visited` and next level's `seen` snapshot are rewritten from
-// the levels (each 32-node word by one thread, plain stores).
+// chunks of 1024 x kPer nodes: coalesced loads of the chunk's levels and
+// offsets into LDS, then thread t handles nodes kPer t .. kPer (t + 1) - 1 of
+// the chunk, so a block scan gives every new node with out-arcs its place in
+// node order and one packed atomic reserves the chunk's entries: the next
+// level reads the CSR in order.  `visited`, next level's `seen` snapshot and
+// every XCD's filter are rewritten from the levels (each 32-node word by one
+// thread, plain stores), so a following scan level needs no k_bfs_prep.
+// What bounds it: 8 bytes per node read, and the reservations, which all hit
+// one address (about 12 ns each).  kPer = 16 where that still gives a chunk to
+// every CU (n >= 2^22), else 4.  Against 256 threads and 4096 nodes with a
+// k_bfs_prep before every scan level: R-MAT 22, 42 -> 31 us between two big
+// levels; 2048 x 2048 grid, 33 -> 17 us.
 // Returns at once after a push-mode level, whose pushes already built
 // worklist L + 1.  The host launches it only after levels it allows to scan
 // (it passes scan_min = UINT32_MAX to the expansion of any other level), so
@@ -1135,24 +1140,28 @@ __global__ __launch_bounds__(kBlock) void k_bfs_prep(KArgs a, uint32_t k) {
   }
 }
 
-constexpr uint32_t kCompactPer = 16;                      // nodes per thread
-constexpr uint32_t kCompactChunk = kBlock * kCompactPer;  // nodes per workgroup step
-__device__ __forceinline__ uint32_t compact_slot(uint32_t j) { return j + (j >> 4); }  // one pad word per 16
+constexpr int kCompactBlock = 1024;
+// Chunk slot of node j: one pad word per kPer, so that threads reading kPer
+// consecutive nodes each hit different LDS banks.
+template <uint32_t kPer>
+__device__ __forceinline__ uint32_t compact_slot(uint32_t j) { return j + j / kPer; }
 
-template <bool kNarrow>
-__global__ __launch_bounds__(kBlock) void k_bfs_compact(KArgs a, uint32_t launch) {
+template <bool kNarrow, uint32_t kPer>
+__global__ __launch_bounds__(kCompactBlock) void k_bfs_compact(KArgs a, uint32_t launch) {
   const uint32_t L = level_of(a, launch);
   constexpr uint32_t T = TileCfg<false>::kEdges;
-  constexpr uint32_t kSlots = kCompactChunk + kCompactChunk / 16 + 1;
+  constexpr uint32_t kChunk = kCompactBlock * kPer;
+  constexpr uint32_t kSlots = kChunk + kCompactBlock + 1;
+  constexpr int kWv = kCompactBlock / 64;
+  static_assert(kPer <= 16 && 32 % kPer == 0, "a thread's nodes are part of one bitmap word");
   __shared__ int32_t lvs[kSlots];
   __shared__ int32_t offs[kSlots];
-  __shared__ uint32_t wsum[2][kWaves];
+  __shared__ uint32_t wsum[2][kWv];
   __shared__ unsigned long long base_sh;
   const unsigned long long c = __hip_atomic_load(&a.ctl->ctr[L % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t Ef = static_cast<uint32_t>(c);
   // push-mode level, or none was run
   if (Ef <= a.min_arcs || Ef < a.scan_min || !level_fits<false, false>(a, c)) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && launch < 64u) atomicOr(&a.ctl->scan_levels, 1ull << launch);
   Frontier nxt = a.fr[(L + 1) & 1];
   nxt.level = L + 1;
   const int nctr = (L + 1) % 3;
@@ -1160,44 +1169,48 @@ __global__ __launch_bounds__(kBlock) void k_bfs_compact(KArgs a, uint32_t launch
   const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int32_t want = static_cast<int32_t>(L + 1);
   uint32_t upd = 0;
-  for (uint32_t c0 = blockIdx.x * kCompactChunk; c0 < a.n; c0 += gridDim.x * kCompactChunk) {
-    // the chunk's levels and offsets (offsets of nodes c0 .. c0 + 4096)
+  for (uint32_t c0 = blockIdx.x * kChunk; c0 < a.n; c0 += gridDim.x * kChunk) {
+    // the chunk's levels and offsets (offsets of nodes c0 .. c0 + kChunk)
 #pragma unroll
-    for (uint32_t k = 0; k < kCompactPer; ++k) {
-      const uint32_t j = k * kBlock + tid, v = c0 + j;
-      lvs[compact_slot(j)] = v < a.n ? *at<kNarrow>(a.levels, v) : 0;
-      offs[compact_slot(j)] = v <= a.n ? *at<kNarrow>(a.offsets, v) : 0;
+    for (uint32_t k = 0; k < kPer; ++k) {
+      const uint32_t j = k * kCompactBlock + tid, v = c0 + j;
+      lvs[compact_slot<kPer>(j)] = v < a.n ? *at<kNarrow>(a.levels, v) : 0;
+      offs[compact_slot<kPer>(j)] = v <= a.n ? *at<kNarrow>(a.offsets, v) : 0;
     }
     if (tid == 0) {
-      const uint32_t v = c0 + kCompactChunk;
-      offs[compact_slot(kCompactChunk)] = v <= a.n ? *at<kNarrow>(a.offsets, v) : 0;
+      const uint32_t v = c0 + kChunk;
+      offs[compact_slot<kPer>(kChunk)] = v <= a.n ? *at<kNarrow>(a.offsets, v) : 0;
     }
     __syncthreads();
-    // this thread's 16 nodes: which are new, their degrees
-    const uint32_t j0 = tid * kCompactPer;
+    // this thread's kPer nodes: which are new, their degrees
+    const uint32_t j0 = tid * kPer;
     uint32_t newm = 0, reached = 0, cnt = 0, deg = 0;
 #pragma unroll
-    for (uint32_t k = 0; k < kCompactPer; ++k) {
+    for (uint32_t k = 0; k < kPer; ++k) {
       const uint32_t j = j0 + k;
-      const int32_t lv = lvs[compact_slot(j)];
+      const int32_t lv = lvs[compact_slot<kPer>(j)];
       if (c0 + j < a.n && lv != static_cast<int32_t>(kBfsInf)) reached |= 1u << k;
       if (c0 + j < a.n && lv == want) {
         newm |= 1u << k;
-        const uint32_t d = static_cast<uint32_t>(offs[compact_slot(j + 1)] - offs[compact_slot(j)]);
+        const uint32_t d = static_cast<uint32_t>(offs[compact_slot<kPer>(j + 1)] - offs[compact_slot<kPer>(j)]);
         cnt += d > 0u ? 1u : 0u;
         deg += d;
       }
     }
     upd += __popc(newm);
-    // The chunk's 32-node words of `visited` and of next level's `seen`:
-    // every node of level <= L + 1, which is exactly what the levels say
-    // now, so the even thread of a pair stores whole words, no read needed.
-    const uint32_t pair = static_cast<uint32_t>(__shfl_xor(static_cast<int>(reached), 1, 64));
-    if (!(tid & 1u) && c0 + j0 < a.n) {
-      const uint32_t word = reached | (pair << 16);
+    // The chunk's 32-node words of `visited`, of next level's `seen` and of
+    // every XCD's filter: the nodes of level <= L + 1, which is exactly what
+    // the levels say now, so whole words are stored, no read needed.
+    uint32_t word = reached << (j0 & 31);
+#pragma unroll
+    for (uint32_t x = 1; x < 32 / kPer; x <<= 1)
+      word |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(word), static_cast<int>(x), 64));
+    if ((j0 & 31) == 0u && c0 + j0 < a.n) {
       const uint32_t w = (c0 + j0) >> 5;
       *at<kNarrow>(a.visited, w) = word;
       *at<kNarrow>(seen_nxt, w) = word;
+#pragma unroll
+      for (int x = 0; x < kXcds; ++x) a.xfilter[static_cast<size_t>(x) * a.words + w] = word;
     }
     // block exclusive scan of (entries, arcs) in node order, one reservation
     const uint32_t ic = wave_incl_scan(cnt), ie = wave_incl_scan(deg);
@@ -1208,7 +1221,7 @@ __global__ __launch_bounds__(kBlock) void k_bfs_compact(KArgs a, uint32_t launch
     __syncthreads();
     uint32_t pc = ic - cnt, pe = ie - deg, tc = 0, te = 0;
 #pragma unroll
-    for (int k = 0; k < kWaves; ++k) {
+    for (int k = 0; k < kWv; ++k) {
       if (static_cast<uint32_t>(k) < wid) {
         pc += wsum[0][k];
         pe += wsum[1][k];
@@ -1222,11 +1235,11 @@ __global__ __launch_bounds__(kBlock) void k_bfs_compact(KArgs a, uint32_t launch
     uint32_t eb = static_cast<uint32_t>(base_sh) + pe;
     uint32_t i = 0;
 #pragma unroll
-    for (uint32_t k = 0; k < kCompactPer; ++k) {
+    for (uint32_t k = 0; k < kPer; ++k) {
       const uint32_t j = j0 + k;
       if (newm & (1u << k)) {
-        const int32_t s = offs[compact_slot(j)];
-        const int32_t d = offs[compact_slot(j + 1)] - s;
+        const int32_t s = offs[compact_slot<kPer>(j)];
+        const int32_t d = offs[compact_slot<kPer>(j + 1)] - s;
         if (d > 0) {
           write_entry<0, T, kNarrow>(a, nxt, nb + i, eb, static_cast<int32_t>(c0 + j), 0, s, d);
           ++i;
@@ -1236,7 +1249,10 @@ __global__ __launch_bounds__(kBlock) void k_bfs_compact(KArgs a, uint32_t launch
     }
     __syncthreads();  // LDS reused by the next chunk
   }
-  add_stats(a, upd, 0u);
+  if (a.count_stats) {
+    const uint32_t su = wave_sum(upd);
+    if (lane == 0 && su) atomicAdd(&a.ctl->xstat[blockIdx.x % kXcds][0], static_cast<unsigned long long>(su));
+  }
 }
 
 // Graph-launched batches: one replay of a graph runs levels level_base + k

@@ -11,6 +11,7 @@ import pytest
 
 import graphgen
 import oracle
+import pins
 
 pytestmark = pytest.mark.gpu
 
@@ -95,3 +96,18 @@ def test_scan_setting_roundtrip():
     assert lbg.get_bfs_scan_min() == 12345
     lbg.set_bfs_scan_min(-7)
     assert lbg.get_bfs_scan_min() == -1
+
+
+@pytest.mark.parametrize("n", [31, 33, 4095, 4097, 65537, (1 << 22) - 1, (1 << 22) + 1, (1 << 22) + 16385])
+def test_compaction_chunk_edges(n):
+    """Node counts around a bitmap word, a compaction chunk (4,096 nodes, or
+    16,384 from 2^22 nodes on) and the size where the chunk changes, every
+    level scanned and with the default threshold."""
+    g = graphgen.uniform(n=n, k=3, salt=n % 97)
+    dg = _dev(g)
+    exp = O.bfs(g.offsets, g.cols, 0)
+    for arcs in (0, -1):
+        lbg.set_bfs_scan_min(arcs)
+        got, st = lbg.bfs(dg, 0, stats=True)
+        assert np.array_equal(got.cpu().numpy(), exp), (n, arcs)
+        assert st["updates"] == int((exp != pins.BFS_INF).sum()) - 1
