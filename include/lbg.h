@@ -125,7 +125,9 @@ typedef enum {
  *         of SSSP worklist entries whose node improved again during the
  *         iteration that expands them (the node is queued for the next
  *         iteration, where its arcs are relaxed with the better distance).
- *         edges_scanned - edges_skipped arcs were read and relaxed.  0 for
+ *         edges_scanned - edges_skipped arcs were read and relaxed.  BFS of
+ *         a symmetric graph of at least 2^24 arcs: the arcs of levels whose
+ *         unreached nodes looked for a reached neighbour instead.  0 for other
  *         BFS and for strategies that relax every queued arc. */
 typedef struct {
   int32_t levels;

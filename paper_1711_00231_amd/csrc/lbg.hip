@@ -9,11 +9,13 @@
 #include <chrono>
 #include <atomic>
 #include <mutex>
+#include <random>
 #include <vector>
 
 #include "../../include/lbg.h"
 #include "lbg_kernels.hpp"
 #include "lbg_team.hpp"
+#include "lbg_pull.hpp"
 #include "lbg_sliced.hpp"
 #include "lbg_split.hpp"
 #include "lbg_order.hpp"
@@ -151,9 +153,9 @@ int cu_count() {
 }
 
 template <typename K>
-int resident_grid(K kernel) {
+int resident_grid(K kernel, int block = lbg::kBlock) {
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, lbg::kBlock, 0) != hipSuccess ||
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, 0) != hipSuccess ||
       per_cu <= 0)
     per_cu = 4;
   return per_cu * cu_count();
@@ -163,6 +165,7 @@ struct Grids {
   int bal[2][2], node[2], edge[2], edge_nc[2], multi[2], binned[2], hier[2];  // bal[is_sssp][narrow], multi[narrow]
   int sliced[2][2];                                      // [is_sssp][narrow], a multiple of 8 (>= 8)
   int bal_p[2];                                          // SSSP with packed arcs [narrow]
+  int sym[2], pull[2];                                   // BFS pull levels [narrow]
   int far[2][2];                                         // near-far SSSP [packed][narrow]
   int bal_s[2][2];                                       // split graph [is_sssp][narrow]
 };
@@ -197,6 +200,10 @@ const Grids& grids() {
     g[dev].multi[1] = resident_grid(lbg::k_expand_balanced<true, true, true>);
     g[dev].bal_p[0] = resident_grid(lbg::k_expand_balanced<true, false, false, true>);
     g[dev].bal_p[1] = resident_grid(lbg::k_expand_balanced<true, true, false, true>);
+    g[dev].sym[0] = resident_grid(lbg::k_bfs_sym<false>);
+    g[dev].sym[1] = resident_grid(lbg::k_bfs_sym<true>);
+    g[dev].pull[0] = resident_grid(lbg::k_bfs_pull<false>, lbg::kPullBlock);
+    g[dev].pull[1] = resident_grid(lbg::k_bfs_pull<true>, lbg::kPullBlock);
     g[dev].far[0][0] = resident_grid(lbg::k_expand_balanced<true, false, false, false, false, true>);
     g[dev].far[0][1] = resident_grid(lbg::k_expand_balanced<true, true, false, false, false, true>);
     g[dev].far[1][0] = resident_grid(lbg::k_expand_balanced<true, false, false, true, false, true>);
@@ -250,6 +257,16 @@ thread_local PinnedCtl g_pinned;
 thread_local uint32_t g_big_hint[2] = {0u, 0u};
 // SSSP solves of sparse graphs of at most this many arcs are expected to stay
 // in the team.
+// BFS solves of graphs of at least this many arcs may pull levels.
+constexpr int64_t kPullGraph = int64_t{1} << 24;
+// Key of k_bfs_sym's hash: drawn once per process.
+unsigned long long sym_key() {
+  static const unsigned long long key = [] {
+    std::random_device rd;
+    return (static_cast<unsigned long long>(rd()) << 32) | rd();
+  }();
+  return key;
+}
 constexpr uint32_t kTeamDense = 512;  // arcs per team workgroup, see solve()
 constexpr int64_t kSmallGraph = int64_t{2} << 20;
 
@@ -460,6 +477,13 @@ int solve(const Problem& P) {
   // next level needs them, and only the first launch after a team launch is
   // preceded by the filter merge.
   const bool scan_all = scan_possible && a.scan_min <= team_limit + 1u;
+  // Pull levels (lbg_pull.hpp): a pass over all arcs establishes symmetry, so
+  // the level must hold a good part of them (a quarter of what it costs to
+  // expand m / 16 arcs), and the graph enough for the extra launches to pay.
+  if (scan_all && P.m >= kPullGraph && a.scan_min <= P.m / 16) {
+    a.pull_min = static_cast<uint32_t>(P.m / 16);
+    a.sym_key = sym_key();
+  }
   const bool wide_chunk = P.n >= (1 << 22);
   const int64_t chunk = lbg::kCompactBlock * (wide_chunk ? 16 : 4);
   const int compact_blocks = static_cast<int>(std::min<int64_t>((P.n + chunk - 1) / chunk, 2 * cu_count()));
@@ -540,6 +564,7 @@ int solve(const Problem& P) {
   HIP_TRY(hipGetLastError());
 
   bool merge = true;  // the next launch is the first after a team launch (or of the solve)
+  uint32_t nth = 0;   // one-level launches since then
   auto launch = [&](uint32_t L) {
     if (P.is_sssp) {
       switch (strat) {
@@ -600,6 +625,10 @@ int solve(const Problem& P) {
           else hipLaunchKernelGGL((lbg::k_expand_balanced<false, false, false, false, true>), dim3(GR.bal_s[sv][nw]), dim3(lbg::kBlock), 0, st, a, L);
           break;
         default:
+          if (a.pull_min && nth < 2) {  // the first level worth pulling comes early
+            if (narrow) hipLaunchKernelGGL((lbg::k_bfs_sym<true>), dim3(GR.sym[nw]), dim3(lbg::kBlock), 0, st, a, L);
+            else hipLaunchKernelGGL((lbg::k_bfs_sym<false>), dim3(GR.sym[nw]), dim3(lbg::kBlock), 0, st, a, L);
+          }
           if (scan_possible) {  // may scan: the filter merge precedes, the compaction follows
             const dim3 cg(compact_blocks), cb(lbg::kCompactBlock);
             if (merge || !scan_all) {
@@ -614,6 +643,12 @@ int solve(const Problem& P) {
             } else {
               if (narrow) hipLaunchKernelGGL((lbg::k_bfs_compact<true, 4>), cg, cb, 0, st, a, L);
               else hipLaunchKernelGGL((lbg::k_bfs_compact<false, 4>), cg, cb, 0, st, a, L);
+            }
+            if (a.pull_min) {
+              const int64_t chunks = (static_cast<int64_t>(P.n) + lbg::kPullChunk - 1) / lbg::kPullChunk;
+              const dim3 pg(static_cast<unsigned>(std::min<int64_t>(chunks, GR.pull[nw]))), pb(lbg::kPullBlock);
+              if (narrow) hipLaunchKernelGGL((lbg::k_bfs_pull<true>), pg, pb, 0, st, a, L);
+              else hipLaunchKernelGGL((lbg::k_bfs_pull<false>), pg, pb, 0, st, a, L);
             }
           } else {
             if (narrow) hipLaunchKernelGGL((lbg::k_expand_balanced<false, true>), dim3(GR.bal[sv][nw]), dim3(lbg::kBlock), 0, st, a, L);
@@ -691,6 +726,7 @@ int solve(const Problem& P) {
     for (uint32_t i = 0; i < count; ++i) {
       ones |= 1ull << (k & 63);
       merge = i == 0 || alone;  // alone: levels below the threshold push, which leaves the filters behind
+      nth = i;
       launch(k);
       const int r = launched(k);
       if (r != LBG_OK) return r;

@@ -61,14 +61,16 @@ struct Ctl {
   unsigned int sub_cnt[3];    // hierarchical strategy: sublist sizes of three sub-iterations
   unsigned int split_at;      // near-far SSSP: 1 + the last step that split the far set,
   unsigned int far_seen;      //   and 1 + the last one that found a node in it
-  unsigned int pad0;
+  unsigned int sym_no;        // BFS: the graph is not symmetric
   unsigned long long worked;  // balanced: bit k % 64 set when launch k found work
-  unsigned long long pad1[2];
+  unsigned int sym_run;       // BFS: 1 + the launch that summed the arcs (k_bfs_sym), 0: none did
+  unsigned int pad0;
+  unsigned long long pad1;
   // [x][0] updates, [x][1] global atomics issued; [x][2], [x][3] the same for
   // levels run by the small-frontier kernel; [x][4 + L % 3] the packed tail
   // (nodes << 32 | edges) of slice x's worklist of level L (destination-
   // sliced strategy); [x][8 + L % 3] the balanced kernel's tile counter of
-  // XCD x for level L (single solves)
+  // XCD x for level L (single solves); [x][11] its part of k_bfs_sym's sum
   unsigned long long xstat[kXcds][16];
 };
 static_assert(sizeof(Ctl) == 128 + kXcds * 128, "Ctl layout");
@@ -156,6 +158,10 @@ struct KArgs {
   // Balanced one-level launches leave levels of at most min_arcs arcs (and
   // near-far splits) to the team launched behind them.  0: none.
   uint32_t min_arcs;
+  // BFS levels of at least pull_min arcs are pulled if the graph is
+  // symmetric (lbg_pull.hpp).  0: never.
+  uint32_t pull_min;
+  unsigned long long sym_key;  // of k_bfs_sym's hash
   const QInfo* qtab;     // batched solves
   uint32_t num_queries;
   uint32_t rows;         // batched solves: total elements of node state

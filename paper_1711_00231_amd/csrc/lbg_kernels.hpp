@@ -309,6 +309,7 @@ __device__ __forceinline__ void init_state(const KArgs& a, int32_t src, uint32_t
     a.ctl->p_edges_scanned = 0ull;
     a.ctl->next = 0u;
     a.ctl->worked = 0ull;
+    a.ctl->sym_run = 0u;
     a.ctl->split_at = 0u;
     a.ctl->far_seen = 0u;
   }
@@ -387,6 +388,45 @@ __device__ __forceinline__ void far_raise(uint32_t delta0, uint32_t most, uint32
   *thr = *thr < kSsspInf - d ? *thr + d : kSsspInf;
 }
 
+// A sample of arcs u -> v for symmetry (the last workgroup of k_init, while
+// the others clear the state; see lbg_pull.hpp): a thread takes a node, the
+// one of its first 8 neighbours with the fewest arcs, and looks for the way
+// back among those, if they are at most 32.  Nodes without such a neighbour
+// say nothing.
+__device__ __forceinline__ void sym_sample(const KArgs& a) {
+  __shared__ uint32_t no;
+  if (threadIdx.x == 0) no = 0u;
+  __syncthreads();
+  const uint32_t u = (threadIdx.x * 0x9e3779b1u + static_cast<uint32_t>(a.sym_key >> 20)) % a.n;
+  const uint32_t s = static_cast<uint32_t>(a.offsets[u]), e = static_cast<uint32_t>(a.offsets[u + 1]);
+  uint32_t vs = 0, ve = 0, best = 33;
+  if (s < e && e <= a.m) {
+    uint32_t v[8];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) v[k] = s + k < e ? static_cast<uint32_t>(a.cols[s + k]) : 0xffffffffu;
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) {
+      if (v[k] >= a.n || v[k] == u) continue;
+      const uint32_t p = static_cast<uint32_t>(a.offsets[v[k]]), q = static_cast<uint32_t>(a.offsets[v[k] + 1]);
+      if (p <= q && q <= a.m && q - p < best) {
+        best = q - p;
+        vs = p;
+        ve = q;
+      }
+    }
+  }
+  if (best <= 32u) {
+    bool back = false;
+    for (uint32_t p = vs; p < ve && !back; p += 8) {
+#pragma unroll
+      for (uint32_t k = 0; k < 8; ++k) back = back || (p + k < ve && static_cast<uint32_t>(a.cols[p + k]) == u);
+    }
+    if (!back) no = 1u;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) a.ctl->sym_no = no;
+}
+
 template <bool kSssp, bool kEdgeWl>
 __global__ __launch_bounds__(kBlock) void k_init(KArgs a, int32_t src) {
   const uint32_t gid = blockIdx.x * kBlock + threadIdx.x;
@@ -401,6 +441,7 @@ __global__ __launch_bounds__(kBlock) void k_init(KArgs a, int32_t src) {
     }
     return;
   }
+  if (!kSssp && a.pull_min && blockIdx.x == gridDim.x - 1) sym_sample(a);
   init_state<kSssp>(a, src, gid, stride);
   if (a.team) {
     if (a.far) {
@@ -1065,6 +1106,15 @@ __device__ __forceinline__ void expand_level(const KArgs& a, uint32_t L, unsigne
   add_stats(a, upd, atom, skip);
 }
 
+// The level is pulled (lbg_pull.hpp): it is large and the graph has been found
+// symmetric.  Grid-uniform once k_bfs_sym has run.
+__device__ __forceinline__ bool pulls(const KArgs& a, uint32_t Ef) {
+  if (a.pull_min == 0u || Ef < a.pull_min || a.ctl->sym_run == 0u || a.ctl->sym_no != 0u) return false;
+  unsigned long long sum = 0;
+  for (int x = 0; x < kXcds; ++x) sum += a.ctl->xstat[x][11];
+  return sum == 0ull;
+}
+
 // Balanced single solves: the level that launch number k of the solve finds
 // is known on the device only (a team launch runs any number of them); one
 // thread leaves it for the next launch and notes whether this one has work.
@@ -1090,6 +1140,7 @@ __device__ __forceinline__ void balanced_level(const KArgs& a, uint32_t k) {
     if (threadIdx.x == 0) atomicOr(&a.ctl->error, kErrNodeCap);
     return;
   }
+  if (!kSssp && !kSplit && pulls(a, static_cast<uint32_t>(c))) return;  // k_bfs_pull does the level
   expand_level<kSssp, kNarrow, kMulti, kPacked, kSplit, kFar>(a, L, c);
 }
 
@@ -1133,6 +1184,9 @@ __global__ __launch_bounds__(kBlock) void k_bfs_prep(KArgs a, uint32_t k) {
   const unsigned long long c = __hip_atomic_load(&a.ctl->ctr[L % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t Ef = static_cast<uint32_t>(c);
   if (Ef <= a.min_arcs || Ef < a.scan_min) return;
+  if (a.pull_min)  // a pull level reads the snapshot
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < a.words; i += gridDim.x * kBlock)
+      a.seen[L & 1][i] = *at<kNarrow>(a.visited, i);
   const uint32_t total = a.words * kXcds;
   for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < total; i += gridDim.x * kBlock) {
     const uint32_t v = *at<kNarrow>(a.visited, i % a.words);
@@ -1161,7 +1215,7 @@ __global__ __launch_bounds__(kCompactBlock) void k_bfs_compact(KArgs a, uint32_t
   const unsigned long long c = __hip_atomic_load(&a.ctl->ctr[L % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t Ef = static_cast<uint32_t>(c);
   // push-mode level, or none was run
-  if (Ef <= a.min_arcs || Ef < a.scan_min || !level_fits<false, false>(a, c)) return;
+  if (Ef <= a.min_arcs || Ef < a.scan_min || !level_fits<false, false>(a, c) || pulls(a, Ef)) return;
   Frontier nxt = a.fr[(L + 1) & 1];
   nxt.level = L + 1;
   const int nctr = (L + 1) % 3;

@@ -1,0 +1,293 @@
+// Pull levels of balanced BFS on symmetric graphs.
+//
+// On a skewed graph the one or two largest levels hold nearly all arcs, and
+// nearly all of those arcs point at nodes reached before: R-MAT scale 22
+// expands 125 M arcs in two levels to find 2.4 M nodes, one random read of
+// the filter each (about 170 G arcs/s).  If every arc u -> v has its reverse,
+// an unreached node can look for a reached one among its own arcs instead and
+// stop at the first (Beamer, Asanovic, Patterson 2012): any reached neighbour
+// of a node that is unreached after level L has level L.  Most find one among
+// their first few arcs.
+//
+// The caller's CSR is any directed graph, so symmetry is established in the
+// solve, and only when a level is about to be pulled:
+//  * k_init samples arcs between low-degree nodes; one without its reverse
+//    settles the matter (directed graphs of low degree stop here);
+//  * k_bfs_sym then reads every arc once, in order (a streaming pass, 4 bytes
+//    per arc), and adds sgn(v - u) * h({u, v}) over all arcs u -> v, h a
+//    64-bit hash with a key drawn at random when the library is loaded.  The
+//    sum over a symmetric graph is 0 by cancellation, always.  For any other
+//    graph it is a sum of hash values with non-zero coefficients, 0 with a
+//    chance of about 2^-64 over the keys, far below that of a memory error;
+//    such a graph is expanded as before.  (Single pairs cannot cancel: h is a
+//    bijection of the pair.)
+// R-MAT 22: 0.98 -> 0.48 ms for the solve, of which the pass over 513 MB of
+// arcs takes 174 us (2.9 TB/s) and the two pulled levels 112 + 38 us, where
+// expansion and compaction took 265 + 582 us; R-MAT 24: 4.28 -> 1.38 ms.
+#pragma once
+
+#include "lbg_kernels.hpp"
+
+namespace lbg {
+
+constexpr int kPullBlock = 512;
+constexpr uint32_t kPullPer = 8;  // nodes per thread and chunk
+constexpr uint32_t kPullChunk = kPullBlock * kPullPer;
+constexpr uint32_t kPullAlone = 32;  // arcs a lane tries before its wavefront helps
+constexpr uint32_t kSymItems = 16;   // arcs per lane of a tile of k_bfs_sym
+constexpr uint32_t kSymTile = 64 * kSymItems;
+
+__device__ __forceinline__ unsigned long long sym_hash(uint32_t u, uint32_t v, unsigned long long key) {
+  unsigned long long x = (static_cast<unsigned long long>(min(u, v)) << 32 | max(u, v)) ^ key;
+  x *= 0x9fb21c651e98df25ull;
+  x ^= x >> 32;
+  x *= 0xd6e8feb86659fd93ull;
+  return x ^ (x >> 29);
+}
+
+// Launched before the solve's one-level launches; does its pass once, before
+// the first level that is large enough to be pulled.  What bounds it: reading
+// cols in order.  Each wavefront takes one contiguous range of arcs, so it
+// looks its first node up once and then walks offsets and arcs together;
+// the arcs of 64 x 16 slots are mapped to nodes through an LDS bitmask of
+// node starts (one word per 64 slots, so a wavefront-wide uniform read).
+template <bool kNarrow>
+__global__ __launch_bounds__(kBlock) void k_bfs_sym(KArgs a, uint32_t launch) {
+  __shared__ unsigned long long flag_s[kWaves][kSymItems];
+  __shared__ uint32_t node_s[kWaves][kSymTile];
+  const uint32_t L = level_of(a, launch);
+  const uint32_t Ef = static_cast<uint32_t>(ld_agent(&a.ctl->ctr[L % 3]));
+  if (Ef < a.pull_min || Ef <= a.min_arcs || a.ctl->sym_no != 0u) return;
+  const uint32_t run = a.ctl->sym_run;
+  if (run != 0u && run != launch + 1u) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl->sym_run = launch + 1u;
+  const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  unsigned long long* flag = flag_s[wid];
+  uint32_t* start = node_s[wid];
+  // whole tiles per wavefront
+  const unsigned long long tiles = (static_cast<unsigned long long>(a.m) + kSymTile - 1) / kSymTile;
+  const unsigned long long W = static_cast<unsigned long long>(gridDim.x) * kWaves;
+  const unsigned long long g = static_cast<unsigned long long>(blockIdx.x) * kWaves + wid;
+  const uint32_t t0 = static_cast<uint32_t>(tiles * g / W), t1 = static_cast<uint32_t>(tiles * (g + 1) / W);
+  unsigned long long acc = 0;
+  bool bad = false;
+  if (t0 < t1) {
+    // the node that holds the range's first arc: the last with offset <= e
+    uint32_t lo = 0, hi = a.n;  // offsets[lo] <= e < offsets[hi] (or hi = n)
+    {
+      const uint32_t e = t0 * kSymTile;
+      while (hi - lo > 1) {
+        const uint32_t step = (hi - lo + 63) / 64;
+        const uint32_t i = lo + lane * step;
+        const bool le = i < hi && static_cast<uint32_t>(*at<kNarrow>(a.offsets, i)) <= e;
+        const uint32_t ranks = static_cast<uint32_t>(__popcll(__ballot(le)));
+        if (ranks == 0u) break;  // malformed offsets
+        lo += (ranks - 1) * step;
+        hi = min(hi, lo + step);
+      }
+    }
+    uint32_t cur = lo, next = lo + 1;  // node of the last slot so far, next node to place
+    for (uint32_t t = t0; t < t1; ++t) {
+      const uint32_t e0 = t * kSymTile, e1 = min(e0 + kSymTile, a.m);
+      if (lane < kSymItems) flag[lane] = 0ull;
+      wave_sync();
+      // starts of the nodes with arcs in this tile
+      for (;;) {
+        const uint32_t i = next + lane;
+        const uint32_t s = i < a.n ? static_cast<uint32_t>(*at<kNarrow>(a.offsets, i)) : 0xffffffffu;
+        const uint32_t f = i < a.n ? static_cast<uint32_t>(*at<kNarrow>(a.offsets, i + 1)) : 0xffffffffu;
+        const bool in = s < e1;  // offsets do not decrease: a prefix of the lanes
+        if (in && s >= e0 && f > s) {
+          atomicOr(&flag[(s - e0) >> 6], 1ull << ((s - e0) & 63));
+          start[s - e0] = i;
+        }
+        const uint64_t mask = __ballot(in);
+        const uint32_t k = static_cast<uint32_t>(__popcll(mask));
+        next += k;
+        if (k < 64u) break;
+      }
+      wave_sync();
+      int32_t vv[kSymItems];
+#pragma unroll
+      for (uint32_t r = 0; r < kSymItems; ++r) {
+        const uint32_t e = e0 + r * 64 + lane;
+        vv[r] = e < e1 ? *at<kNarrow>(a.cols, e) : -1;
+      }
+#pragma unroll
+      for (uint32_t r = 0; r < kSymItems; ++r) {
+        const unsigned long long word = flag[r];  // wavefront-uniform
+        const unsigned long long upto = word & (~0ull >> (63 - lane));
+        const uint32_t u = upto ? start[r * 64 + 63 - __builtin_clzll(upto)] : cur;
+        if (word) cur = start[r * 64 + 63 - __builtin_clzll(word)];
+        const uint32_t v = static_cast<uint32_t>(vv[r]);
+        if (e0 + r * 64 + lane < e1) {
+          bad = bad || v >= a.n;
+          if (v != u) {
+            const unsigned long long h = sym_hash(u, v, a.sym_key);
+            acc += v > u ? h : 0ull - h;
+          }
+        }
+      }
+      wave_sync();
+    }
+  }
+  // one atomic per workgroup on its XCD's line
+  __shared__ unsigned long long sums[kWaves];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) acc += bcast64(acc, static_cast<int>(lane ^ d));
+  if (lane == 0) sums[wid] = acc;
+  if (__any(bad) && lane == 0) a.ctl->sym_no = 1u;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long s = 0;
+    for (int w = 0; w < kWaves; ++w) s += sums[w];
+    if (s) atomicAdd(&a.ctl->xstat[blockIdx.x % kXcds][11], s);
+  }
+}
+
+// One pulled level, after k_expand_balanced has accounted for it: every
+// unreached node with a reached neighbour gets level L + 1 and joins worklist
+// L + 1.  Reached means the frozen snapshot seen[L & 1], so nodes found here
+// do not count; the next snapshot, `visited` and every XCD's filter are
+// written as whole words.  What bounds it: the dependent reads of a node's
+// offsets, arcs and their snapshot words (random 4-byte reads that hit L2).
+template <bool kNarrow>
+__global__ __launch_bounds__(kPullBlock) void k_bfs_pull(KArgs a, uint32_t launch) {
+  constexpr uint32_t T = TileCfg<false>::kEdges;
+  constexpr int kWv = kPullBlock / 64;
+  __shared__ uint32_t wsum[2][kWv];
+  __shared__ unsigned long long base_sh;
+  const uint32_t L = level_of(a, launch);
+  const unsigned long long c = ld_agent(&a.ctl->ctr[L % 3]);
+  const uint32_t Ef = static_cast<uint32_t>(c);
+  if (Ef <= a.min_arcs || !level_fits<false, false>(a, c) || !pulls(a, Ef)) return;
+  Frontier nxt = a.fr[(L + 1) & 1];
+  nxt.level = L + 1;
+  const int nctr = (L + 1) % 3;
+  const uint32_t* seen = a.seen[L & 1];
+  uint32_t* seen_nxt = a.seen[(L + 1) & 1];
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  // the balanced kernel's tile counters of level L + 1 (see expand_level)
+  if (blockIdx.x == 0 && tid < static_cast<uint32_t>(kXcds)) a.ctl->xstat[tid][8 + (L + 1) % 3] = 0ull;
+  uint32_t upd = 0;
+  bool bad = false;
+  for (uint32_t c0 = blockIdx.x * kPullChunk; c0 < a.n; c0 += gridDim.x * kPullChunk) {
+    uint32_t s[kPullPer], e[kPullPer], word[kPullPer];
+#pragma unroll
+    for (uint32_t i = 0; i < kPullPer; ++i) {
+      const uint32_t v = c0 + i * kPullBlock + tid;
+      word[i] = v < a.n ? *at<kNarrow>(seen, v >> 5) : ~0u;
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kPullPer; ++i) {
+      const uint32_t v = c0 + i * kPullBlock + tid;
+      s[i] = 0u;
+      e[i] = 0u;
+      if (!((word[i] >> (v & 31)) & 1u)) {
+        s[i] = static_cast<uint32_t>(*at<kNarrow>(a.offsets, v));
+        e[i] = static_cast<uint32_t>(*at<kNarrow>(a.offsets, v + 1));
+        if (s[i] > e[i] || e[i] > a.m) {
+          bad = true;
+          e[i] = s[i] = 0u;
+        }
+      }
+    }
+    uint32_t found = 0, cnt = 0, deg = 0;  // bit i: node i is new
+#pragma unroll
+    for (uint32_t i = 0; i < kPullPer; ++i) {
+      uint32_t p = s[i];
+      const uint32_t stop = min(e[i], s[i] + kPullAlone);
+      bool hit = false;
+      while (p < stop && !hit) {
+        uint32_t col[4];
+        bool ok[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          ok[b] = p + b < stop;
+          col[b] = ok[b] ? static_cast<uint32_t>(*at<kNarrow>(a.cols, p + b)) : 0u;
+          if (col[b] >= a.n) {
+            bad = true;
+            ok[b] = false;
+            col[b] = 0u;
+          }
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const uint32_t w = *at<kNarrow>(seen, col[b] >> 5);
+          hit = hit || (ok[b] && ((w >> (col[b] & 31)) & 1u));
+        }
+        p += 4;
+      }
+      // long lists: the wavefront reads them together
+      for (uint64_t more = __ballot(!hit && p < e[i]); more; more &= more - 1ull) {
+        const int who = __builtin_ctzll(more);
+        const uint32_t q1 = __shfl(e[i], who, 64);
+        bool any = false;
+        for (uint32_t q = __shfl(p, who, 64) + lane; !any && q - lane < q1; q += 64) {
+          bool here = false;
+          if (q < q1) {
+            const uint32_t col = static_cast<uint32_t>(*at<kNarrow>(a.cols, q));
+            if (col < a.n) here = (*at<kNarrow>(seen, col >> 5) >> (col & 31)) & 1u;
+            else bad = true;
+          }
+          any = __any(here);
+        }
+        if (static_cast<int>(lane) == who) hit = any;
+      }
+      const uint32_t v = c0 + i * kPullBlock + tid;
+      if (hit) {
+        *at<kNarrow>(a.levels, v) = static_cast<int32_t>(L + 1);
+        found |= 1u << i;
+        ++cnt;
+        deg += e[i] - s[i];
+      }
+      const uint64_t hits = __ballot(hit);
+      const uint32_t now = word[i] | static_cast<uint32_t>(hits >> (lane & 32));
+      if ((lane & 31) == 0u && v < a.n) {
+        const uint32_t w = v >> 5;
+        *at<kNarrow>(a.visited, w) = now;
+        *at<kNarrow>(seen_nxt, w) = now;
+#pragma unroll
+        for (int x = 0; x < kXcds; ++x) a.xfilter[static_cast<size_t>(x) * a.words + w] = now;
+      }
+    }
+    upd += cnt;
+    // the chunk's new nodes: one reservation
+    const uint32_t ic = wave_incl_scan(cnt), ie = wave_incl_scan(deg);
+    if (lane == 63) {
+      wsum[0][wid] = ic;
+      wsum[1][wid] = ie;
+    }
+    __syncthreads();
+    uint32_t pc = ic - cnt, pe = ie - deg, tc = 0, te = 0;
+#pragma unroll
+    for (int k = 0; k < kWv; ++k) {
+      if (static_cast<uint32_t>(k) < wid) {
+        pc += wsum[0][k];
+        pe += wsum[1][k];
+      }
+      tc += wsum[0][k];
+      te += wsum[1][k];
+    }
+    if (tid == 0) base_sh = tc ? atomicAdd(&a.ctl->ctr[nctr], (static_cast<unsigned long long>(tc) << 32) | te) : 0ull;
+    __syncthreads();
+    uint32_t nb = static_cast<uint32_t>(base_sh >> 32) + pc, eb = static_cast<uint32_t>(base_sh) + pe;
+#pragma unroll
+    for (uint32_t i = 0; i < kPullPer; ++i) {
+      if (found & (1u << i)) {
+        write_entry<0, T, kNarrow>(a, nxt, nb, eb, 0, 0, static_cast<int32_t>(s[i]), static_cast<int32_t>(e[i] - s[i]));
+        ++nb;
+        eb += e[i] - s[i];
+      }
+    }
+  }
+  if (__any(bad) && lane == 0) atomicOr(&a.ctl->error, kErrBadArc);
+  if (a.count_stats) {
+    const uint32_t su = wave_sum(upd);
+    if (lane == 0 && su) atomicAdd(&a.ctl->xstat[blockIdx.x % kXcds][0], static_cast<unsigned long long>(su));
+    // none of the worklist's arcs were loaded
+    if (blockIdx.x == 0 && tid == 0) atomicAdd(&a.ctl->xstat[0][7], static_cast<unsigned long long>(Ef));
+  }
+}
+
+}  // namespace lbg

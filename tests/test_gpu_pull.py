@@ -1,0 +1,126 @@
+"""BFS pull levels (graphs of at least 2^24 arcs, levels of at least m / 16)
+against the oracle, bit for bit: symmetric graphs, which are pulled; directed
+ones, which are not; and symmetric ones with a single arc missing, where a
+pull would reach a node that no arc leads to."""
+import numpy as np
+import pytest
+
+import graphgen
+import oracle
+import pins
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+from paper_1711_00231_amd import lbg  # noqa: E402
+
+O = oracle.get()
+
+
+@pytest.fixture(autouse=True)
+def _reset():
+    yield
+    lbg.set_addressing(0)
+    lbg.set_bfs_scan_min(-1)
+
+
+@pytest.fixture(scope="module")
+def rmat20():
+    return graphgen.rmat(20)
+
+
+def _solve(g, srcs, pulled):
+    assert g.m >= 1 << 24
+    dg = lbg.DeviceGraph.from_numpy(g.offsets, g.cols)
+    ws = lbg.Workspace()
+    skipped = 0
+    for s in srcs:
+        s = int(s)
+        exp = O.bfs(g.offsets, g.cols, s)
+        for wide in (0, 1):
+            lbg.set_addressing(wide)
+            got, st = lbg.bfs(dg, s, workspace=ws, stats=True)
+            assert np.array_equal(got.cpu().numpy(), exp), (g.name, s, wide)
+            reached = exp != pins.BFS_INF
+            assert st["updates"] == int(reached.sum()) - 1
+            assert st["edges_scanned"] == g.reached_arcs(reached)
+            skipped += st["edges_skipped"]
+    assert (skipped > 0) == pulled, (g.name, skipped)
+
+
+def _without(g, drop):
+    """g without the arcs numbered `drop`."""
+    keep = np.ones(g.m, dtype=bool)
+    keep[drop] = False
+    off = np.concatenate([[0], np.cumsum(keep)])[g.offsets.astype(np.int64)].astype(np.int32)
+    return graphgen.Graph(g.name + "-less", off, g.cols[keep], g.weights[keep])
+
+
+def _arc(g, u, v):
+    row = g.cols[g.offsets[u]: g.offsets[u + 1]]
+    return int(g.offsets[u]) + int(np.nonzero(row == v)[0][0])
+
+
+def test_symmetric_rmat_is_pulled(rmat20):
+    _solve(rmat20, graphgen.sources(rmat20, 4, graphgen.FAMILY_RMAT), True)
+
+
+def test_directed_graphs_are_not():
+    g = graphgen.uniform(n=2_200_001, k=8, salt=5)
+    _solve(g, [0, 77], False)
+    # a power-law digraph: no low-degree way back to sample
+    rng = np.random.default_rng(2)
+    n, m = 60_000, 17_000_000
+    src = np.sort(rng.integers(0, n, m))
+    dst = (rng.random(m) ** 4 * n).astype(np.int64)
+    h = graphgen.from_edges(n, src, dst, None, "powerlaw")
+    _solve(h, [5, 59_999], False)
+
+
+def test_one_missing_arc(rmat20):
+    """Leaves whose only way in is dropped, first, last and between, and one
+    arc between two hubs."""
+    g = rmat20
+    deg = g.degrees
+    leaves = np.nonzero(deg == 1)[0]
+    hubs = np.argsort(deg)[-40:]
+    src = int(graphgen.sources(g, 1, graphgen.FAMILY_RMAT)[0])
+    for x in (leaves[0], leaves[leaves.size // 2], leaves[-1]):
+        _solve(_without(g, [_arc(g, int(g.cols[g.offsets[x]]), int(x))]), [src], False)
+    a = next(int(h) for h in hubs[::-1] if np.isin(g.cols[g.offsets[hubs[-1]]: g.offsets[hubs[-1] + 1]], h).any())
+    _solve(_without(g, [_arc(g, int(hubs[-1]), a)]), [src], False)
+    # both directions dropped: symmetric again
+    x = int(leaves[3])
+    h = int(g.cols[g.offsets[x]])
+    _solve(_without(g, [_arc(g, h, x), _arc(g, x, h)]), [src], True)
+
+
+@pytest.mark.parametrize("extra", [1, 31, 4097])
+def test_node_counts_loops_and_duplicates(extra):
+    """Node counts around the bitmap word and the chunk; self-loops and
+    duplicate arcs in both directions keep a graph symmetric, one duplicate
+    in one direction does not (and changes no level)."""
+    rng = np.random.default_rng(extra)
+    n, half = (1 << 18) + extra, 8_600_000
+    u = (rng.random(half) ** 3 * n).astype(np.int64)  # skewed, so the levels are large
+    v = rng.integers(0, n, half)
+    loops = rng.integers(0, n, 1000)
+    s = np.concatenate([u, v, loops])
+    d = np.concatenate([v, u, loops])
+    g = graphgen.from_edges(n, s, d, None, "multi")
+    _solve(g, [int(u[0])], True)
+    h = graphgen.from_edges(n, np.append(s, u[5]), np.append(d, v[5]), None, "multi+1")
+    assert u[5] != v[5]
+    _solve(h, [int(u[0])], False)
+
+
+def test_thresholds(rmat20):
+    """With every level scanned, a caller's threshold or none, the levels are
+    the same; pull levels need the scans."""
+    for arcs in (0, 5000, 1 << 40):
+        lbg.set_bfs_scan_min(arcs)
+        dg = lbg.DeviceGraph.from_numpy(rmat20.offsets, rmat20.cols)
+        s = int(graphgen.sources(rmat20, 1, graphgen.FAMILY_RMAT)[0])
+        assert np.array_equal(lbg.bfs(dg, s).cpu().numpy(), O.bfs(rmat20.offsets, rmat20.cols, s)), arcs
