@@ -775,8 +775,10 @@ int solve(const Problem& P) {
     if (ef == 0u && (!a.far || (host->split_at == L && host->far_seen != L))) break;
     if (L > level_cap)
       return fail(LBG_EINTERNAL, "more than n + 1 levels; the CSR is probably malformed");
-    // no progress (the team came together too small): one-level launches alone
-    alone = small_ok && !alone && L == L_prev && !first;
+    // no progress (the team came together too small): one-level launches
+    // alone, which always advance
+    if (alone && L == L_prev) return fail(LBG_EINTERNAL, "level %u was not expanded", L);
+    alone = small_ok && L == L_prev && !first;
     if (alone) batch = 8;
     first = false;
     L_prev = L;

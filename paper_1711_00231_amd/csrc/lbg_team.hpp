@@ -51,6 +51,13 @@ constexpr unsigned long long kTeamPatience = 1000000000ull;  // 10 s
 constexpr uint32_t kTeamArcs = 0xfffffu;  // largest arc count of a flag (more than any level run here)
 constexpr uint32_t kTeamClosed = 0x80000000u;
 
+// The words that launch seq + 2 will use; by one thread of every launch,
+// whether it runs a level or not.
+__device__ __forceinline__ void team_clear(const KArgs& a, uint32_t seq) {
+  a.team->join[(seq + 2) & 3] = 0u;
+  a.team->size[(seq + 2) & 3] = 0u;
+}
+
 // Joins launch seq's team (one thread).  Returns the workgroup's number and
 // sets *size, or returns kTeamMax when it is not a member.
 __device__ __forceinline__ uint32_t team_join(const KArgs& a, uint32_t seq, uint32_t* size) {
@@ -61,8 +68,7 @@ __device__ __forceinline__ uint32_t team_join(const KArgs& a, uint32_t seq, uint
   if (me & kTeamClosed) return kTeamMax;
   const unsigned long long t0 = wall_clock64();
   if (me == 0u) {
-    t->join[(seq + 2) & 3] = 0u;
-    t->size[(seq + 2) & 3] = 0u;
+    team_clear(a, seq);
     while (ld_agent(join) < gridDim.x && wall_clock64() - t0 < kTeamWait) __builtin_amdgcn_s_sleep(1);
     const uint32_t p = __hip_atomic_fetch_or(join, kTeamClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     st_agent(&t->size[seq & 3], p);
@@ -199,7 +205,10 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
   uint32_t nf = static_cast<uint32_t>(c0 >> 32), E = static_cast<uint32_t>(c0);
   const bool far = kSssp && a.far;
   if ((E == 0u && !far) || E > min(limit, kTeamE) || nf > a.node_cap) {  // grid-uniform
-    if (blockIdx.x == 0 && tid == 0) level_next(a, launch, L0, false);
+    if (blockIdx.x == 0 && tid == 0) {
+      team_clear(a, seq);
+      level_next(a, launch, L0, false);
+    }
     return;
   }
   if (tid == 0) {

@@ -168,3 +168,31 @@ def test_near_far(layout):
             d, st = lbg.sssp(dg, s, workspace=ws, packed=layout == "packed", ordered=layout == "ordered", stats=True)
             assert np.array_equal(d.cpu().numpy().view(np.uint32), exp), (g.name, s, wide)
             assert st["edges_scanned"] >= g.reached_arcs(exp != 0xFFFFFFFF)
+
+
+@pytest.mark.parametrize("path_len", [1, 2, 40])
+def test_many_team_launches(path_len):
+    """A chain of ten dense blocks joined by paths: big levels run as one-level
+    launches, the paths in the team, so a solve makes many team launches, some
+    of which find nothing to do; each has to find its control words cleared by
+    the launches before it, whether those ran a level or not."""
+    parts_s, parts_d, base, n_mid = [], [], 0, 60_000
+    for b in range(10):
+        ids = base + np.arange(path_len)
+        if b:
+            parts_s.append([base - 1]); parts_d.append([base])
+        parts_s.append(ids[:-1]); parts_d.append(ids[1:])
+        base += path_len
+        blk = graphgen.uniform(n=n_mid, k=24, salt=70 + b)
+        parts_s.append([base - 1]); parts_d.append([base])
+        parts_s.append(base + np.repeat(np.arange(n_mid), blk.degrees)); parts_d.append(base + blk.cols.astype(np.int64))
+        base += n_mid
+    s, d = np.concatenate(parts_s), np.concatenate(parts_d)
+    w = np.random.default_rng(path_len).integers(1, 60, s.size)
+    for wts in (w, np.ones_like(w)):
+        g = graphgen.from_edges(base, s, d, wts, "chain")
+        dg = lbg.DeviceGraph.from_numpy(g.offsets, g.cols, g.weights)
+        assert np.array_equal(lbg.bfs(dg, 0).cpu().numpy(), O.bfs(g.offsets, g.cols, 0))
+        exp = O.dijkstra(g.offsets, g.cols, g.weights, 0)
+        for kw in ({}, {"ordered": True}):
+            assert np.array_equal(lbg.sssp(dg, 0, **kw).cpu().numpy().view(np.uint32), exp), kw
