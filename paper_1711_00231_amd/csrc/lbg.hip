@@ -16,6 +16,7 @@
 #include "lbg_kernels.hpp"
 #include "lbg_team.hpp"
 #include "lbg_pull.hpp"
+#include "lbg_solo.hpp"
 #include "lbg_sliced.hpp"
 #include "lbg_split.hpp"
 #include "lbg_order.hpp"
@@ -166,6 +167,7 @@ struct Grids {
   int sliced[2][2];                                      // [is_sssp][narrow], a multiple of 8 (>= 8)
   int bal_p[2];                                          // SSSP with packed arcs [narrow]
   int sym[2], pull[2];                                   // BFS pull levels [narrow]
+  int solo[5][2];                                        // batched queries by one workgroup [class][narrow]
   int far[2][2];                                         // near-far SSSP [packed][narrow]
   int bal_s[2][2];                                       // split graph [is_sssp][narrow]
 };
@@ -204,6 +206,14 @@ const Grids& grids() {
     g[dev].sym[1] = resident_grid(lbg::k_bfs_sym<true>);
     g[dev].pull[0] = resident_grid(lbg::k_bfs_pull<false>, lbg::kPullBlock);
     g[dev].pull[1] = resident_grid(lbg::k_bfs_pull<true>, lbg::kPullBlock);
+    g[dev].solo[1][0] = resident_grid(lbg::k_solo<1, false>, lbg::kSoloBlock);
+    g[dev].solo[1][1] = resident_grid(lbg::k_solo<1, true>, lbg::kSoloBlock);
+    g[dev].solo[2][0] = resident_grid(lbg::k_solo<2, false>, lbg::kSoloBlock);
+    g[dev].solo[2][1] = resident_grid(lbg::k_solo<2, true>, lbg::kSoloBlock);
+    g[dev].solo[3][0] = resident_grid(lbg::k_solo<3, false>, lbg::kSoloBlock);
+    g[dev].solo[3][1] = resident_grid(lbg::k_solo<3, true>, lbg::kSoloBlock);
+    g[dev].solo[4][0] = resident_grid(lbg::k_solo<4, false>, lbg::kSoloBlock);
+    g[dev].solo[4][1] = resident_grid(lbg::k_solo<4, true>, lbg::kSoloBlock);
     g[dev].far[0][0] = resident_grid(lbg::k_expand_balanced<true, false, false, false, false, true>);
     g[dev].far[0][1] = resident_grid(lbg::k_expand_balanced<true, true, false, false, false, true>);
     g[dev].far[1][0] = resident_grid(lbg::k_expand_balanced<true, false, false, true, false, true>);
@@ -876,6 +886,8 @@ BatchLayout batch_layout(int32_t num_queries, int64_t rows, int64_t total_arcs) 
   return L;
 }
 
+constexpr int64_t kSoloBatch = int64_t{1} << 28;  // see batch_solve
+
 // An instantiated graph of one replay of a graph-launched batch: kGraphLevels
 // expansion launches, the level advance, the conditional write-out and the
 // read-back of the control block.  Cached per thread and reused while the
@@ -957,6 +969,42 @@ int batch_graph(const KArgs& a, bool narrow, int expand_blocks, dim3 rgrid, Ctl*
   return LBG_OK;
 }
 
+// Launches the solo kernels of the classes that the batch may hold.
+int launch_solo(const KArgs& a, const bool (&has)[5], bool narrow, hipStream_t st) {
+  const Grids& GR = grids();
+  const dim3 b(lbg::kSoloBlock);
+  auto grid = [&](int c) {
+    return dim3(std::min<unsigned>(static_cast<unsigned>(GR.solo[c][narrow ? 1 : 0]), a.num_queries));
+  };
+  if (has[2]) {
+    if (narrow) hipLaunchKernelGGL((lbg::k_solo<2, true>), grid(2), b, 0, st, a);
+    else hipLaunchKernelGGL((lbg::k_solo<2, false>), grid(2), b, 0, st, a);
+  }
+  if (has[4]) {
+    if (narrow) hipLaunchKernelGGL((lbg::k_solo<4, true>), grid(4), b, 0, st, a);
+    else hipLaunchKernelGGL((lbg::k_solo<4, false>), grid(4), b, 0, st, a);
+  }
+  if (has[1]) {
+    if (narrow) hipLaunchKernelGGL((lbg::k_solo<1, true>), grid(1), b, 0, st, a);
+    else hipLaunchKernelGGL((lbg::k_solo<1, false>), grid(1), b, 0, st, a);
+  }
+  if (has[3]) {
+    if (narrow) hipLaunchKernelGGL((lbg::k_solo<3, true>), grid(3), b, 0, st, a);
+    else hipLaunchKernelGGL((lbg::k_solo<3, false>), grid(3), b, 0, st, a);
+  }
+  HIP_TRY(hipGetLastError());
+  return LBG_OK;
+}
+
+// The classes a query may be of, by its size (the device also looks at its
+// instance's arcs: solo_class).
+int solo_by_size(const lbg::QInfo& I) {
+  const uint32_t len = static_cast<uint32_t>(I.row_len);
+  const uint32_t words = I.kind ? len : (len + 31) / 32;
+  if (words > lbg::kSoloWords[2]) return 0;
+  return (I.kind ? 3 : 1) + (words > lbg::kSoloWords[1] ? 1 : 0);
+}
+
 int batch_solve(const int32_t* offsets, const int32_t* cols, const uint32_t* weights, int32_t n,
                 int64_t m, const lbg_query* queries, int32_t num_queries, uint32_t* out,
                 int64_t rows, int64_t total_arcs, void* workspace, size_t workspace_bytes,
@@ -995,12 +1043,26 @@ int batch_solve(const int32_t* offsets, const int32_t* cols, const uint32_t* wei
     I.pad[0] = I.pad[1] = 0;
   }
 
+  bool has[5] = {};
+  if (!use_graph && total_arcs >= kSoloBatch) {
+    // longest first (a query's place in the table means nothing)
+    std::sort(qt.begin(), qt.end(), [](const lbg::QInfo& x, const lbg::QInfo& y) { return x.row_len > y.row_len; });
+    for (const lbg::QInfo& I : qt) has[solo_by_size(I)] = true;
+  }
   char* ws = static_cast<char*>(workspace);
   KArgs a{};
   a.offsets = offsets;
   a.cols = cols;
   a.weights = weights;
   a.dist = out;
+  // One workgroup gets through 0.6 to 1.2 G arcs/s, the chip through about
+  // 200 when it has several for every CU: batches of 2^28 arcs and more take
+  // their small queries that way (2,048 queries over 2.6 G arcs: the 1,024
+  // BFS queries 20 -> 6.8 ms), except those with more than a 256th of the
+  // batch, which would hold it up.  Smaller batches are done sooner in the
+  // shared worklist (28 queries, 8 M arcs: 1.1 against 2.5 ms).
+  if (!use_graph && total_arcs >= kSoloBatch)
+    a.solo_arcs = static_cast<uint32_t>(total_arcs / 256);
   a.dstate = reinterpret_cast<unsigned long long*>(ws + Lay.dstate);
   a.visited = reinterpret_cast<uint32_t*>(ws + Lay.rbits);
   a.d16 = reinterpret_cast<uint16_t*>(ws + Lay.d16);
@@ -1041,6 +1103,10 @@ int batch_solve(const int32_t* offsets, const int32_t* cols, const uint32_t* wei
   if (narrow) hipLaunchKernelGGL(lbg::k_batch_seed<true>, dim3(seed_blocks), dim3(lbg::kBlock), 0, st, a);
   else hipLaunchKernelGGL(lbg::k_batch_seed<false>, dim3(seed_blocks), dim3(lbg::kBlock), 0, st, a);
   HIP_TRY(hipGetLastError());
+  if (a.solo_arcs) {
+    const int rc = launch_solo(a, has, narrow, st);
+    if (rc) return rc;
+  }
 
   uint32_t L = 0, batch = 8;
   size_t nev = 0;
@@ -1101,17 +1167,17 @@ int batch_solve(const int32_t* offsets, const int32_t* cols, const uint32_t* wei
         gp.empty_ms += ms;
       }
     }
-    gp.frontier_entries += static_cast<int64_t>(host->frontier_entries);
-    gp.edges_scanned += static_cast<int64_t>(host->edges_scanned);
+    gp.frontier_entries += static_cast<int64_t>(host->frontier_entries) + xsum(host, 13);
+    gp.edges_scanned += static_cast<int64_t>(host->edges_scanned) + xsum(host, 14);
     gp.updates += xsum(host, 0);
     gp.atomics += xsum(host, 1);
     gp.edges_skipped += xsum(host, 7);
   }
   if (stats) {
-    stats->levels = static_cast<int32_t>(host->levels);
+    stats->levels = static_cast<int32_t>(std::max(host->levels, host->solo_levels));
     stats->reserved = 0;
-    stats->frontier_entries = static_cast<int64_t>(host->frontier_entries);
-    stats->edges_scanned = static_cast<int64_t>(host->edges_scanned);
+    stats->frontier_entries = static_cast<int64_t>(host->frontier_entries) + xsum(host, 13);
+    stats->edges_scanned = static_cast<int64_t>(host->edges_scanned) + xsum(host, 14);
     stats->updates = xsum(host, 0);
     stats->atomics = xsum(host, 1);
     stats->edges_skipped = xsum(host, 7);

@@ -64,13 +64,15 @@ struct Ctl {
   unsigned int sym_no;        // BFS: the graph is not symmetric
   unsigned long long worked;  // balanced: bit k % 64 set when launch k found work
   unsigned int sym_run;       // BFS: 1 + the launch that summed the arcs (k_bfs_sym), 0: none did
-  unsigned int pad0;
+  unsigned int solo_levels;   // batches: most levels of a query solved by one workgroup
   unsigned long long pad1;
   // [x][0] updates, [x][1] global atomics issued; [x][2], [x][3] the same for
   // levels run by the small-frontier kernel; [x][4 + L % 3] the packed tail
   // (nodes << 32 | edges) of slice x's worklist of level L (destination-
   // sliced strategy); [x][8 + L % 3] the balanced kernel's tile counter of
-  // XCD x for level L (single solves); [x][11] its part of k_bfs_sym's sum
+  // XCD x for level L (single solves); [x][11] its part of k_bfs_sym's sum;
+  // [class][12] next query of k_solo; [x][13], [x][14] entries and arcs of
+  // queries solved by it
   unsigned long long xstat[kXcds][16];
 };
 static_assert(sizeof(Ctl) == 128 + kXcds * 128, "Ctl layout");
@@ -164,6 +166,7 @@ struct KArgs {
   unsigned long long sym_key;  // of k_bfs_sym's hash
   const QInfo* qtab;     // batched solves
   uint32_t num_queries;
+  uint32_t solo_arcs;    // a query on an instance of at most this many arcs may be solved by one workgroup (0: none)
   uint32_t rows;         // batched solves: total elements of node state
   uint32_t* qlast;       // engine: per query, the last level that holds one of its entries
   // Degree-binned strategy: a node with more than `mdt` out-arcs is queued as

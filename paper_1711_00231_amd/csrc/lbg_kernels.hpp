@@ -1769,6 +1769,20 @@ __global__ __launch_bounds__(kBlock) void k_expand_edge(KArgs a, uint32_t L) {
 // row range are cleared with an atomic AND.
 constexpr uint32_t kRowChunk = 4096;
 
+// Queries that one workgroup solves alone (lbg_solo.hpp), by the LDS words
+// their state takes: classes 1 and 2, BFS with a bit per node; 3 and 4, SSSP
+// with a word per node.  Class 0: the shared worklist.
+constexpr uint32_t kSoloWords[5] = {0u, 8192u, 32768u, 8192u, 32768u};
+__device__ __forceinline__ int solo_class(const KArgs& a, const QInfo& qi) {
+  const uint32_t len = static_cast<uint32_t>(qi.row_len);
+  const uint32_t words = qi.kind ? len : (len + 31) / 32;
+  if (a.solo_arcs == 0u || words > kSoloWords[2]) return 0;
+  const int32_t lo = qi.row_start - qi.delta;
+  const int32_t s = a.offsets[lo], e = a.offsets[lo + qi.row_len];
+  if (s < 0 || e < s || static_cast<uint32_t>(e) > a.m || static_cast<uint32_t>(e - s) > a.solo_arcs) return 0;
+  return (qi.kind ? 3 : 1) + (words > kSoloWords[1] ? 1 : 0);
+}
+
 __device__ __forceinline__ void fill_chunk(const KArgs& a, const QInfo& qi, uint32_t c0) {
   const uint32_t r0 = static_cast<uint32_t>(qi.row_start) + c0;
   const uint32_t r1 = static_cast<uint32_t>(qi.row_start) + min(static_cast<uint32_t>(qi.row_len), c0 + kRowChunk);
@@ -1812,6 +1826,7 @@ __device__ __forceinline__ void seed_row(const KArgs& a, const QInfo& qi) {
 __global__ __launch_bounds__(kBlock) void k_batch_fill(KArgs a) {
   for (uint32_t q = blockIdx.y; q < a.num_queries; q += gridDim.y) {
     const QInfo qi = a.qtab[q];
+    if (solo_class(a, qi)) continue;
     for (uint32_t c0 = blockIdx.x * kRowChunk; c0 < static_cast<uint32_t>(qi.row_len); c0 += gridDim.x * kRowChunk)
       fill_chunk(a, qi, c0);
   }
@@ -1821,6 +1836,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_fill(KArgs a) {
       a.ctl->error = 0u;
       a.ctl->levels = 0u;
       a.ctl->level_base = 0u;
+      a.ctl->solo_levels = 0u;
       a.ctl->frontier_entries = 0ull;
       a.ctl->edges_scanned = 0ull;
     }
@@ -1832,12 +1848,13 @@ __global__ __launch_bounds__(kBlock) void k_batch_fill(KArgs a) {
 template <bool kNarrow>
 __global__ __launch_bounds__(kBlock) void k_batch_seed(KArgs a) {
   const uint32_t q = blockIdx.x * kBlock + threadIdx.x;
-  const bool act = q < a.num_queries;
+  bool act = q < a.num_queries;
   int32_t v = 0;
   if (act) {
     const QInfo qi = a.qtab[q];
     v = qi.src;
-    seed_row(a, qi);
+    act = solo_class(a, qi) == 0;
+    if (act) seed_row(a, qi);
   }
   Frontier f0 = a.fr[0];
   f0.level = 0;
@@ -1896,6 +1913,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_finish(KArgs a, uint32_t L) {
   if (static_cast<uint32_t>(c) != 0u) return;
   for (uint32_t q = blockIdx.y; q < a.num_queries; q += gridDim.y) {
     const QInfo qi = a.qtab[q];
+    if (solo_class(a, qi)) continue;
     for (uint32_t c0 = blockIdx.x * kRowChunk; c0 < static_cast<uint32_t>(qi.row_len); c0 += gridDim.x * kRowChunk)
       finish_chunk(a, qi, c0);
   }
