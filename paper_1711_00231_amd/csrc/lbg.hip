@@ -272,8 +272,14 @@ constexpr int64_t kPullGraph = int64_t{1} << 24;
 // Key of k_bfs_sym's hash: drawn once per process.
 unsigned long long sym_key() {
   static const unsigned long long key = [] {
-    std::random_device rd;
-    return (static_cast<unsigned long long>(rd()) << 32) | rd();
+    unsigned long long k = static_cast<unsigned long long>(std::chrono::steady_clock::now().time_since_epoch().count());
+    try {
+      std::random_device rd;
+      k ^= (static_cast<unsigned long long>(rd()) << 32) | rd();
+    } catch (...) {  // no entropy source: the clock alone
+      k *= 0x9e3779b97f4a7c15ull;
+    }
+    return k;
   }();
   return key;
 }
@@ -1040,7 +1046,7 @@ int batch_solve(const int32_t* offsets, const int32_t* cols, const uint32_t* wei
     I.kind = Q.kind;
     I.src = Q.src;
     I.level0 = 0;
-    I.pad[0] = I.pad[1] = 0;
+    I.slot = I.pad = 0;
   }
 
   bool has[5] = {};
@@ -1189,7 +1195,7 @@ int batch_solve(const int32_t* offsets, const int32_t* cols, const uint32_t* wei
 // ---------------------------------------------------------------- engine --
 struct EngineLayout {
   BatchLayout b;
-  size_t qlast, slots, qstage, total;
+  size_t qlast, qstage, total;
 };
 
 EngineLayout engine_layout(int32_t max_queries, int64_t max_rows, int64_t max_level_arcs) {
@@ -1198,8 +1204,6 @@ EngineLayout engine_layout(int32_t max_queries, int64_t max_rows, int64_t max_le
   size_t off = E.b.total;
   E.qlast = off;
   off += align_up(sizeof(uint32_t) * static_cast<size_t>(max_queries));
-  E.slots = off;
-  off += align_up(sizeof(int32_t) * static_cast<size_t>(max_queries));
   E.qstage = off;  // descriptors of the queries being admitted
   off += align_up(sizeof(lbg::QInfo) * static_cast<size_t>(max_queries));
   E.total = off;
@@ -1221,7 +1225,6 @@ struct lbg_engine {
   std::vector<uint8_t> state;  // 0 free, 1 pending seed, 2 running, 3 finished (row written)
   std::vector<int32_t> pending, done;
   uint32_t* host_qlast = nullptr;  // pinned
-  int32_t* host_slots = nullptr;   // pinned
   lbg::QInfo* host_qstage = nullptr;  // pinned
   Ctl* host_ctl = nullptr;         // pinned
   int64_t steps = 0;
@@ -1229,16 +1232,6 @@ struct lbg_engine {
 
 namespace {
 
-int engine_sync_state(lbg_engine* e) {
-  HIP_TRY(hipMemcpyAsync(e->host_ctl, e->a.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, e->st));
-  HIP_TRY(hipMemcpyAsync(e->host_qlast, e->ws + e->lay.qlast, sizeof(uint32_t) * e->max_q,
-                         hipMemcpyDeviceToHost, e->st));
-  HIP_TRY(hipStreamSynchronize(e->st));
-  if (e->host_ctl->error)
-    return fail(LBG_EOVERFLOW, "device guard tripped (flags 0x%x: %s)", e->host_ctl->error,
-                guard_names(e->host_ctl->error));
-  return LBG_OK;
-}
 
 }  // namespace
 
@@ -1280,20 +1273,17 @@ int lbg_engine_create(const int32_t* offsets, const int32_t* cols, const uint32_
   void* p1 = nullptr;
   void* p2 = nullptr;
   void* p3 = nullptr;
-  void* p4 = nullptr;
   if (hipHostMalloc(&p1, sizeof(uint32_t) * max_queries, hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(&p2, sizeof(int32_t) * max_queries, hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(&p3, sizeof(Ctl), hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(&p4, sizeof(lbg::QInfo) * max_queries, hipHostMallocDefault) != hipSuccess) {
-    for (void* p : {p1, p2, p3, p4})
+      hipHostMalloc(&p2, sizeof(Ctl), hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc(&p3, sizeof(lbg::QInfo) * max_queries, hipHostMallocDefault) != hipSuccess) {
+    for (void* p : {p1, p2, p3})
       if (p) (void)hipHostFree(p);
     delete e;
     return fail(LBG_EHIP, "hipHostMalloc failed");
   }
   e->host_qlast = static_cast<uint32_t*>(p1);
-  e->host_slots = static_cast<int32_t*>(p2);
-  e->host_ctl = static_cast<Ctl*>(p3);
-  e->host_qstage = static_cast<lbg::QInfo*>(p4);
+  e->host_ctl = static_cast<Ctl*>(p2);
+  e->host_qstage = static_cast<lbg::QInfo*>(p3);
   const BatchLayout& Lay = e->lay.b;
   KArgs& a = e->a;
   a.offsets = offsets;
@@ -1320,9 +1310,9 @@ int lbg_engine_create(const int32_t* offsets, const int32_t* cols, const uint32_
   a.num_queries = static_cast<uint32_t>(max_queries);
   a.rows = static_cast<uint32_t>(max_rows);
   a.count_stats = 1u;
-  // clear the control block (counters of levels 0..2, stats) and qlast
+  // clear the control block (counters of levels 0..2, stats); no slot in use
   if (hipMemsetAsync(a.ctl, 0, sizeof(Ctl), e->st) != hipSuccess ||
-      hipMemsetAsync(a.qlast, 0, sizeof(uint32_t) * max_queries, e->st) != hipSuccess ||
+      hipMemsetAsync(a.qlast, 0xff, sizeof(uint32_t) * max_queries, e->st) != hipSuccess ||
       hipStreamSynchronize(e->st) != hipSuccess) {
     lbg_engine_destroy(e);
     return fail(LBG_EHIP, "engine initialisation failed");
@@ -1354,7 +1344,8 @@ int lbg_engine_submit(lbg_engine* e, const lbg_query* q, int32_t* slot) {
   I.kind = q->kind;
   I.src = q->src;
   I.level0 = 0;
-  I.pad[0] = I.pad[1] = 0;
+  I.slot = s;
+  I.pad = 0;
   e->state[static_cast<size_t>(s)] = 1;
   e->pending.push_back(s);
   *slot = s;
@@ -1367,27 +1358,24 @@ int lbg_engine_step(lbg_engine* e, int32_t levels, int32_t* finished) {
   const hipStream_t st = e->st;
   const Grids& GR = grids();
   if (!e->pending.empty()) {
-    // Admissions: descriptors and slots go up in one copy each (pinned
-    // staging; the previous step's copies finished before it returned).
+    // Admissions: the descriptors go up in one copy (pinned staging; the
+    // previous step's copy finished before it returned).
     const int cnt = static_cast<int>(e->pending.size());
+    int64_t max_len = 1;
     for (int k = 0; k < cnt; ++k) {
-      const int32_t s = e->pending[static_cast<size_t>(k)];
-      e->host_slots[k] = s;
-      e->qt[static_cast<size_t>(s)].level0 = e->L;  // its source joins worklist L
-      e->host_qstage[k] = e->qt[static_cast<size_t>(s)];
+      lbg::QInfo& I = e->qt[static_cast<size_t>(e->pending[static_cast<size_t>(k)])];
+      I.level0 = e->L;  // its source joins worklist L
+      e->host_qstage[k] = I;
+      max_len = std::max<int64_t>(max_len, I.row_len);
     }
-    int32_t* dslots = reinterpret_cast<int32_t*>(e->ws + e->lay.slots);
     lbg::QInfo* dstage = reinterpret_cast<lbg::QInfo*>(e->ws + e->lay.qstage);
     HIP_TRY(hipMemcpyAsync(dstage, e->host_qstage, sizeof(lbg::QInfo) * cnt, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(dslots, e->host_slots, sizeof(int32_t) * cnt, hipMemcpyHostToDevice, st));
-    int64_t max_len = 1;
-    for (int k = 0; k < cnt; ++k) max_len = std::max<int64_t>(max_len, e->host_qstage[k].row_len);
     hipLaunchKernelGGL(lbg::k_engine_fill, row_grid(cnt, max_len), dim3(lbg::kBlock), 0, st, a,
-                       static_cast<const int32_t*>(dslots), static_cast<const lbg::QInfo*>(dstage),
+                       static_cast<const lbg::QInfo*>(dstage),
                        reinterpret_cast<lbg::QInfo*>(e->ws + e->lay.b.qtab), cnt);
     const int sb = (cnt + lbg::kBlock - 1) / lbg::kBlock;
-    if (e->narrow) hipLaunchKernelGGL(lbg::k_engine_seed<true>, dim3(sb), dim3(lbg::kBlock), 0, st, a, static_cast<const int32_t*>(dslots), cnt, e->L);
-    else hipLaunchKernelGGL(lbg::k_engine_seed<false>, dim3(sb), dim3(lbg::kBlock), 0, st, a, static_cast<const int32_t*>(dslots), cnt, e->L);
+    if (e->narrow) hipLaunchKernelGGL(lbg::k_engine_seed<true>, dim3(sb), dim3(lbg::kBlock), 0, st, a, static_cast<const lbg::QInfo*>(dstage), cnt, e->L);
+    else hipLaunchKernelGGL(lbg::k_engine_seed<false>, dim3(sb), dim3(lbg::kBlock), 0, st, a, static_cast<const lbg::QInfo*>(dstage), cnt, e->L);
     HIP_TRY(hipGetLastError());
     for (int32_t s : e->pending) e->state[static_cast<size_t>(s)] = 2;
     e->pending.clear();
@@ -1399,27 +1387,27 @@ int lbg_engine_step(lbg_engine* e, int32_t levels, int32_t* finished) {
       hipLaunchKernelGGL((lbg::k_expand_balanced<true, false, true>), dim3(GR.multi[0]), dim3(lbg::kBlock), 0, st, a, e->L);
     HIP_TRY(hipGetLastError());
   }
-  int rc = engine_sync_state(e);
-  if (rc) return rc;
-  // a running query is finished once no worklist from level L on holds it
+  // A running query is finished once no worklist from level L on holds it:
+  // the device writes its row and frees its slot's mark, and the control
+  // block and the marks come back from the same kernel, so a step waits once.
+  int64_t max_len = 0;
+  for (int32_t s = 0; s < e->max_q; ++s)
+    if (e->state[static_cast<size_t>(s)] == 2) max_len = std::max<int64_t>(max_len, e->qt[static_cast<size_t>(s)].row_len);
+  hipLaunchKernelGGL(lbg::k_engine_finish, row_grid(e->max_q, max_len), dim3(lbg::kBlock), 0, st, a, e->L,
+                     e->host_qlast, e->host_ctl);
+  hipLaunchKernelGGL(lbg::k_engine_idle, dim3(1), dim3(lbg::kBlock), 0, st, a, e->L);
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(hipStreamSynchronize(st));
+  if (e->host_ctl->error)
+    return fail(LBG_EOVERFLOW, "device guard tripped (flags 0x%x: %s)", e->host_ctl->error,
+                guard_names(e->host_ctl->error));
   e->done.clear();
-  int cnt = 0;
   for (int32_t s = 0; s < e->max_q; ++s)
     if (e->state[static_cast<size_t>(s)] == 2 && e->host_qlast[s] < e->L) {
       e->done.push_back(s);
-      e->host_slots[cnt++] = s;
+      e->state[static_cast<size_t>(s)] = 3;
     }
-  if (cnt) {
-    int32_t* dslots = reinterpret_cast<int32_t*>(e->ws + e->lay.slots);
-    HIP_TRY(hipMemcpyAsync(dslots, e->host_slots, sizeof(int32_t) * cnt, hipMemcpyHostToDevice, st));
-    int64_t max_len = 1;
-    for (int32_t s : e->done) max_len = std::max<int64_t>(max_len, e->qt[static_cast<size_t>(s)].row_len);
-    hipLaunchKernelGGL(lbg::k_engine_finish, row_grid(cnt, max_len), dim3(lbg::kBlock), 0, st, a,
-                       static_cast<const int32_t*>(dslots), cnt);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipStreamSynchronize(st));
-    for (int32_t s : e->done) e->state[static_cast<size_t>(s)] = 3;
-  }
+  const int32_t cnt = static_cast<int32_t>(e->done.size());
   ++e->steps;
   if (finished) *finished = cnt;
   return LBG_OK;
@@ -1463,7 +1451,6 @@ void lbg_engine_destroy(lbg_engine* e) {
   if (!e) return;
   if (e->st) (void)hipStreamSynchronize(e->st);
   if (e->host_qlast) (void)hipHostFree(e->host_qlast);
-  if (e->host_slots) (void)hipHostFree(e->host_slots);
   if (e->host_ctl) (void)hipHostFree(e->host_ctl);
   if (e->host_qstage) (void)hipHostFree(e->host_qstage);
   delete e;

@@ -33,8 +33,10 @@ struct QInfo {
   int32_t row_len;    // hi - lo
   int32_t src;        // global source node
   uint32_t level0;    // level whose worklist received the source (engine admissions)
-  int32_t pad[2];
+  int32_t slot;       // engine: the query's slot
+  int32_t pad;
 };
+constexpr uint32_t kQIdle = 0xffffffffu;
 constexpr int kXcds = 8;                 // MI355X: 8 XCDs, workgroups dealt round-robin
 
 // Control block at the start of the workspace.  ctr[] are the worklist tail
@@ -168,7 +170,7 @@ struct KArgs {
   uint32_t num_queries;
   uint32_t solo_arcs;    // a query on an instance of at most this many arcs may be solved by one workgroup (0: none)
   uint32_t rows;         // batched solves: total elements of node state
-  uint32_t* qlast;       // engine: per query, the last level that holds one of its entries
+  uint32_t* qlast;       // engine: per slot, the last level that holds one of its query's entries (kQIdle: none)
   // Degree-binned strategy: a node with more than `mdt` out-arcs is queued as
   // ceil(deg / mdt) pieces (0 = no splitting); a piece longer than t_block
   // is expanded by a workgroup, longer than t_wave by a wavefront, else by
