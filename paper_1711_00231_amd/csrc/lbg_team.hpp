@@ -204,8 +204,14 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
   const unsigned long long c0 = ld_agent(&a.ctl->ctr[L0 % 3]);
   uint32_t nf = static_cast<uint32_t>(c0 >> 32), E = static_cast<uint32_t>(c0);
   const bool far = kSssp && a.far;
-  if ((E == 0u && !far) || E > min(limit, kTeamE) || nf > a.node_cap) {  // grid-uniform
-    if (blockIdx.x == 0 && tid == 0) {
+  if ((E == 0u && !far) || E > min(limit, kTeamE) || nf > a.node_cap) {
+    // Nothing for a team to do, if nobody has joined one: a workgroup that
+    // starts late (other streams hold the CUs) may find the counter as a team
+    // that has come and gone left it, and that team has set the next level.
+    // The counter is read before join (the branch needs it), and a team
+    // changes it only after its members joined.
+    if (blockIdx.x == 0 && tid == 0 &&
+        __hip_atomic_fetch_or(&a.team->join[seq & 3], kTeamClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) {
       team_clear(a, seq);
       level_next(a, launch, L0, false);
     }

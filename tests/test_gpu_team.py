@@ -196,3 +196,45 @@ def test_many_team_launches(path_len):
         exp = O.dijkstra(g.offsets, g.cols, g.weights, 0)
         for kw in ({}, {"ordered": True}):
             assert np.array_equal(lbg.sssp(dg, 0, **kw).cpu().numpy().view(np.uint32), exp), kw
+
+
+@pytest.mark.parametrize("solve", ["bfs", "sssp"])
+def test_teams_beside_big_levels(solve):
+    """Team launches of several streams while big levels of others hold the
+    CUs, XCD by XCD: a team's first workgroup may start after the team has
+    come together without it, run its levels and ended, and must then leave
+    the next level alone."""
+    import threading
+
+    big = graphgen.rmat(18)
+    small = graphgen.grid(256, shortcut_frac=0)
+    mid = graphgen.uniform(16)
+    srcs = graphgen.sources(big, 2, graphgen.FAMILY_RMAT)
+    jobs = [(big, int(srcs[0])), (small, 9), (big, int(srcs[1])), (mid, 4), (mid, 77), (small, 3000)]
+    if solve == "bfs":
+        exp = [O.bfs(x.offsets, x.cols, s) for x, s in jobs]
+    else:
+        exp = [O.dijkstra(x.offsets, x.cols, x.weights, s) for x, s in jobs]
+    dgs = {id(x): lbg.DeviceGraph.from_numpy(x.offsets, x.cols, x.weights) for x in (big, small, mid)}
+    bad = []
+
+    def work(k):
+        try:
+            x, s = jobs[k]
+            st = torch.cuda.Stream()
+            ws = lbg.Workspace()
+            for i in range(24):
+                out = getattr(lbg, solve)(dgs[id(x)], s, workspace=ws, stream=st)
+                st.synchronize()
+                if not np.array_equal(out.cpu().numpy().view(exp[k].dtype), exp[k]):
+                    bad.append((k, i))
+        except Exception as e:  # reported below
+            bad.append(repr(e))
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(len(jobs))]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join(100)
+    assert not any(t.is_alive() for t in ts)
+    assert not bad, bad
