@@ -398,10 +398,10 @@ int check_common(const Problem& P) {
 }
 
 // Whether an SSSP solve defers nodes beyond a threshold (near_far_init).  Not
-// above 16 arcs per node: the skewed graphs measured there lose as much to
-// the extra iterations as they gain (R-MAT scale 20, 30 arcs per node, host
-// emulation with the measured rates: 1.55 ms at best against 1.76 ms, before
-// the one-level kernel's own skipping of improved entries, which saves more).
+// above 16 arcs per node: skewed graphs lose more to the extra iterations than
+// they save (R-MAT, thresholds from a quarter of a mean list's weight to all
+// of it: scale 18, 0.48 -> 0.60 - 0.68 ms; scale 22 ordered, 2.50 -> 2.66 -
+// 3.38 ms).
 // Not below 2^20 arcs: there every level is latency and a level saved is worth
 // more than the arcs (uniform graph of 2^14 nodes: 20 iterations, 24 with the
 // best step).

@@ -626,6 +626,8 @@ __device__ __forceinline__ bool level_fits(const KArgs& a, unsigned long long c)
          Ef <= (kMulti ? static_cast<unsigned long long>(a.tile_cap) * T : static_cast<unsigned long long>(a.m));
 }
 
+constexpr uint32_t kTilesPerWave = 4;
+
 // One level of the balanced expansion by the whole grid (all threads of
 // every block must call it).  c = the level's packed tail, non-empty and
 // within capacity.
@@ -682,7 +684,23 @@ __device__ __forceinline__ void expand_level(const KArgs& a, uint32_t L, unsigne
   }
 
   const uint32_t ntiles = (Ef + T - 1) / T;
-  const uint32_t W = gridDim.x * kWaves;
+  // How many workgroups take part.  SSSP levels of few tiles per wavefront
+  // relax too early when all of them run at once: every arc then sees the
+  // distances from before the level, where half the wavefronts see those of
+  // the tiles before theirs too, skip more entries and improve fewer nodes
+  // twice.  From kTilesPerWave tiles for each wavefront on there is no
+  // difference left, and memory needs the wavefronts.  R-MAT, 300,007 nodes:
+  // 0.50 -> 0.46 ms; scale 18: 0.51 -> 0.48 ms, 25.0 -> 23.0 M arcs relaxed;
+  // scale 22 unchanged (2.50 ms; 2.66 with three quarters of the wavefronts
+  // throughout, 3.17 with half).  A quarter on the smallest levels gains
+  // nothing more on scale 18 and loses 4 % on scale 15.  Near-far solves
+  // relax few arcs twice, and lose 6 % (grid) and 1 % (uniform) with it.
+  uint32_t G = gridDim.x;
+  if (kSssp && !kMulti && !kFar) {
+    G = min(G, max(G / 2, ntiles / (kWaves * kTilesPerWave)));
+    if (blockIdx.x >= G) return;
+  }
+  const uint32_t W = G * kWaves;
   // Tile deal.  Tiles [0, S) go round-robin to the W wavefronts (tile g,
   // g + W, ...); single solves take the last eighth from per-XCD counters
   // (XCD x hands out S + x, S + x + 8, ...), so a wavefront that drew cheap
@@ -695,7 +713,7 @@ __device__ __forceinline__ void expand_level(const KArgs& a, uint32_t L, unsigne
   // W tiles take no atomic.  The counters of level L are
   // ctl->xstat[x][8 + L % 3], cleared by launch L - 1 (or by the
   // small-frontier kernel that ran level L - 1, or by k_init).
-  const bool dyn = !kMulti && gridDim.x >= static_cast<uint32_t>(kXcds);
+  const bool dyn = !kMulti && G >= static_cast<uint32_t>(kXcds);
   const uint32_t S = (dyn && ntiles > W) ? max(W, (ntiles - ntiles / 8) / W * W) : ntiles;
   const uint32_t xcd = blockIdx.x % kXcds;
   unsigned long long* const dctr = &a.ctl->xstat[xcd][8 + L % 3];
