@@ -265,8 +265,11 @@ thread_local PinnedCtl g_pinned;
 // enqueues that many, so a typical solve needs one read-back and few empty
 // launches.
 thread_local uint32_t g_big_hint[2] = {0u, 0u};
-// SSSP solves of sparse graphs of at most this many arcs are expected to stay
-// in the team.
+// Likewise, levels of the thread's previous BFS / SSSP solve by another
+// strategy: its first submission holds that many and one more (an empty level
+// of hierarchical processing with 256-arc windows is 640 launches: R-MAT 22
+// SSSP 51 - 56 ms, 84 with submissions of 8, 16, ... levels).
+thread_local uint32_t g_level_hint[2] = {0u, 0u};
 // BFS solves of graphs of at least this many arcs may pull levels.
 constexpr int64_t kPullGraph = int64_t{1} << 24;
 // Key of k_bfs_sym's hash: drawn once per process.
@@ -284,6 +287,8 @@ unsigned long long sym_key() {
   return key;
 }
 constexpr uint32_t kTeamDense = 512;  // arcs per team workgroup, see solve()
+// SSSP solves of sparse graphs of at most this many arcs are expected to stay
+// in the team.
 constexpr int64_t kSmallGraph = int64_t{2} << 20;
 
 thread_local std::vector<hipEvent_t> g_events;
@@ -689,6 +694,7 @@ int solve(const Problem& P) {
   uint32_t seq = 0;            // team launches among them
   const int kind = P.is_sssp ? 1 : 0;
   uint32_t batch = small_ok && g_big_hint[kind] ? std::min<uint32_t>(g_big_hint[kind], 16) : 8;
+  if (!small_ok && g_level_hint[kind]) batch = std::clamp<uint32_t>(g_level_hint[kind] + 1, 8, 64);
   // how many one-level launches can find work: a BFS expands every arc once,
   // so at most m / (team_limit + 1) levels outgrow the team; an SSSP solve of a
   // graph of few arcs has none, most likely (then it reads back first: an
@@ -756,7 +762,8 @@ int solve(const Problem& P) {
     if (!small_ok || alone) {
       a.min_arcs = 0u;
       if ((rc = one_level(batch)) != LBG_OK) return rc;
-      batch = std::min<uint32_t>(batch * 2, 64);
+      // the levels beyond a hint are few, most likely
+      batch = first && !small_ok && g_level_hint[kind] ? 8 : std::min<uint32_t>(batch * 2, 64);
     } else {
       a.min_arcs = team_limit;
       if (ef <= team_limit && (rc = team()) != LBG_OK) return rc;
@@ -799,6 +806,7 @@ int solve(const Problem& P) {
     first = false;
     L_prev = L;
   }
+  if (!small_ok) g_level_hint[kind] = host->levels;
   if (strat == LBG_HIER && !P.no_alloc) {
     g_hier_sched.assign(static_cast<size_t>(lbg::kHierTraceLevels) * lbg::kHierTraceSubs, 0u);
     HIP_TRY(hipMemcpyAsync(g_hier_sched.data(), a.hier_trace, sizeof(uint32_t) * g_hier_sched.size(),
