@@ -100,7 +100,8 @@ def make_workload(name):
 # (the SSSP layout the benchmark times).
 TRAFFIC_SOURCES = ("paper_1711_00231_amd/csrc/lbg_kernels.hpp", "paper_1711_00231_amd/csrc/lbg_device.hpp",
                    "paper_1711_00231_amd/csrc/lbg_sliced.hpp", "paper_1711_00231_amd/csrc/lbg_order.hpp",
-                   "paper_1711_00231_amd/csrc/lbg_team.hpp", "paper_1711_00231_amd/csrc/lbg.hip")
+                   "paper_1711_00231_amd/csrc/lbg_team.hpp", "paper_1711_00231_amd/csrc/lbg_pull.hpp",
+                   "paper_1711_00231_amd/csrc/lbg_solo.hpp", "paper_1711_00231_amd/csrc/lbg.hip")
 
 
 def recorded_traffic():
@@ -329,9 +330,13 @@ def run_plain(args, lbg, torch, dev):
             label = f"k_expand_{kname}<{'true' if kind == 'sssp' else 'false'}>"
             if kind == "sssp" and ordered:
                 label += " ordered"
+            # BFS: an arc of a pulled level (whose unreached nodes look for a
+            # reached neighbour instead) is charged the 4 bytes that the
+            # symmetry pass before it reads, not the expansion's 8
+            pulled = p["edges_skipped"] if kind == "bfs" else 0
             kern[kind] = {"kernel": label,
                           "launches": nl, "kernel_ms": p["kernel_ms"] + p["empty_ms"],
-                          "bytes": algorithmic_bytes(kind, p),
+                          "bytes": algorithmic_bytes(kind, p) - 4 * pulled,
                           "edges_scanned": p["edges_scanned"], "edges_skipped": p["edges_skipped"]}
         dom = max(kern, key=lambda k: kern[k]["kernel_ms"])
         traffic = recorded_traffic() if args.workload == "rmat22" else {}
@@ -344,6 +349,8 @@ def run_plain(args, lbg, torch, dev):
                    "kernel": kd["kernel"], "launches": kd["launches"],
                    "avg_launch_us": round(kd["kernel_ms"] * 1e3 / max(kd["launches"], 1), 3),
                    "bytes_per_launch": round(kd["bytes"] / max(kd["launches"], 1))}
+            if kind == "bfs" and kd["edges_scanned"]:
+                obj["pulled_fraction"] = round(kd["edges_skipped"] / kd["edges_scanned"], 4)
             if kind == "sssp" and kd["edges_scanned"]:
                 # arcs queued vs arcs actually loaded and relaxed by the
                 # one-level launches, and all relaxations (small-frontier

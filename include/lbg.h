@@ -62,9 +62,11 @@
  *   - All array arguments are DEVICE pointers (hipMalloc'd or torch CUDA
  *     tensors), except `stats` and the batched query table (host).  The
  *     caller owns every buffer; the library allocates no device memory.  It
- *     keeps, between calls: process-wide profiling counters and degree-bin
- *     parameters, per-device launch sizes, and per host thread one pinned
- *     control-block copy, its event pool and the last batch graph.
+ *     keeps, between calls: process-wide profiling counters, degree-bin
+ *     parameters and the hash key of the symmetry check, per-device launch
+ *     sizes, and per host thread one pinned control-block copy, its event
+ *     pool, the last batch graph and how many large levels the thread's last
+ *     BFS and SSSP had (which sizes the next solve's first submission).
  *   - `stream` is a hipStream_t passed as void* (NULL = default stream).  All
  *     work is ordered on it.  The call returns after the solve has finished
  *     on the stream (the level loop reads the frontier size back to decide

@@ -16,9 +16,9 @@
 // whole L2s and cost about 30 us per level (measured), which is as slow as
 // one launch per level.  Against one workgroup with the frontier in its LDS
 // (levels of at most 16 K arcs) and one-level launches for the rest: a solve
-// of a 16 K-node uniform graph went from 194 to 92 us (BFS) and from 311 to
-// 179 us (SSSP), BFS of the 2048 x 2048 grid with shortcuts from 1.71 to
-// 1.24 ms.
+// of a 16 K-node uniform graph went from 198 to 87 us (BFS) and from 318 to
+// 194 us (SSSP), BFS of the 2048 x 2048 grid with shortcuts from 1.73 to
+// 0.87 ms, without them from 53 to 13.7 ms (2,500 to 3,700 levels).
 //
 // Membership: a workgroup joins by an atomic on join[]; the first one closes
 // the team when every workgroup of the grid has joined or after kTeamWait,
