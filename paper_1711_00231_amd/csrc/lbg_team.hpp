@@ -103,7 +103,7 @@ struct TeamLds {
   uint32_t segn[kTeamMax + 1];  // entries before workgroup q's
   uint32_t sege[kTeamMax + 1];  // arcs before workgroup q's
   unsigned long long flag[kTeamSlots / 64];  // bit s: an entry starts at slot s
-  unsigned long long push;      // (entries << 32) | arcs pushed so far
+  unsigned long long push;      // (entries << 48) | arcs pushed so far
   uint32_t me, size, ok;
   uint32_t found;               // split: this workgroup found nodes in the far set
   uint32_t any_found;           //   or some other one did
@@ -245,7 +245,8 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
   unsigned long long tot_f = 0, tot_e = 0;  // this workgroup's share
   bool bad = false, alive = true, done = false;
   uint32_t cur = 0;            // the list of this level
-  uint32_t cnt = 0, arcs = 0;  // its size
+  uint32_t cnt = 0, arcs = 0;  // its size (arcs: at most 2^32 - 1)
+  uint32_t end = 0;            // its arcs mod 2^32, as pre[] counts them
   uint32_t L = L0;
 
   bool staged = E > 0u;                  // the lists are an equal cut of level L: nothing to ask the others
@@ -253,16 +254,22 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
   uint32_t rounds = 1;                   // until the next exchange
   uint32_t part = 0;                     // stage() took an entry whose first arc is another workgroup's
 
-  // Adds (per wavefront, convergent) the lanes with `put` to list `to`.
+  // Adds (per wavefront, convergent) the lanes with `put` to list `to`.  SSSP
+  // lists a node once for every improvement, with all of its arcs each time,
+  // so their sum is bounded by no graph size: 4096 entries of less than 2^31
+  // arcs take 43 bits.
   auto put_all = [&](uint32_t to, bool put, int32_t v, int32_t s0, int32_t d, uint32_t du) {
     const uint64_t mask = __ballot(put);
     if (mask == 0) return;
-    const uint32_t inc = wave_incl_scan(put ? static_cast<uint32_t>(d) : 0u);
+    const uint32_t x = put ? static_cast<uint32_t>(d) : 0u;
+    const uint32_t inc = wave_incl_scan(x);  // mod 2^32
+    unsigned long long sum = inc;            // lane 63: of the wavefront
+    if (__any(x >> 20)) sum = (static_cast<unsigned long long>(wave_sum(x >> 16)) << 16) + wave_sum(x & 0xffffu);
     unsigned long long b = 0;
-    if (lane == 63) b = atomicAdd(&sm.push, (static_cast<unsigned long long>(__popcll(mask)) << 32) | inc);
+    if (lane == 63) b = atomicAdd(&sm.push, (static_cast<unsigned long long>(__popcll(mask)) << 48) + sum);
     b = bcast64(b, 63);
     if (put) {
-      const uint32_t k = static_cast<uint32_t>(b >> 32) + lane_rank(mask);
+      const uint32_t k = static_cast<uint32_t>(b >> 48) + lane_rank(mask);
       if (k < kTeamSlots) {
         sm.list[to].pre[k] = static_cast<uint32_t>(b) + inc - static_cast<uint32_t>(d);
         sm.list[to].st[k] = s0;
@@ -280,8 +287,9 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
     __syncthreads();
     const unsigned long long p = sm.push;
     cur ^= 1u;
-    cnt = min(static_cast<uint32_t>(p >> 32), kTeamSlots);
-    arcs = static_cast<uint32_t>(p);
+    cnt = min(static_cast<uint32_t>(p >> 48), kTeamSlots);
+    end = static_cast<uint32_t>(p);
+    arcs = (p & 0xffff00000000ull) ? 0xffffffffu : end;
     __syncthreads();
     if (tid == 0) sm.push = 0ull;
   };
@@ -302,7 +310,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
       i1 = min(i1, i0 + step);
     }
     cnt = 0;
-    arcs = hi - lo;
+    arcs = end = hi - lo;
     part = lo < hi && ld_agent(at<kNarrow>(f.eprefix, i0)) < lo ? 1u : 0u;
     if (lo < hi) {
       for (uint32_t k0 = 0;; k0 += kTeamBlock) {  // at least one arc of every entry taken lies in [lo, hi)
@@ -337,7 +345,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
       const uint32_t p = sm.list[cur].pre[k];
       const int32_t v = kSssp ? sm.list[cur].node[k] : 0;
       if (last) {
-        const uint32_t pn = k + 1 < cnt ? sm.list[cur].pre[k + 1] : arcs;
+        const uint32_t pn = k + 1 < cnt ? sm.list[cur].pre[k + 1] : end;
         write_entry<kPay, T, kNarrow>(a, out, nb + k, eb + p, v, 0, sm.list[cur].st[k], static_cast<int32_t>(pn - p));
       } else if (nb + k < a.node_cap) {
         st_agent(at<kNarrow>(out.eprefix, nb + k), eb + p);
@@ -552,8 +560,8 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
 #pragma unroll
               for (int b = 0; b < kB; ++b) {
                 // room for this push and one in flight of every wavefront
-                const bool room = (sm.push >> 32) + kTeamBlock <= kTeamSlots;
-                const bool go = v[b] >= 0 && d[b] <= thr && __any(room);
+                const bool room = __any((sm.push >> 48) + kTeamBlock <= kTeamSlots);
+                const bool go = v[b] >= 0 && d[b] <= thr && room;
                 if (v[b] >= 0 && !go) kept |= 1u << (v[b] & 31);
                 put_all(cur ^ 1u, go && s1[b] > s0[b], v[b], s0[b], s1[b] - s0[b], d[b]);
               }
@@ -594,7 +602,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
               v = sm.list[cur].node[k];
               x = sm.list[cur].du[k];
               s0 = sm.list[cur].st[k];
-              d = static_cast<int32_t>((k + 1 < cnt ? sm.list[cur].pre[k + 1] : arcs) - sm.list[cur].pre[k]);
+              d = static_cast<int32_t>((k + 1 < cnt ? sm.list[cur].pre[k + 1] : end) - sm.list[cur].pre[k]);
               keep = static_cast<uint32_t>(v) < a.n &&
                      static_cast<uint32_t>(ld_agent(at<kNarrow>(a.dstate, static_cast<uint32_t>(v))) >> 32) == x;
             }
@@ -608,6 +616,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
         }
         __syncthreads();  // the prefixes are read before the next exchange writes them
         if (leave || sm.most >= kTeamArcs) {
+          bad = bad || arcs > a.m;  // each node once from here on
           ++e;
           alive = team_exchange<kSssp, true>(a, sm, e, me, P, arcs);
           if (!alive) break;
@@ -621,7 +630,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
         alive = team_exchange<kSssp, false>(a, sm, e, me, P, 0ull);
         if (!alive) break;
         if (E > 0u) stage();
-        else cnt = arcs = 0u;
+        else cnt = arcs = end = 0u;
         staged = true;
         rounds = 1u;
         continue;

@@ -238,3 +238,20 @@ def test_teams_beside_big_levels(solve):
         t.join(100)
     assert not any(t.is_alive() for t in ts)
     assert not bad, bad
+
+
+def test_hub_improved_many_times_in_one_level():
+    """3,000 parallel arcs of falling weight to a node of 2^26 arcs, which
+    every improvement queues again: 64 times its arcs are 2^32."""
+    n, k, hub = 1000, 3000, 1 << 26
+    off = np.zeros(n + 1, dtype=np.int32)
+    off[2:] = k
+    off[n] = k + hub
+    cols = np.concatenate([np.full(k, n - 1), np.arange(hub, dtype=np.int32) % (n - 1)]).astype(np.int32)
+    w = np.concatenate([2 * k - np.arange(k), np.full(hub, 7)]).astype(np.uint32)
+    dg = lbg.DeviceGraph.from_numpy(off, cols, w)
+    exp = O.dijkstra(off, cols, w, 1)
+    ws = lbg.Workspace()
+    for _ in range(20):
+        got = lbg.sssp(dg, 1, workspace=ws).cpu().numpy().view(np.uint32)
+        assert np.array_equal(got, exp)

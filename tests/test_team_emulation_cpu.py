@@ -1,0 +1,106 @@
+"""The balanced strategy's kernels on the host (tests/c/emul): the team of
+workgroups that runs small levels, near-far SSSP and the one-level launches,
+compiled from the sources that the library is built from, with a workgroup's
+first or second wavefront running ahead of the others and every array ending
+at an unmapped page.  Full solves equal the oracle; the cases after them are
+inputs on which an earlier form of these kernels was wrong."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import graphgen
+import oracle
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+O = oracle.get()
+
+
+@pytest.fixture(scope="module")
+def emu(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    d = tmp_path_factory.mktemp("team")
+    exe = str(d / "team_run")
+    # 32-bit sources of 64-lane masks: the warnings the device compiler has not
+    subprocess.run(["g++", "-O1", "-std=c++20", "-pthread", "-w", "-I", os.path.join(ROOT, "tests", "c", "emul"),
+                    "-I", os.path.join(ROOT, "paper_1711_00231_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "c", "emul", "team_run.cpp"), "-o", exe], check=True)
+
+    def run(g, **opt):
+        gf, of = str(d / "graph"), str(d / "out")
+        w = g.weights if g.weights is not None else np.ones(g.m)
+        with open(gf, "wb") as f:
+            np.array([g.n, g.m], dtype=np.int32).tofile(f)
+            np.asarray(g.offsets, dtype=np.int32).tofile(f)
+            np.asarray(g.cols, dtype=np.int32).tofile(f)
+            np.asarray(w, dtype=np.uint32).tofile(f)
+        r = subprocess.run([exe, gf, of] + [f"{k}={int(v)}" for k, v in opt.items()], capture_output=True, text=True,
+                           timeout=300)
+        assert r.returncode == 0, (r.returncode, r.stderr[-500:])
+        raw = open(of, "rb").read()
+        head = np.frombuffer(raw, np.int64, 7)
+        st = dict(zip(("error", "levels", "next", "arcs", "entries", "teams", "ones"), (int(x) for x in head)))
+        rest = np.frombuffer(raw, np.uint32, offset=56)
+        st["worklist"] = rest[g.n:].reshape(2, -1)  # edge prefixes, first arcs
+        return rest[: g.n], st
+
+    return run
+
+
+def _graphs():
+    yield graphgen.uniform(9)
+    yield graphgen.grid(24, shortcut_frac=0.02)
+    yield graphgen.rmat(9)
+
+
+@pytest.mark.parametrize("first", [0, 1])
+@pytest.mark.parametrize("far,alone", [(0, 0), (0, 1), (1, 1)])
+def test_sssp_equals_the_oracle(emu, far, alone, first):
+    """alone: the launches that follow a submission without progress, which
+    split the far set in the one-level kernel."""
+    for g in _graphs():
+        s = int(np.argmax(g.degrees))
+        for limit in (1 << 20, 300):  # levels in the team; some beyond it
+            got, st = emu(g, src=s, far=far, alone=alone, first=first, fill=0x5A, limit=limit, blocks=4)
+            assert st["error"] == 0
+            assert np.array_equal(got, O.dijkstra(g.offsets, g.cols, g.weights, s)), (g.name, limit)
+            assert (st["ones"] > 0) == bool(alone or (limit == 300 and not g.name.startswith("grid"))), g.name
+            if alone:
+                break
+
+
+@pytest.mark.parametrize("first", [0, 1])
+def test_bfs_equals_the_oracle(emu, first):
+    for g in _graphs():
+        s = int(np.argmax(g.degrees))
+        for limit, alone in ((1 << 20, 0), (300, 0), (300, 1)):
+            got, st = emu(g, sssp=0, src=s, alone=alone, first=first, fill=0x5A, limit=limit, blocks=4)
+            assert st["error"] == 0
+            assert np.array_equal(got.view(np.int32), O.bfs(g.offsets, g.cols, s)), (g.name, limit, alone)
+
+
+def _graph(n, arcs):
+    """A graph of the arcs (u, v, w), in the order given."""
+    u, v, w = (np.array(x) for x in zip(*arcs))
+    o = np.argsort(u, kind="stable")
+    off = np.concatenate([[0], np.cumsum(np.bincount(u, minlength=n))]).astype(np.int32)
+    return graphgen.Graph("made", off, v[o].astype(np.int32), w[o].astype(np.uint32))
+
+
+@pytest.mark.parametrize("hub", [1 << 26, (1 << 26) - 1, 1 << 22, 3])
+def test_a_hub_improved_many_times_in_one_level(emu, hub):
+    """1,024 parallel arcs of falling weight to a node of `hub` arcs: every
+    improvement queues the node, and 64 x 2^26 arcs are 2^32.  The next level
+    holds the hub's arcs once."""
+    n = 1000
+    g = _graph(n, [(1, n - 1, 5000 - k) for k in range(1024)])
+    _, st = emu(g, src=1, extra=hub, limit=4096, blocks=8, stop=hub > 4096)
+    assert st["error"] == 0
+    if hub > 4096:
+        assert (st["arcs"], st["entries"]) == (hub, 1)
+        assert st["worklist"].tolist() == [[0], [1024]]
+    else:
+        assert st["arcs"] == 0 and st["next"] > 1
