@@ -588,6 +588,9 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
       }
       const bool leave = E > limit || L - L0 >= max_levels;
       if (leave || sm.most > max(kSssp ? kTeamOwnSssp : kTeamOwnBfs, 2 * ((E + P - 1) / P)) || sm.most > kTeamSlots) {
+        // load() has read the flags in every wavefront; after a split no
+        // exchange, with its barrier, lies in between
+        __syncthreads();
         if (tid < kTeamSlots / 64) sm.flag[tid] = 0ull;
         if (kSssp && (leave || nf > a.node_cap)) {
           // only the entry with its node's distance: one per node, so the

@@ -57,7 +57,7 @@ def _graphs():
 
 
 @pytest.mark.parametrize("first", [0, 1])
-@pytest.mark.parametrize("far,alone", [(0, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("far,alone", [(0, 0), (1, 0), (0, 1), (1, 1)])
 def test_sssp_equals_the_oracle(emu, far, alone, first):
     """alone: the launches that follow a submission without progress, which
     split the far set in the one-level kernel."""
@@ -104,3 +104,15 @@ def test_a_hub_improved_many_times_in_one_level(emu, hub):
         assert st["worklist"].tolist() == [[0], [1024]]
     else:
         assert st["arcs"] == 0 and st["next"] > 1
+
+
+@pytest.mark.parametrize("first", [0, 1])
+def test_a_split_whose_nodes_are_all_one_workgroups(emu, first):
+    """Nodes that leave the far set together and lie in one workgroup's share
+    of it: their arcs are dealt out again right after the split."""
+    arcs = [(1000, v, 500_000 + v) for v in range(30)]
+    arcs += [(v, 200 + (17 * v + 13 * k) % 800, 1 + k) for v in range(30) for k in range(60)]
+    g = _graph(1024, arcs)
+    got, st = emu(g, src=1000, far=1, limit=8 * 4096, blocks=8, first=first)
+    assert st["error"] == 0
+    assert np.array_equal(got, O.dijkstra(g.offsets, g.cols, g.weights, 1000))
