@@ -379,6 +379,11 @@ __device__ __forceinline__ void far_move(const KArgs& a, uint32_t v, uint32_t wa
   }
 }
 
+// The bits of word k of the far set that stand for nodes.
+__device__ __forceinline__ uint32_t far_mask(const KArgs& a, uint32_t k) {
+  return k + 1 < a.words || (a.n & 31u) == 0u ? ~0u : (1u << (a.n & 31u)) - 1u;
+}
+
 // The threshold and step of a split, from those of the steps before.
 __device__ __forceinline__ void far_raise(uint32_t delta0, uint32_t most, uint32_t* thr, uint32_t* delta) {
   uint32_t d = *delta;
@@ -433,17 +438,7 @@ __global__ __launch_bounds__(kBlock) void k_init(KArgs a, int32_t src) {
   const uint32_t stride = gridDim.x * kBlock;
   // the host checked 0 <= src < n; a renaming table is the caller's array
   if (a.node_map) src = a.node_map[src];
-  if (static_cast<uint32_t>(src) >= a.n) {
-    if (gid == 0) {
-      a.ctl->error = kErrBadSrc;
-      a.ctl->levels = 0u;
-      a.ctl->ctr[0] = a.ctl->ctr[1] = a.ctl->ctr[2] = 0ull;  // every level finds no work
-    }
-    return;
-  }
-  if (!kSssp && a.pull_min && blockIdx.x == gridDim.x - 1) sym_sample(a);
-  init_state<kSssp>(a, src, gid, stride);
-  if (a.team) {
+  if (a.team) {  // also for a source outside the graph: the launches that follow read it
     if (a.far) {
       for (uint32_t k = gid; k < a.words; k += stride) a.far[k] = 0u;
       if (blockIdx.x == 0) near_far_init(a);
@@ -452,6 +447,20 @@ __global__ __launch_bounds__(kBlock) void k_init(KArgs a, int32_t src) {
     }
     for (uint32_t k = gid; k < 2 * a.tblocks; k += stride) a.tflag[k] = 0ull;
   }
+  if (static_cast<uint32_t>(src) >= a.n) {
+    if (gid == 0) {
+      a.ctl->error = kErrBadSrc;
+      a.ctl->levels = 0u;
+      // every level finds no work, and the far set, if any, no node
+      a.ctl->ctr[0] = a.ctl->ctr[1] = a.ctl->ctr[2] = 0ull;
+      a.ctl->next = 0u;
+      a.ctl->split_at = 0u;
+      a.ctl->far_seen = 0u;
+    }
+    return;
+  }
+  if (!kSssp && a.pull_min && blockIdx.x == gridDim.x - 1) sym_sample(a);
+  init_state<kSssp>(a, src, gid, stride);
   if (a.hier_trace)
     for (uint32_t k = gid; k < kHierTraceLevels * kHierTraceSubs; k += stride) a.hier_trace[k] = 0u;
   const int32_t s0 = a.offsets[src];
@@ -732,7 +741,7 @@ __device__ __forceinline__ void expand_level(const KArgs& a, uint32_t L, unsigne
     if (split) {
       for (uint32_t k0 = tile * 64; k0 < a.words; k0 += W * 64) {
         const uint32_t k = k0 + lane;
-        const uint32_t had = k < a.words ? *at<kNarrow>(a.far, k) : 0u;
+        const uint32_t had = k < a.words ? *at<kNarrow>(a.far, k) & far_mask(a, k) : 0u;
         uint32_t left = had, kept = 0u;
         if (__any(had != 0u) && lane == 0) a.ctl->far_seen = L + 1;  // one value from every writer
         while (__any(left != 0u)) {

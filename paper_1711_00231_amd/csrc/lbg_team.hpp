@@ -534,7 +534,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
           const uint32_t k1 = min((me + 1) * share, a.words);
           for (uint32_t k0 = me * share; k0 < k1; k0 += kTeamBlock) {
             const uint32_t k = k0 + tid;
-            const uint32_t had = k < k1 ? ld_agent(at<kNarrow>(a.far, k)) : 0u;
+            const uint32_t had = k < k1 ? ld_agent(at<kNarrow>(a.far, k)) & far_mask(a, k) : 0u;
             if (had) sm.found = 1u;
             uint32_t left = had, kept = 0u;
             while (__any(left != 0u)) {

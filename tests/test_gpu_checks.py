@@ -3,6 +3,8 @@ numpy: the hierarchical strategy's sub-iteration schedule (Section III-C)
 against oracle_hp_schedule, the skipped-arc counter behind the SSSP roofline
 figure, the COO source builder, and the device guards that turn a foreign
 renaming or split table into an error instead of an out-of-range access."""
+import time
+
 import numpy as np
 import pytest
 
@@ -173,3 +175,26 @@ def test_malformed_split_table_is_an_error():
         sp.split_offsets = saved
     again = lbg.bfs(dg, s, strategy="split", mdt=64).cpu().numpy()
     assert np.array_equal(again, ok)
+
+
+@pytest.mark.parametrize("n,k", [(140_001, 8), (2_000, 8)])
+def test_foreign_renaming_table_on_sparse_graphs(n, k):
+    """The same on graphs of at most 16 arcs per node, the larger of which
+    defers far nodes; the call returns at once."""
+    g = graphgen.uniform(n=n, k=k)
+    dg = _dev(g)
+    og = dg.ensure_ordered()
+    out = torch.full((g.n,), -1, dtype=torch.int32, device="cuda")
+    exp = O.dijkstra(g.offsets, g.cols, g.weights, 5)
+    saved, bad = og.new_id, og.new_id.clone()
+    for wrong in (g.n, g.n + 17, -3):
+        bad[5] = wrong
+        og.new_id = bad
+        try:
+            t0 = time.perf_counter()
+            with pytest.raises(lbg.LbgError, match="source outside"):
+                lbg.sssp(dg, 5, out=out, ordered=True)
+            assert time.perf_counter() - t0 < 5.0  # a team without members would wait for 10 s
+        finally:
+            og.new_id = saved
+        assert np.array_equal(lbg.sssp(dg, 5, out=out, ordered=True).cpu().numpy().view(np.uint32), exp)

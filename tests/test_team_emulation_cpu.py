@@ -16,6 +16,7 @@ import oracle
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 O = oracle.get()
+BAD_SRC = 32  # the guard of a source outside the graph
 
 
 @pytest.fixture(scope="module")
@@ -116,3 +117,14 @@ def test_a_split_whose_nodes_are_all_one_workgroups(emu, first):
     got, st = emu(g, src=1000, far=1, limit=8 * 4096, blocks=8, first=first)
     assert st["error"] == 0
     assert np.array_equal(got, O.dijkstra(g.offsets, g.cols, g.weights, 1000))
+
+
+@pytest.mark.parametrize("fill,join", [(0xFF, 0), (0x25, 0), (0x00, 1), (0xA5, 0x7FFFFFFF), (0x01, 0x80000003)])
+@pytest.mark.parametrize("far", [0, 1])
+def test_a_source_renamed_out_of_the_graph(emu, far, fill, join):
+    """The call ends with the error at once, whatever the workspace and the
+    output (which holds the far set) were left with."""
+    g = graphgen.uniform(n=1001, k=8)
+    for renamed in (g.n, g.n + 17, -1):
+        _, st = emu(g, src=5, renamed=renamed, far=far, fill=fill, join=join, blocks=4)
+        assert st["error"] == BAD_SRC
