@@ -272,19 +272,32 @@ thread_local uint32_t g_big_hint[2] = {0u, 0u};
 thread_local uint32_t g_level_hint[2] = {0u, 0u};
 // BFS solves of graphs of at least this many arcs may pull levels.
 constexpr int64_t kPullGraph = int64_t{1} << 24;
-// Key of k_bfs_sym's hash: drawn once per process.
-unsigned long long sym_key() {
-  static const unsigned long long key = [] {
-    unsigned long long k = static_cast<unsigned long long>(std::chrono::steady_clock::now().time_since_epoch().count());
-    try {
-      std::random_device rd;
-      k ^= (static_cast<unsigned long long>(rd()) << 32) | rd();
-    } catch (...) {  // no entropy source: the clock alone
-      k *= 0x9e3779b97f4a7c15ull;
+// The points of k_bfs_sym for one solve: uniform in the field, from a start
+// drawn at random when the first solve asks and moved on with each one, so a
+// graph that passed by chance does not pass again and again.
+void sym_points(double (&x)[lbg::kSymPoints]) {
+  constexpr unsigned long long p = lbg::kSymP;
+  struct Start {
+    unsigned long long x[lbg::kSymPoints];
+    Start() {
+      unsigned long long mix = static_cast<unsigned long long>(std::chrono::steady_clock::now().time_since_epoch().count());
+      for (unsigned long long& v : x) {
+        do {
+          try {
+            std::random_device rd;
+            v = ((static_cast<unsigned long long>(rd()) << 32) | rd()) >> 13;
+          } catch (...) {  // no entropy source: the clock alone
+            v = (mix = mix * 6364136223846793005ull + 1442695040888963407ull) >> 13;
+          }
+        } while (v >= p);
+      }
     }
-    return k;
-  }();
-  return key;
+  };
+  static const Start start;
+  static std::atomic<unsigned long long> solves{0};
+  const unsigned long long k = solves.fetch_add(1, std::memory_order_relaxed) % p;
+  for (int i = 0; i < lbg::kSymPoints; ++i)
+    x[i] = static_cast<double>((1ull << 52) + (start.x[i] + static_cast<unsigned __int128>(k) * (p / 3)) % p);
 }
 constexpr uint32_t kTeamDense = 512;  // arcs per team workgroup, see solve()
 // SSSP solves of sparse graphs of at most this many arcs are expected to stay
@@ -501,9 +514,15 @@ int solve(const Problem& P) {
   // Pull levels (lbg_pull.hpp): a pass over all arcs establishes symmetry, so
   // the level must hold a good part of them (a quarter of what it costs to
   // expand m / 16 arcs), and the graph enough for the extra launches to pay.
-  if (scan_all && P.m >= kPullGraph && a.scan_min <= P.m / 16) {
+  // The pass tells the pairs of kSymNodes nodes apart, and its workgroups leave
+  // their products (12 words each) in a worklist's node array, of n words.
+  constexpr int kPartWords = 2 * 2 * lbg::kSymPoints;
+  int sym_blocks = 0;
+  if (scan_all && P.m >= kPullGraph && a.scan_min <= P.m / 16 && P.n >= kPartWords &&
+      static_cast<uint32_t>(P.n) <= lbg::kSymNodes) {
     a.pull_min = static_cast<uint32_t>(P.m / 16);
-    a.sym_key = sym_key();
+    sym_points(a.sym_x);
+    sym_blocks = P.n / kPartWords;
   }
   const bool wide_chunk = P.n >= (1 << 22);
   const int64_t chunk = lbg::kCompactBlock * (wide_chunk ? 16 : 4);
@@ -647,8 +666,8 @@ int solve(const Problem& P) {
           break;
         default:
           if (a.pull_min && nth < 2) {  // the first level worth pulling comes early
-            if (narrow) hipLaunchKernelGGL((lbg::k_bfs_sym<true>), dim3(GR.sym[nw]), dim3(lbg::kBlock), 0, st, a, L);
-            else hipLaunchKernelGGL((lbg::k_bfs_sym<false>), dim3(GR.sym[nw]), dim3(lbg::kBlock), 0, st, a, L);
+            if (narrow) hipLaunchKernelGGL((lbg::k_bfs_sym<true>), dim3(std::min(GR.sym[nw], sym_blocks)), dim3(lbg::kBlock), 0, st, a, L);
+            else hipLaunchKernelGGL((lbg::k_bfs_sym<false>), dim3(std::min(GR.sym[nw], sym_blocks)), dim3(lbg::kBlock), 0, st, a, L);
           }
           if (scan_possible) {  // may scan: the filter merge precedes, the compaction follows
             const dim3 cg(compact_blocks), cb(lbg::kCompactBlock);

@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "lbg_sym.hpp"
+
 namespace lbg {
 
 constexpr int kBlock = 256;              // threads per workgroup (4 waves)
@@ -65,14 +67,14 @@ struct Ctl {
   unsigned int far_seen;      //   and 1 + the last one that found a node in it
   unsigned int sym_no;        // BFS: the graph is not symmetric
   unsigned long long worked;  // balanced: bit k % 64 set when launch k found work
-  unsigned int sym_run;       // BFS: 1 + the launch that summed the arcs (k_bfs_sym), 0: none did
+  unsigned int sym_run;       // BFS: 1 + the launch that went over the arcs (k_bfs_sym), 0: none did
   unsigned int solo_levels;   // batches: most levels of a query solved by one workgroup
   unsigned long long pad1;
   // [x][0] updates, [x][1] global atomics issued; [x][2], [x][3] the same for
   // levels run by the small-frontier kernel; [x][4 + L % 3] the packed tail
   // (nodes << 32 | edges) of slice x's worklist of level L (destination-
   // sliced strategy); [x][8 + L % 3] the balanced kernel's tile counter of
-  // XCD x for level L (single solves); [x][11] its part of k_bfs_sym's sum;
+  // XCD x for level L (single solves); [0][11] k_bfs_sym's workgroups that are done;
   // [class][12] next query of k_solo; [x][13], [x][14] entries and arcs of
   // queries solved by it
   unsigned long long xstat[kXcds][16];
@@ -165,7 +167,7 @@ struct KArgs {
   // BFS levels of at least pull_min arcs are pulled if the graph is
   // symmetric (lbg_pull.hpp).  0: never.
   uint32_t pull_min;
-  unsigned long long sym_key;  // of k_bfs_sym's hash
+  double sym_x[kSymPoints];  // 2^52 + k_bfs_sym's points
   const QInfo* qtab;     // batched solves
   uint32_t num_queries;
   uint32_t solo_arcs;    // a query on an instance of at most this many arcs may be solved by one workgroup (0: none)

@@ -402,7 +402,7 @@ __device__ __forceinline__ void sym_sample(const KArgs& a) {
   __shared__ uint32_t no;
   if (threadIdx.x == 0) no = 0u;
   __syncthreads();
-  const uint32_t u = (threadIdx.x * 0x9e3779b1u + static_cast<uint32_t>(a.sym_key >> 20)) % a.n;
+  const uint32_t u = (threadIdx.x * 0x9e3779b1u + static_cast<uint32_t>(__builtin_bit_cast(unsigned long long, a.sym_x[0]) >> 8)) % a.n;
   const uint32_t s = static_cast<uint32_t>(a.offsets[u]), e = static_cast<uint32_t>(a.offsets[u + 1]);
   uint32_t vs = 0, ve = 0, best = 33;
   if (s < e && e <= a.m) {
@@ -1136,10 +1136,7 @@ __device__ __forceinline__ void expand_level(const KArgs& a, uint32_t L, unsigne
 // The level is pulled (lbg_pull.hpp): it is large and the graph has been found
 // symmetric.  Grid-uniform once k_bfs_sym has run.
 __device__ __forceinline__ bool pulls(const KArgs& a, uint32_t Ef) {
-  if (a.pull_min == 0u || Ef < a.pull_min || a.ctl->sym_run == 0u || a.ctl->sym_no != 0u) return false;
-  unsigned long long sum = 0;
-  for (int x = 0; x < kXcds; ++x) sum += a.ctl->xstat[x][11];
-  return sum == 0ull;
+  return a.pull_min != 0u && Ef >= a.pull_min && a.ctl->sym_run != 0u && a.ctl->sym_no == 0u;
 }
 
 // Balanced single solves: the level that launch number k of the solve finds

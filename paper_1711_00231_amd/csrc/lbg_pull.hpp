@@ -14,19 +14,16 @@
 //  * k_init samples arcs between low-degree nodes; one without its reverse
 //    settles the matter (directed graphs of low degree stop here);
 //  * k_bfs_sym then reads every arc once, in order (a streaming pass, 4 bytes
-//    per arc), and adds sgn(v - u) * h({u, v}) over all arcs u -> v, h a
-//    64-bit hash with a key drawn at random when the library is loaded.  The
-//    sum over a symmetric graph is 0 by cancellation, always.  For any other
-//    graph it is a sum of hash values with non-zero coefficients, 0 with a
-//    chance of about 2^-64 over the keys, far below that of a memory error;
-//    such a graph is expanded as before.  (Single pairs cannot cancel: h is a
-//    bijection of the pair.)
+//    per arc), and compares the products of lbg_sym.hpp at three random points:
+//    a symmetric graph always passes, any other one with a chance below 2^-60,
+//    and then it is expanded as before.
 // R-MAT 22: 0.98 -> 0.48 ms for the solve, of which the pass over 513 MB of
 // arcs takes 174 us (2.9 TB/s) and the two pulled levels 112 + 38 us, where
 // expansion and compaction took 265 + 582 us; R-MAT 24: 4.28 -> 1.38 ms.
 #pragma once
 
 #include "lbg_kernels.hpp"
+#include "lbg_sym.hpp"
 
 namespace lbg {
 
@@ -37,12 +34,38 @@ constexpr uint32_t kPullAlone = 32;  // arcs a lane tries before its wavefront h
 constexpr uint32_t kSymItems = 16;   // arcs per lane of a tile of k_bfs_sym
 constexpr uint32_t kSymTile = 64 * kSymItems;
 
-__device__ __forceinline__ unsigned long long sym_hash(uint32_t u, uint32_t v, unsigned long long key) {
-  unsigned long long x = (static_cast<unsigned long long>(min(u, v)) << 32 | max(u, v)) ^ key;
-  x *= 0x9fb21c651e98df25ull;
-  x ^= x >> 32;
-  x *= 0xd6e8feb86659fd93ull;
-  return x ^ (x >> 29);
+// The products of a workgroup's threads, in thread 0.  Begins and ends with
+// the use of `sums`: two calls need a barrier in between.
+__device__ __forceinline__ void sym_block(SymProducts& s, double (&sums)[kWaves][2 * kSymPoints]) {
+  const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  sym_finish(s);
+  double up[kSymPoints], down[kSymPoints];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    const int l = static_cast<int>(lane ^ d);
+#pragma unroll
+    for (int i = 0; i < kSymPoints; ++i) {
+      up[i] = __builtin_bit_cast(double, bcast64(__builtin_bit_cast(unsigned long long, s.up[i]), l));
+      down[i] = __builtin_bit_cast(double, bcast64(__builtin_bit_cast(unsigned long long, s.down[i]), l));
+    }
+    sym_join(s, up, down);
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int i = 0; i < kSymPoints; ++i) {
+      sums[wid][2 * i] = s.up[i];
+      sums[wid][2 * i + 1] = s.down[i];
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int w = 1; w < kWaves; ++w) {
+      for (int i = 0; i < kSymPoints; ++i) {
+        up[i] = sums[w][2 * i];
+        down[i] = sums[w][2 * i + 1];
+      }
+      sym_join(s, up, down);
+    }
 }
 
 // Launched before the solve's one-level launches; does its pass once, before
@@ -55,6 +78,8 @@ template <bool kNarrow>
 __global__ __launch_bounds__(kBlock) void k_bfs_sym(KArgs a, uint32_t launch) {
   __shared__ unsigned long long flag_s[kWaves][kSymItems];
   __shared__ uint32_t node_s[kWaves][kSymTile];
+  __shared__ double sums[kWaves][2 * kSymPoints];
+  __shared__ uint32_t last;
   const uint32_t L = level_of(a, launch);
   const uint32_t Ef = static_cast<uint32_t>(ld_agent(&a.ctl->ctr[L % 3]));
   if (Ef < a.pull_min || Ef <= a.min_arcs || a.ctl->sym_no != 0u) return;
@@ -69,7 +94,9 @@ __global__ __launch_bounds__(kBlock) void k_bfs_sym(KArgs a, uint32_t launch) {
   const unsigned long long W = static_cast<unsigned long long>(gridDim.x) * kWaves;
   const unsigned long long g = static_cast<unsigned long long>(blockIdx.x) * kWaves + wid;
   const uint32_t t0 = static_cast<uint32_t>(tiles * g / W), t1 = static_cast<uint32_t>(tiles * (g + 1) / W);
-  unsigned long long acc = 0;
+  SymProducts prod;
+  sym_start(prod);
+  const double x[kSymPoints] = {a.sym_x[0], a.sym_x[1], a.sym_x[2]};
   bool bad = false;
   if (t0 < t1) {
     // the node that holds the range's first arc: the last with offset <= e
@@ -121,27 +148,44 @@ __global__ __launch_bounds__(kBlock) void k_bfs_sym(KArgs a, uint32_t launch) {
         if (word) cur = start[r * 64 + 63 - __builtin_clzll(word)];
         const uint32_t v = static_cast<uint32_t>(vv[r]);
         if (e0 + r * 64 + lane < e1) {
-          bad = bad || v >= a.n;
-          if (v != u) {
-            const unsigned long long h = sym_hash(u, v, a.sym_key);
-            acc += v > u ? h : 0ull - h;
-          }
+          if (v >= a.n) bad = true;
+          else if (v != u) sym_arc(prod, u, v, x);
         }
       }
       wave_sync();
     }
   }
-  // one atomic per workgroup on its XCD's line
-  __shared__ unsigned long long sums[kWaves];
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) acc += bcast64(acc, static_cast<int>(lane ^ d));
-  if (lane == 0) sums[wid] = acc;
   if (__any(bad) && lane == 0) a.ctl->sym_no = 1u;
-  __syncthreads();
+  sym_block(prod, sums);
+  unsigned long long* const part = reinterpret_cast<unsigned long long*>(a.fr[1].node);
   if (threadIdx.x == 0) {
-    unsigned long long s = 0;
-    for (int w = 0; w < kWaves; ++w) s += sums[w];
-    if (s) atomicAdd(&a.ctl->xstat[blockIdx.x % kXcds][11], s);
+    unsigned long long* mine = part + 2 * kSymPoints * static_cast<size_t>(blockIdx.x);
+#pragma unroll
+    for (int i = 0; i < kSymPoints; ++i) {
+      st_agent(&mine[2 * i], __builtin_bit_cast(unsigned long long, prod.up[i]));
+      st_agent(&mine[2 * i + 1], __builtin_bit_cast(unsigned long long, prod.down[i]));
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    last = atomicAdd(&a.ctl->xstat[0][11], 1ull) == gridDim.x - 1 ? 1u : 0u;
+  }
+  __syncthreads();
+  if (!last) return;
+  sym_start(prod);
+  for (uint32_t b = threadIdx.x; b < gridDim.x; b += kBlock) {
+    const unsigned long long* w = part + 2 * kSymPoints * static_cast<size_t>(b);
+    double up[kSymPoints], down[kSymPoints];
+#pragma unroll
+    for (int i = 0; i < kSymPoints; ++i) {
+      up[i] = __builtin_bit_cast(double, ld_agent(&w[2 * i]));
+      down[i] = __builtin_bit_cast(double, ld_agent(&w[2 * i + 1]));
+    }
+    sym_join(prod, up, down);
+  }
+  sym_block(prod, sums);
+  if (threadIdx.x == 0) {
+    bool same = true;
+    for (int i = 0; i < kSymPoints; ++i) same = same && sym_equal(prod.up[i], prod.down[i]);
+    if (!same) a.ctl->sym_no = 1u;
   }
 }
 

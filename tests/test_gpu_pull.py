@@ -124,3 +124,14 @@ def test_thresholds(rmat20):
         dg = lbg.DeviceGraph.from_numpy(rmat20.offsets, rmat20.cols)
         s = int(graphgen.sources(rmat20, 1, graphgen.FAMILY_RMAT)[0])
         assert np.array_equal(lbg.bfs(dg, s).cpu().numpy(), O.bfs(rmat20.offsets, rmat20.cols, s)), arcs
+
+
+def test_structured_one_way_arcs(rmat20):
+    """Four arcs around a cycle, of ids that differ in high bits: sums of hash
+    values with a key that was only xored in used to cancel on such."""
+    g = rmat20
+    s = np.repeat(np.arange(g.n), g.degrees)
+    for a, a2, b, b2 in ((5, 5 ^ 2**18, 2**19 + 9, (2**19 + 9) ^ 2**17), (3, 3 ^ 2**17, 2**19 + 123, 2**18 + 123)):
+        h = graphgen.from_edges(g.n, np.concatenate([s, [a, b, a2, b2]]),
+                                np.concatenate([g.cols, [b, a2, b2, a]]), None, "cycle")
+        _solve(h, graphgen.sources(g, 2, graphgen.FAMILY_RMAT), False)
