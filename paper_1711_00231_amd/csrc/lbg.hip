@@ -260,6 +260,37 @@ struct PinnedCtl {
   }
 };
 thread_local PinnedCtl g_pinned;
+// Whether a solve on this device has a team of many workgroups (lbg_team.hpp)
+// at the moment: held for the time of one.  Members of a team wait for each
+// other, and a team's kernel is only ever placed beside kernels that wait for
+// nobody: the solves that find the place taken run their small levels in one
+// workgroup (and defer no far nodes, whose splits need the many).  Eight
+// threads solving side by side, with a team each, once stopped making
+// progress, for a reason that was not found; nor do several teams, which fill
+// the CUs with waiting wavefronts, serve each other.
+class TeamPlace {
+ public:
+  explicit TeamPlace(bool wanted) {
+    int dev = 0;
+    if (!wanted) return;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
+    if (!taken()[dev].exchange(true)) mine_ = &taken()[dev];
+  }
+  ~TeamPlace() {
+    if (mine_) mine_->store(false);
+  }
+  TeamPlace(const TeamPlace&) = delete;
+  TeamPlace& operator=(const TeamPlace&) = delete;
+  bool mine() const { return mine_ != nullptr; }
+
+ private:
+  static std::atomic<bool>* taken() {
+    static std::atomic<bool> t[64];
+    return t;
+  }
+  std::atomic<bool>* mine_ = nullptr;
+};
+
 // One-level launches that had work in the first submission of this thread's
 // previous balanced solve, plus one, per kind (BFS, SSSP): the next solve
 // enqueues that many, so a typical solve needs one read-back and few empty
@@ -473,10 +504,12 @@ int solve(const Problem& P) {
     else a.tflag = reinterpret_cast<unsigned long long*>(
         P.is_sssp ? (reinterpret_cast<uintptr_t>(P.out) + 7) / 8 * 8 : reinterpret_cast<uintptr_t>(ws + Lay.node[0]));
   }
+  const TeamPlace place(a.tblocks > 1);
+  const uint32_t team_wgs = place.mine() ? a.tblocks : std::min<uint32_t>(a.tblocks, 1u);
   a.n = static_cast<uint32_t>(P.n);
   a.m = static_cast<uint32_t>(P.m);
   a.words = static_cast<uint32_t>((static_cast<size_t>(P.n) + 31) / 32);
-  if (P.is_sssp && strat == LBG_BALANCED && near_far(P.n, P.m))
+  if (P.is_sssp && place.mine() && near_far(P.n, P.m))
     a.far = reinterpret_cast<uint32_t*>(a.tflag + 2 * a.tblocks);  // n / 32 of the output's n words
   a.node_cap = Lay.node_cap;
   a.tile_cap = Lay.tile_cap;
@@ -484,7 +517,7 @@ int solve(const Problem& P) {
   a.scan_min = 0xffffffffu;
   // levels of at most this many arcs run in the small-frontier team; a level
   // that a caller's threshold makes a scan level does not
-  uint32_t team_limit = strat == LBG_BALANCED ? a.tblocks * lbg::kTeamSlots : 0u;
+  uint32_t team_limit = team_wgs * lbg::kTeamSlots;
   if (!P.is_sssp && strat == LBG_BALANCED) {
     int64_t smin;
     {
@@ -503,7 +536,7 @@ int solve(const Problem& P) {
   // entries that improve again while they are expanded, which saves more than
   // the team's shorter steps from 64 K arcs on (R-MAT 15: 0.296 against
   // 0.315 ms with the full limit)
-  if (P.is_sssp && P.m > 16 * static_cast<int64_t>(P.n)) team_limit = std::min(team_limit, a.tblocks * kTeamDense);
+  if (P.is_sssp && P.m > 16 * static_cast<int64_t>(P.n)) team_limit = std::min(team_limit, team_wgs * kTeamDense);
   // a level can only run in scan mode if the graph has that many arcs
   const bool scan_possible = static_cast<int64_t>(a.scan_min) <= P.m;
   // Every level that reaches the one-level launches scans (the default on
@@ -748,7 +781,7 @@ int solve(const Problem& P) {
   };
   auto team = [&]() -> int {
     const uint32_t max_levels = static_cast<uint32_t>(std::min<uint64_t>(level_cap + 1 - L, 0xffffffffu));
-    const dim3 tg(a.tblocks), tb(lbg::kTeamBlock);
+    const dim3 tg(team_wgs), tb(lbg::kTeamBlock);
     if (P.is_sssp && packed) {
       if (narrow) hipLaunchKernelGGL((lbg::k_expand_team<true, true, true>), tg, tb, 0, st, a, k, seq, team_limit, max_levels);
       else hipLaunchKernelGGL((lbg::k_expand_team<true, false, true>), tg, tb, 0, st, a, k, seq, team_limit, max_levels);

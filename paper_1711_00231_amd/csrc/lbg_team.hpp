@@ -24,7 +24,9 @@
 // the team when every workgroup of the grid has joined or after kTeamWait,
 // and only the workgroups that joined before take part.  So the members are
 // all running, and nobody ever waits for a workgroup that has not been
-// scheduled.  A wait gives up after kTeamPatience (kErrTeam).
+// scheduled.  A wait gives up after kTeamPatience (kErrTeam), and the launches
+// behind it do nothing.  One solve at a time has a team of several workgroups
+// (TeamPlace in lbg.hip); the others launch this kernel with one.
 #pragma once
 
 #include "lbg_kernels.hpp"
@@ -200,6 +202,8 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
   __shared__ uint32_t red[2][kTeamWaves];
   const uint32_t tid = threadIdx.x, lane = tid & 63;
 
+  // an earlier launch of the solve failed: what it left is not to be built on
+  if (ld_agent(&a.ctl->error) != 0u) return;
   const uint32_t L0 = level_of(a, launch);
   const unsigned long long c0 = ld_agent(&a.ctl->ctr[L0 % 3]);
   uint32_t nf = static_cast<uint32_t>(c0 >> 32), E = static_cast<uint32_t>(c0);
@@ -306,6 +310,10 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
       const uint32_t i = i0 + tid * step;
       const bool le = i < i1 && ld_agent(at<kNarrow>(f.eprefix, i)) <= lo;
       const uint32_t ranks = static_cast<uint32_t>(__syncthreads_count(le));
+      if (ranks == 0u) {  // not a worklist
+        bad = true;
+        break;
+      }
       i0 += (ranks - 1) * step;
       i1 = min(i1, i0 + step);
     }

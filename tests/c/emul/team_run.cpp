@@ -14,6 +14,7 @@
 //   fill=B     byte that the workspace and the output hold before the solve
 //   join=J     words 0 .. 3 of the team's control block (its join counters)
 //   alone=1    one-level launches only, as after a submission without progress
+//   error=E    an error that the launches after k_init find
 //   stop=1     end after the first team launch
 //   first=W    the wavefront of a workgroup that runs first
 #include <sys/mman.h>
@@ -134,10 +135,11 @@ int main(int argc, char** argv) {
     if (sssp) k_init<true, false>(a, src);
     else k_init<false, false>(a, src);
   });
+  if (opt.count("error")) a.ctl->error = static_cast<unsigned>(get("error", 0));
   for (int step = 0; step < 2000; ++step) {
     a.min_arcs = alone ? 0u : limit;
     if (!alone) team();
-    if (get("stop", 0)) break;
+    if (get("stop", 0) || opt.count("error")) break;
     for (int i = 0; i < 3; ++i) one();
     if (!alone) team();
     if (sssp) emu::launch(2, kBlock, [=] { k_sssp_finish(a); });

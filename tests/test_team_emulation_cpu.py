@@ -128,3 +128,12 @@ def test_a_source_renamed_out_of_the_graph(emu, far, fill, join):
     for renamed in (g.n, g.n + 17, -1):
         _, st = emu(g, src=5, renamed=renamed, far=far, fill=fill, join=join, blocks=4)
         assert st["error"] == BAD_SRC
+
+
+def test_nothing_runs_after_an_error(emu):
+    """A team launch behind one that failed leaves everything as it is."""
+    g = graphgen.grid(24, shortcut_frac=0.02)
+    for far in (0, 1):
+        out, st = emu(g, src=5, far=far, blocks=4, error=128, fill=0x5A)
+        assert (st["error"], st["levels"], st["next"]) == (128, 0, 0)
+        assert st["arcs"] == g.degrees[5]
