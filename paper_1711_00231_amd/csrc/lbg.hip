@@ -547,12 +547,14 @@ int solve(const Problem& P) {
   // Pull levels (lbg_pull.hpp): a pass over all arcs establishes symmetry, so
   // the level must hold a good part of them (a quarter of what it costs to
   // expand m / 16 arcs), and the graph enough for the extra launches to pay.
+  // Whether smaller levels scan does not matter: where one may not have, the
+  // filter merge precedes every launch and takes the snapshot, too.
   // The pass tells the pairs of kSymNodes nodes apart, and its workgroups leave
   // their products (12 words each) in a worklist's node array, of n words.
   constexpr int kPartWords = 2 * 2 * lbg::kSymPoints;
   int sym_blocks = 0;
-  if (scan_all && P.m >= kPullGraph && a.scan_min <= P.m / 16 && P.n >= kPartWords &&
-      static_cast<uint32_t>(P.n) <= lbg::kSymNodes) {
+  if (scan_possible && P.m >= kPullGraph && std::max(a.scan_min, team_limit + 1u) <= P.m / 16 &&
+      P.n >= kPartWords && static_cast<uint32_t>(P.n) <= lbg::kSymNodes) {
     a.pull_min = static_cast<uint32_t>(P.m / 16);
     sym_points(a.sym_x);
     sym_blocks = P.n / kPartWords;

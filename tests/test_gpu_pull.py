@@ -135,3 +135,16 @@ def test_structured_one_way_arcs(rmat20):
         h = graphgen.from_edges(g.n, np.concatenate([s, [a, b, a2, b2]]),
                                 np.concatenate([g.cols, [b, a2, b2, a]]), None, "cycle")
         _solve(h, graphgen.sources(g, 2, graphgen.FAMILY_RMAT), False)
+
+
+def test_more_nodes_than_every_level_scanning():
+    """Beyond 2^24 nodes (and with a threshold of one's own) some levels push:
+    the snapshot that a pulled level reads is taken before its launch."""
+    rng = np.random.default_rng(24)
+    n, core, half = (1 << 24) + 100, 1 << 18, 8_600_000
+    u = np.concatenate([(rng.random(half) ** 3 * core).astype(np.int64), np.arange(50)])
+    v = np.concatenate([rng.integers(0, core, half), np.arange(n - 50, n)])
+    g = graphgen.from_edges(n, np.concatenate([u, v]), np.concatenate([v, u]), None, "tall")
+    _solve(g, [int(u[0]), n - 1], True)
+    lbg.set_bfs_scan_min(600_000)  # levels of 524,289 .. 599,999 arcs push
+    _solve(g, [int(u[0])], True)
