@@ -954,8 +954,6 @@ BatchLayout batch_layout(int32_t num_queries, int64_t rows, int64_t total_arcs) 
   return L;
 }
 
-constexpr int64_t kSoloBatch = int64_t{1} << 28;  // see batch_solve
-
 // An instantiated graph of one replay of a graph-launched batch: kGraphLevels
 // expansion launches, the level advance, the conditional write-out and the
 // read-back of the control block.  Cached per thread and reused while the
@@ -1112,7 +1110,8 @@ int batch_solve(const int32_t* offsets, const int32_t* cols, const uint32_t* wei
   }
 
   bool has[5] = {};
-  if (!use_graph && total_arcs >= kSoloBatch) {
+  const bool solo = !use_graph && total_arcs >= static_cast<int64_t>(lbg::kSoloBatch);
+  if (solo) {
     // longest first (a query's place in the table means nothing)
     std::sort(qt.begin(), qt.end(), [](const lbg::QInfo& x, const lbg::QInfo& y) { return x.row_len > y.row_len; });
     for (const lbg::QInfo& I : qt) has[solo_by_size(I)] = true;
@@ -1123,14 +1122,7 @@ int batch_solve(const int32_t* offsets, const int32_t* cols, const uint32_t* wei
   a.cols = cols;
   a.weights = weights;
   a.dist = out;
-  // One workgroup gets through 0.6 to 1.2 G arcs/s, the chip through about
-  // 200 when it has several for every CU: batches of 2^28 arcs and more take
-  // their small queries that way (2,048 queries over 2.6 G arcs: the 1,024
-  // BFS queries 20 -> 6.8 ms), except those with more than a 256th of the
-  // batch, which would hold it up.  Smaller batches are done sooner in the
-  // shared worklist (28 queries, 8 M arcs: 1.1 against 2.5 ms).
-  if (!use_graph && total_arcs >= kSoloBatch)
-    a.solo_arcs = static_cast<uint32_t>(total_arcs / 256);
+  a.solo = solo ? 1u : 0u;
   a.dstate = reinterpret_cast<unsigned long long*>(ws + Lay.dstate);
   a.visited = reinterpret_cast<uint32_t*>(ws + Lay.rbits);
   a.d16 = reinterpret_cast<uint16_t*>(ws + Lay.d16);
@@ -1167,11 +1159,12 @@ int batch_solve(const int32_t* offsets, const int32_t* cols, const uint32_t* wei
   for (const lbg::QInfo& I : qt) max_len = std::max<int64_t>(max_len, I.row_len);
   const dim3 rgrid = row_grid(num_queries, max_len);
   const int seed_blocks = (num_queries + lbg::kBlock - 1) / lbg::kBlock;
+  if (solo) hipLaunchKernelGGL(lbg::k_solo_limit, dim3(1), dim3(1024), 0, st, a);
   hipLaunchKernelGGL(lbg::k_batch_fill, rgrid, dim3(lbg::kBlock), 0, st, a);
   if (narrow) hipLaunchKernelGGL(lbg::k_batch_seed<true>, dim3(seed_blocks), dim3(lbg::kBlock), 0, st, a);
   else hipLaunchKernelGGL(lbg::k_batch_seed<false>, dim3(seed_blocks), dim3(lbg::kBlock), 0, st, a);
   HIP_TRY(hipGetLastError());
-  if (a.solo_arcs) {
+  if (solo) {
     const int rc = launch_solo(a, has, narrow, st);
     if (rc) return rc;
   }

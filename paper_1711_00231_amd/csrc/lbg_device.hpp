@@ -69,7 +69,8 @@ struct Ctl {
   unsigned long long worked;  // balanced: bit k % 64 set when launch k found work
   unsigned int sym_run;       // BFS: 1 + the launch that went over the arcs (k_bfs_sym), 0: none did
   unsigned int solo_levels;   // batches: most levels of a query solved by one workgroup
-  unsigned long long pad1;
+  unsigned int solo_limit;    // batches: arcs of the largest instance whose queries one workgroup may solve
+  unsigned int pad1;
   // [x][0] updates, [x][1] global atomics issued; [x][2], [x][3] the same for
   // levels run by the small-frontier kernel; [x][4 + L % 3] the packed tail
   // (nodes << 32 | edges) of slice x's worklist of level L (destination-
@@ -170,7 +171,7 @@ struct KArgs {
   double sym_x[kSymPoints];  // 2^52 + k_bfs_sym's points
   const QInfo* qtab;     // batched solves
   uint32_t num_queries;
-  uint32_t solo_arcs;    // a query on an instance of at most this many arcs may be solved by one workgroup (0: none)
+  uint32_t solo;         // 1: small queries are solved by one workgroup each (ctl->solo_limit), 0: none
   uint32_t rows;         // batched solves: total elements of node state
   uint32_t* qlast;       // engine: per slot, the last level that holds one of its query's entries (kQIdle: none)
   // Degree-binned strategy: a node with more than `mdt` out-arcs is queued as

@@ -1797,14 +1797,45 @@ constexpr uint32_t kRowChunk = 4096;
 // their state takes: classes 1 and 2, BFS with a bit per node; 3 and 4, SSSP
 // with a word per node.  Class 0: the shared worklist.
 constexpr uint32_t kSoloWords[5] = {0u, 8192u, 32768u, 8192u, 32768u};
+__device__ __forceinline__ bool query_arcs(const KArgs& a, const QInfo& qi, uint32_t* arcs) {
+  const int32_t lo = qi.row_start - qi.delta;
+  const int32_t s = a.offsets[lo], e = a.offsets[lo + qi.row_len];
+  *arcs = static_cast<uint32_t>(e - s);
+  return s >= 0 && e >= s && static_cast<uint32_t>(e) <= a.m;
+}
 __device__ __forceinline__ int solo_class(const KArgs& a, const QInfo& qi) {
   const uint32_t len = static_cast<uint32_t>(qi.row_len);
   const uint32_t words = qi.kind ? len : (len + 31) / 32;
-  if (a.solo_arcs == 0u || words > kSoloWords[2]) return 0;
-  const int32_t lo = qi.row_start - qi.delta;
-  const int32_t s = a.offsets[lo], e = a.offsets[lo + qi.row_len];
-  if (s < 0 || e < s || static_cast<uint32_t>(e) > a.m || static_cast<uint32_t>(e - s) > a.solo_arcs) return 0;
+  if (a.solo == 0u || words > kSoloWords[2]) return 0;
+  const uint32_t limit = a.ctl->solo_limit;
+  uint32_t arcs;
+  if (limit == 0u || !query_arcs(a, qi, &arcs) || arcs > limit) return 0;
   return (qi.kind ? 3 : 1) + (words > kSoloWords[1] ? 1 : 0);
+}
+
+// One workgroup gets through 0.6 to 1.2 G arcs/s, the chip through about 200
+// when it has several for every CU: batches of 2^28 arcs and more take their
+// small queries that way (2,048 queries over 2.6 G arcs: the 1,024 BFS queries
+// 20 -> 6.8 ms), except those with more than a 256th of the batch, which would
+// hold it up.  Smaller batches are done sooner in the shared worklist (28
+// queries, 8 M arcs: 1.1 against 2.5 ms).  The arcs are those of the batch's
+// instances (one pass over the query table, 1,024 threads); the caller's bound
+// on them only says whether it is worth asking.
+constexpr unsigned long long kSoloBatch = 1ull << 28;
+__global__ __launch_bounds__(1024) void k_solo_limit(KArgs a) {
+  __shared__ unsigned long long total;
+  if (threadIdx.x == 0) total = 0ull;
+  __syncthreads();
+  unsigned long long sum = 0;
+  for (uint32_t q = threadIdx.x; q < a.num_queries; q += 1024) {
+    uint32_t arcs;
+    if (query_arcs(a, a.qtab[q], &arcs)) sum += arcs;
+  }
+  atomicAdd(&total, sum);
+  __syncthreads();
+  if (threadIdx.x == 0)
+    a.ctl->solo_limit =
+        total < kSoloBatch ? 0u : static_cast<uint32_t>(min(total / 256ull, static_cast<unsigned long long>(0x7fffffffu)));
 }
 
 __device__ __forceinline__ void fill_chunk(const KArgs& a, const QInfo& qi, uint32_t c0) {

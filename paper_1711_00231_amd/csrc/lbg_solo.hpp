@@ -14,7 +14,7 @@
 // What bounds it: the latency of a level's dependent reads (list, offsets,
 // arcs) on one CU, and the arcs themselves, read in order.  So a query on an
 // instance with many more arcs than the others' share would run long after
-// the rest is done: those with more than KArgs::solo_arcs stay in the shared
+// the rest is done: those with more than Ctl::solo_limit stay in the shared
 // worklist.
 #pragma once
 
@@ -238,6 +238,7 @@ __global__ __launch_bounds__(kSoloBlock) void k_solo(KArgs a) {
   constexpr bool kSssp = kClass >= 3;
   constexpr uint32_t kWords = kSoloWords[kClass];
   __shared__ SoloLds<kSssp, kWords> sm;
+  if (a.ctl->solo_limit == 0u) return;
   for (;;) {
     if (threadIdx.x == 0) sm.query = static_cast<uint32_t>(atomicAdd(&a.ctl->xstat[kClass][12], 1ull));
     __syncthreads();

@@ -82,3 +82,41 @@ def test_solo_rejects_arc_leaving_instance():
         with pytest.raises(lbg.LbgError) as ei:
             lbg.batch_solve(dg, [(0, 0, 3, kind), (3, 3, 6, kind)], total_arcs=BOUND)
         assert ei.value.code == lbg.EOVERFLOW
+
+
+@pytest.mark.parametrize("wide", [0, 1])
+def test_solo_batches_of_as_many_arcs(wide):
+    """The same instances in batches whose queries hold 2^28 arcs and more, by
+    repetition.  One workgroup's atomics are in LDS and not counted: a BFS batch
+    without the large instance counts none."""
+    lbg.set_addressing(wide)
+    gs = _instances()
+    u, nb, _ = graphgen.pack(gs)
+    dg = lbg.DeviceGraph.from_numpy(u.offsets, u.cols, u.weights)
+    for kinds, largest in (((lbg.KIND_BFS, lbg.KIND_SSSP), 1 << 30), ((lbg.KIND_BFS,), 1 << 20)):
+        once, expect, arcs = [], [], 0
+        for i, g in enumerate(gs):
+            for kind in kinds if g.m <= largest else ():
+                once.append((int(nb[i] + g.n - 1), int(nb[i]), int(nb[i + 1]), kind))
+                expect.append(O.bfs(g.offsets, g.cols, g.n - 1) if kind == lbg.KIND_BFS
+                              else O.dijkstra(g.offsets, g.cols, g.weights, g.n - 1).view(np.int32))
+                arcs += g.m
+        exp = torch.from_numpy(np.concatenate(expect)).cuda()
+        times = -(-BOUND // arcs)
+        out, st = lbg.batch_solve(dg, once * times, stats=True)
+        assert bool((out.view(times, -1) == exp).all())
+        assert (st["atomics"] == 0) == (len(kinds) == 1)
+
+
+@pytest.mark.parametrize("bound", [BOUND, (1 << 32) - 1])
+def test_a_loose_bound_keeps_the_route(bound):
+    """The bound sizes the workspace; a batch of few arcs is solved in the
+    shared worklist whatever it is."""
+    gs = [graphgen.uniform(n=n, k=8, salt=n) for n in (3000, 20000, 100000)]
+    u, nb, _ = graphgen.pack(gs)
+    dg = lbg.DeviceGraph.from_numpy(u.offsets, u.cols, u.weights)
+    queries = [(int(nb[i]), int(nb[i]), int(nb[i + 1]), kind) for i in range(3) for kind in (lbg.KIND_BFS, lbg.KIND_SSSP)]
+    ref, s0 = lbg.batch_solve(dg, queries, stats=True)
+    got, st = lbg.batch_solve(dg, queries, total_arcs=bound, stats=True)
+    assert torch.equal(got, ref)
+    assert st["atomics"] > s0["atomics"] // 2 > 0  # one workgroup's atomics are in LDS and not counted
