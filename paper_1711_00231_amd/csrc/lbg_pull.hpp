@@ -14,13 +14,14 @@
 //  * k_init samples arcs between low-degree nodes; one without its reverse
 //    settles the matter (directed graphs of low degree stop here);
 //  * k_bfs_sym then reads every arc once, in order (a streaming pass, 4 bytes
-//    per arc), and compares the products of lbg_sym.hpp at three random points:
-//    a symmetric graph always passes, any other one with a chance below 2^-60,
-//    and then it is expanded as before.
+//    per arc), and compares the products of lbg_sym.hpp at two random points.
+//    A graph that does not pass is expanded as before.
 // R-MAT 22: 0.98 -> 0.48 ms for the solve, of which the pass over 513 MB of
 // arcs takes 174 us (2.9 TB/s) and the two pulled levels 112 + 38 us, where
 // expansion and compaction took 265 + 582 us; R-MAT 24: 4.28 -> 1.38 ms.
 #pragma once
+
+#include <type_traits>
 
 #include "lbg_kernels.hpp"
 #include "lbg_sym.hpp"
@@ -38,7 +39,6 @@ constexpr uint32_t kSymTile = 64 * kSymItems;
 // the use of `sums`: two calls need a barrier in between.
 __device__ __forceinline__ void sym_block(SymProducts& s, double (&sums)[kWaves][2 * kSymPoints]) {
   const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  sym_finish(s);
   double up[kSymPoints], down[kSymPoints];
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) {
@@ -77,7 +77,7 @@ __device__ __forceinline__ void sym_block(SymProducts& s, double (&sums)[kWaves]
 template <bool kNarrow>
 __global__ __launch_bounds__(kBlock) void k_bfs_sym(KArgs a, uint32_t launch) {
   __shared__ unsigned long long flag_s[kWaves][kSymItems];
-  __shared__ uint32_t node_s[kWaves][kSymTile];
+  __shared__ uint32_t node_s[kWaves][kSymTile + 1];
   __shared__ double sums[kWaves][2 * kSymPoints];
   __shared__ uint32_t last;
   const uint32_t L = level_of(a, launch);
@@ -88,15 +88,16 @@ __global__ __launch_bounds__(kBlock) void k_bfs_sym(KArgs a, uint32_t launch) {
   if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl->sym_run = launch + 1u;
   const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   unsigned long long* flag = flag_s[wid];
-  uint32_t* start = node_s[wid];
+  uint32_t* nodes = node_s[wid];
   // whole tiles per wavefront
   const unsigned long long tiles = (static_cast<unsigned long long>(a.m) + kSymTile - 1) / kSymTile;
   const unsigned long long W = static_cast<unsigned long long>(gridDim.x) * kWaves;
   const unsigned long long g = static_cast<unsigned long long>(blockIdx.x) * kWaves + wid;
   const uint32_t t0 = static_cast<uint32_t>(tiles * g / W), t1 = static_cast<uint32_t>(tiles * (g + 1) / W);
   SymProducts prod;
+  int32_t swapped = 0;
   sym_start(prod);
-  const double x[kSymPoints] = {a.sym_x[0], a.sym_x[1], a.sym_x[2]};
+  const double x[kSymPoints] = {a.sym_x[0], a.sym_x[1]};
   bool bad = false;
   if (t0 < t1) {
     // the node that holds the range's first arc: the last with offset <= e
@@ -113,49 +114,74 @@ __global__ __launch_bounds__(kBlock) void k_bfs_sym(KArgs a, uint32_t launch) {
         hi = min(hi, lo + step);
       }
     }
-    uint32_t cur = lo, next = lo + 1;  // node of the last slot so far, next node to place
+    uint32_t next = lo + 1;  // next node to place
+    if (lane == 0) nodes[0] = lo;
     for (uint32_t t = t0; t < t1; ++t) {
       const uint32_t e0 = t * kSymTile, e1 = min(e0 + kSymTile, a.m);
       if (lane < kSymItems) flag[lane] = 0ull;
       wave_sync();
-      // starts of the nodes with arcs in this tile
+      // the nodes that start in this tile, in order, behind the one that holds
+      // its first arc unless another starts there
+      uint32_t found = 0;
       for (;;) {
         const uint32_t i = next + lane;
         const uint32_t s = i < a.n ? static_cast<uint32_t>(*at<kNarrow>(a.offsets, i)) : 0xffffffffu;
         const uint32_t f = i < a.n ? static_cast<uint32_t>(*at<kNarrow>(a.offsets, i + 1)) : 0xffffffffu;
         const bool in = s < e1;  // offsets do not decrease: a prefix of the lanes
-        if (in && s >= e0 && f > s) {
+        const bool put = in && s >= e0 && f > s;
+        const uint64_t puts = __ballot(put);
+        if (put) {
           atomicOr(&flag[(s - e0) >> 6], 1ull << ((s - e0) & 63));
-          start[s - e0] = i;
+          const uint32_t k = found + lane_rank(puts);
+          if (k < kSymTile) nodes[1 + k] = i;  // as many as there are slots, at most
         }
-        const uint64_t mask = __ballot(in);
-        const uint32_t k = static_cast<uint32_t>(__popcll(mask));
+        found += static_cast<uint32_t>(__popcll(puts));
+        const uint32_t k = static_cast<uint32_t>(__popcll(__ballot(in)));
         next += k;
         if (k < 64u) break;
       }
       wave_sync();
-      int32_t vv[kSymItems];
+      const unsigned long long words = flag[lane % kSymItems];
+      uint32_t before = 0;  // nodes that start before the word
+      // all but the last tile are full, and need no bounds
+      auto arcs = [&](auto full) {
+        constexpr bool kFull = decltype(full)::value;
+        const int32_t* cols = at<kNarrow>(a.cols, e0 + lane);
+        uint32_t uu[kSymItems], vv[kSymItems];
 #pragma unroll
-      for (uint32_t r = 0; r < kSymItems; ++r) {
-        const uint32_t e = e0 + r * 64 + lane;
-        vv[r] = e < e1 ? *at<kNarrow>(a.cols, e) : -1;
-      }
+        for (uint32_t r = 0; r < kSymItems; ++r)
+          vv[r] = kFull || e0 + r * 64 + lane < e1 ? static_cast<uint32_t>(cols[r * 64]) : 0u;
 #pragma unroll
-      for (uint32_t r = 0; r < kSymItems; ++r) {
-        const unsigned long long word = flag[r];  // wavefront-uniform
-        const unsigned long long upto = word & (~0ull >> (63 - lane));
-        const uint32_t u = upto ? start[r * 64 + 63 - __builtin_clzll(upto)] : cur;
-        if (word) cur = start[r * 64 + 63 - __builtin_clzll(word)];
-        const uint32_t v = static_cast<uint32_t>(vv[r]);
-        if (e0 + r * 64 + lane < e1) {
-          if (v >= a.n) bad = true;
-          else if (v != u) sym_arc(prod, u, v, x);
+        for (uint32_t r = 0; r < kSymItems; ++r) {
+          const uint32_t w0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(words), r));
+          const uint32_t w1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(words >> 32), r));
+          // starts up to this lane's slot: the word's first bit, and those
+          // below the lane among the others
+          uu[r] = nodes[__builtin_amdgcn_mbcnt_hi(w1 >> 1, __builtin_amdgcn_mbcnt_lo(w0 >> 1 | w1 << 31,
+                                                                                    before + (w0 & 1u)))];
+          before += static_cast<uint32_t>(__popc(w0) + __popc(w1));
         }
-      }
+#pragma unroll
+        for (uint32_t r = 0; r < kSymItems; ++r) {
+          const uint32_t u = uu[r], v = vv[r];
+          const bool in = kFull || e0 + r * 64 + lane < e1;
+          bad = bad || (in && v >= a.n);  // its product is of no use then
+          if (in && u != v) {
+            const int32_t side = static_cast<int32_t>(v - u);  // negative: v < u
+            sym_take(prod, (side ^ swapped) < 0, min(u, v), max(u, v), x);
+            swapped = side;
+          }
+        }
+      };
+      if (e1 - e0 == kSymTile) arcs(std::true_type{});
+      else arcs(std::false_type{});
+      const uint32_t cur = nodes[before];
       wave_sync();
+      if (lane == 0) nodes[0] = cur;
     }
   }
   if (__any(bad) && lane == 0) a.ctl->sym_no = 1u;
+  sym_finish(prod, swapped < 0);
   sym_block(prod, sums);
   unsigned long long* const part = reinterpret_cast<unsigned long long*>(a.fr[1].node);
   if (threadIdx.x == 0) {

@@ -2,17 +2,21 @@
 //
 // A graph is symmetric when the pairs {u, v} of its arcs u -> v with u < v
 // are, as a multiset, those of its arcs with u > v (self-loops are their own
-// reverse).  Two multisets of numbers e in a field are equal exactly when the
-// polynomials prod (x - e) are, and two different ones of degree at most m
-// agree at no more than m points of the field: so both products are formed at
-// a point x drawn at random, in the field of p = 2^51 - 129 elements, for
-// e = 2^25 min(u, v) + max(u, v), which tells all pairs of a graph of at most
-// 2^25 nodes apart.  A symmetric graph always passes.  Any other one, however
-// its one-way arcs are arranged, passes with a chance of at most m / p over
-// the draw, and the three points that are used are drawn independently: at
-// most (m / p)^3, below 2^-60 for every m < 2^31 (2^-72 for the 2^27 arcs of
-// R-MAT scale 22).  (Equality of multisets by products at a random point:
-// Lipton 1989; Blum et al., Checking the correctness of memories, 1991.)
+// reverse).  So the products of x - e over the ones and over the others are
+// formed at points x drawn at random, in the field of p = 2^51 - 129 elements,
+// for e = 2^25 min(u, v) + max(u, v), which tells all pairs of a graph of at
+// most 2^25 nodes apart (equality of multisets by products at a random point:
+// Lipton 1989; Blum et al., Checking the correctness of memories, 1991).  The
+// graph passes when the products are equal, and not zero, at every point.  A
+// symmetric one does unless a point happens to be one of its e, which costs
+// the pull levels of one solve.  Take any other, and k the larger of the
+// numbers of arcs that its two sides hold beyond each other: without the
+// factors they share, which are not zero, the products are two different
+// monic polynomials in x of degree at most k, equal at no more than k points.
+// So it passes with a chance of at most (k / p)^2 over the two points, which
+// are drawn independently: below 2^-96 for up to eight one-way arcs, however
+// they are arranged, below 2^-48 if all of 2^27 arcs are one-way (where a
+// sample of a few arcs has long found one, see sym_sample).
 //
 // The products are formed in double precision, where a multiply-add of 53
 // bits is as fast as one of 24 and four times as fast as a 32-bit integer
@@ -30,7 +34,7 @@ namespace lbg {
 
 constexpr unsigned long long kSymP = (1ull << 51) - 129;  // a prime
 constexpr uint32_t kSymNodes = 1u << 25;                  // node ids are below
-constexpr int kSymPoints = 3;
+constexpr int kSymPoints = 2;
 
 // a * b mod p, up to a multiple of p: for integers |a| < 2 p and |b| < p, an
 // integer below 2 p in size again.  h + l is the exact product and q its
@@ -51,52 +55,48 @@ __device__ __forceinline__ double sym_small(double a) {
   return __builtin_fma(-__builtin_rint(a * inv), p, a);
 }
 
-// 2^52 + e of a pair: e is below 2^50, so these are its bits.
-__device__ __forceinline__ double sym_pair(uint32_t u, uint32_t v) {
-  const uint32_t a = u < v ? u : v, b = u < v ? v : u;
-  const unsigned long long bits = 0x4330000000000000ull | (static_cast<unsigned long long>(a) << 25) | b;
-  return __builtin_bit_cast(double, bits);
+// 2^52 + e of a pair, a < b: e is below 2^50, so these are its bits.
+__device__ __forceinline__ double sym_pair(uint32_t a, uint32_t b) {
+  const uint32_t hi = 0x43300000u | (a >> 7), lo = (a << 25) | b;
+  return __builtin_bit_cast(double, (static_cast<unsigned long long>(hi) << 32) | lo);
 }
 
-// The products at the points.  up: over arcs u -> v with u < v, down: over the
-// others; `swapped` says which is which, so that an arc needs one
-// multiplication whatever its direction.
+// The products at the points: up over arcs u -> v with u < v, down over those
+// with u > v, or (while `swapped`) the other way round, so that an arc takes
+// one multiplication and a choice, whatever its direction.
 struct SymProducts {
   double up[kSymPoints], down[kSymPoints];
-  bool swapped;
 };
 
 __device__ __forceinline__ void sym_start(SymProducts& s) {
 #pragma unroll
   for (int i = 0; i < kSymPoints; ++i) s.up[i] = s.down[i] = 1.0;
-  s.swapped = false;
 }
 
-// Arc u -> v, u != v, both below kSymNodes; x: the points, each an integer in
-// [0, p) plus 2^52 (exact: below 2^53).
-__device__ __forceinline__ void sym_arc(SymProducts& s, uint32_t u, uint32_t v, const double (&x)[kSymPoints]) {
-  const bool down = u > v, swap = down != s.swapped;
-  const double e = sym_pair(u, v);
-  s.swapped = down;
+// Takes in pair a < b; swap: its direction is not the last one's.  x: the
+// points, each an integer in [0, p) plus 2^52 (exact: below 2^53).
+__device__ __forceinline__ void sym_take(SymProducts& s, bool swap, uint32_t a, uint32_t b,
+                                         const double (&x)[kSymPoints]) {
+  const double e = sym_pair(a, b);
 #pragma unroll
   for (int i = 0; i < kSymPoints; ++i) {
     const double now = swap ? s.down[i] : s.up[i];
     s.down[i] = swap ? s.up[i] : s.down[i];
-    s.up[i] = sym_mul(now, x[i] - e);  // |x - e| < p: both terms lie in [0, p)
+    s.up[i] = sym_mul(now, x[i] - e);  // |x - e| < p: both lie in [0, p)
   }
 }
 
-__device__ __forceinline__ void sym_finish(SymProducts& s) {
+// After the last pair.
+__device__ __forceinline__ void sym_finish(SymProducts& s, bool swapped) {
 #pragma unroll
   for (int i = 0; i < kSymPoints; ++i) {
     const double a = s.up[i];
-    s.up[i] = s.swapped ? s.down[i] : a;
-    s.down[i] = s.swapped ? a : s.down[i];
+    s.up[i] = swapped ? s.down[i] : a;
+    s.down[i] = swapped ? a : s.down[i];
   }
-  s.swapped = false;
 }
 
-// Takes in the products of other arcs (sym_finish both).
+// Takes in the products of other arcs.
 __device__ __forceinline__ void sym_join(SymProducts& s, const double (&up)[kSymPoints],
                                          const double (&down)[kSymPoints]) {
 #pragma unroll
@@ -106,9 +106,11 @@ __device__ __forceinline__ void sym_join(SymProducts& s, const double (&up)[kSym
   }
 }
 
-// Whether the two products of a point are the same element.
+// Whether the two products of a point are one element, and not zero.
 __device__ __forceinline__ bool sym_equal(double a, double b) {
-  return (static_cast<long long>(a) - static_cast<long long>(b)) % static_cast<long long>(kSymP) == 0;
+  constexpr long long p = static_cast<long long>(kSymP);
+  const long long x = static_cast<long long>(a), y = static_cast<long long>(b);
+  return (x - y) % p == 0 && x % p != 0;
 }
 
 }  // namespace lbg

@@ -39,6 +39,7 @@
 #define __hip_atomic_fetch_or(p, v, order, scope) __atomic_fetch_or(p, v, order)
 #define __builtin_amdgcn_fence(order, scope)
 #define __builtin_amdgcn_wave_barrier() emu::wave_exchange('b', 0)
+#define __builtin_amdgcn_readlane(v, l) __shfl(v, l, 64)
 #define __builtin_amdgcn_s_sleep(n) emu::spin()
 #define __builtin_amdgcn_mbcnt_lo(m, c) ((c) + __builtin_popcount((m) & emu::below_lo()))
 #define __builtin_amdgcn_mbcnt_hi(m, c) ((c) + __builtin_popcount((m) & emu::below_hi()))

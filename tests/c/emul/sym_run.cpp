@@ -10,7 +10,7 @@ using namespace lbg;
 int main(int argc, char** argv) {
   FILE* f = fopen(argv[1], "rb");
   int32_t nm[2];
-  if (argc < 6 || !f || fread(nm, 4, 2, f) != 2) emu::die("graph");
+  if (argc < 5 || !f || fread(nm, 4, 2, f) != 2) emu::die("graph");
   std::vector<int32_t> offsets(nm[0] + 1), cols(nm[1]);
   if (fread(offsets.data(), 4, offsets.size(), f) != offsets.size() ||
       fread(cols.data(), 4, cols.size(), f) != cols.size())

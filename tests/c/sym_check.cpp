@@ -6,19 +6,30 @@
 
 using namespace lbg;
 
+// The products of the arcs at the points p.
+static SymProducts products(const uint32_t* u, const uint32_t* v, int64_t count, const double (&p)[kSymPoints]) {
+  SymProducts s;
+  sym_start(s);
+  bool swapped = false;
+  for (int64_t k = 0; k < count; ++k) {
+    const bool side = u[k] > v[k];
+    sym_take(s, side != swapped, side ? v[k] : u[k], side ? u[k] : v[k], p);
+    swapped = side;
+  }
+  sym_finish(s, swapped);
+  return s;
+}
+
 extern "C" {
 
 double sc_mul(double a, double b) { return sym_mul(a, b); }
 double sc_small(double a) { return sym_small(a); }
 
-// The products (up, down of each point, as residues) of `count` arcs at the points x[0 .. 2].
+// The products (up, down of each point, as residues) of `count` arcs at the points x[0 .. 1].
 void sc_products(const uint32_t* u, const uint32_t* v, int64_t count, const uint64_t* x, uint64_t* out) {
   double p[kSymPoints];
   for (int i = 0; i < kSymPoints; ++i) p[i] = static_cast<double>((1ull << 52) + x[i]);
-  SymProducts s;
-  sym_start(s);
-  for (int64_t k = 0; k < count; ++k) sym_arc(s, u[k], v[k], p);
-  sym_finish(s);
+  const SymProducts s = products(u, v, count, p);
   const int64_t m = static_cast<int64_t>(kSymP);
   for (int i = 0; i < kSymPoints; ++i) {
     out[2 * i] = static_cast<uint64_t>((static_cast<int64_t>(s.up[i]) % m + m) % m);
@@ -33,10 +44,7 @@ void sc_passes(const uint32_t* u, const uint32_t* v, int64_t count, int64_t draw
   for (int64_t d = 0; d < draws; ++d) {
     double p[kSymPoints];
     for (double& x : p) x = static_cast<double>((1ull << 52) + (rng() >> 13) % kSymP);
-    SymProducts s;
-    sym_start(s);
-    for (int64_t k = 0; k < count; ++k) sym_arc(s, u[k], v[k], p);
-    sym_finish(s);
+    const SymProducts s = products(u, v, count, p);
     int same = 0;
     for (int i = 0; i < kSymPoints; ++i) same += sym_equal(s.up[i], s.down[i]);
     out[0] += same > 0;

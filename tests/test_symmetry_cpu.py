@@ -50,7 +50,7 @@ def test_products_are_exact(lib):
 
 def _products(lib, u, v, x):
     u, v, x = np.array(u, np.uint32), np.array(v, np.uint32), np.array(x, np.uint64)
-    out = np.zeros(6, np.uint64)
+    out = np.zeros(4, np.uint64)
     lib.sc_products(u.ctypes.data, v.ctypes.data, u.size, x.ctypes.data, out.ctypes.data)
     return [int(y) for y in out]
 
@@ -64,7 +64,7 @@ def test_products_equal_integers(lib, ids):
         if a != b:
             u.append(a)
             v.append(b)
-    for x in ([0, 1, P - 1], [rng.randrange(P) for _ in range(3)]):
+    for x in ([0, 1], [P - 1, 5], [rng.randrange(P) for _ in range(2)]):
         exp = []
         for t in x:
             for down in (False, True):
@@ -77,7 +77,7 @@ def test_products_equal_integers(lib, ids):
     # and the other way round, in another order: symmetric
     both = list(zip(u + v, v + u))
     rng.shuffle(both)
-    out = _products(lib, [a for a, _ in both], [b for _, b in both], [rng.randrange(P) for _ in range(3)])
+    out = _products(lib, [a for a, _ in both], [b for _, b in both], [rng.randrange(P) for _ in range(2)])
     assert out[::2] == out[1::2]
 
 
@@ -124,7 +124,7 @@ def kernel(tmp_path_factory):
             np.asarray(g.offsets, dtype=np.int32).tofile(f)
             np.asarray(g.cols, dtype=np.int32).tofile(f)
         rng = random.Random(blocks)
-        r = subprocess.run([exe, str(d / "g"), str(blocks)] + [str(rng.randrange(P)) for _ in range(3)],
+        r = subprocess.run([exe, str(d / "g"), str(blocks)] + [str(rng.randrange(P)) for _ in range(2)],
                            capture_output=True, text=True, timeout=120)
         assert r.returncode == 0, r.stderr[-300:]
         return r.stdout.strip() == "1"
