@@ -396,15 +396,21 @@ __device__ __forceinline__ void far_raise(uint32_t delta0, uint32_t most, uint32
 // A sample of arcs u -> v for symmetry (the last workgroup of k_init, while
 // the others clear the state; see lbg_pull.hpp): a thread takes a node, the
 // one of its first 8 neighbours with the fewest arcs, and looks for the way
-// back among those, if they are at most 32.  Nodes without such a neighbour
-// say nothing.
+// back among those, if they are at most 32.  Where few threads find such a
+// neighbour (dense graphs), each wavefront looks through the two shortest
+// longer lists, of at most 4096 arcs, together.  Nodes without either say
+// nothing.  (A digraph of 30,000 nodes and 10^8 arcs, whose lists are all
+// longer than 32: without the second part every solve went over all arcs,
+// 0.49 ms against 0.41 without pull levels.)
+constexpr uint32_t kSampleAlone = 32, kSampleLong = 4096;
 __device__ __forceinline__ void sym_sample(const KArgs& a) {
   __shared__ uint32_t no;
   if (threadIdx.x == 0) no = 0u;
   __syncthreads();
-  const uint32_t u = (threadIdx.x * 0x9e3779b1u + static_cast<uint32_t>(__builtin_bit_cast(unsigned long long, a.sym_x[0]) >> 8)) % a.n;
+  const uint32_t u =
+      (threadIdx.x * 0x9e3779b1u + static_cast<uint32_t>(__builtin_bit_cast(unsigned long long, a.sym_x[0]) >> 8)) % a.n;
   const uint32_t s = static_cast<uint32_t>(a.offsets[u]), e = static_cast<uint32_t>(a.offsets[u + 1]);
-  uint32_t vs = 0, ve = 0, best = 33;
+  uint32_t vs = 0, ve = 0, best = kSampleLong + 1;
   if (s < e && e <= a.m) {
     uint32_t v[8];
 #pragma unroll
@@ -420,13 +426,33 @@ __device__ __forceinline__ void sym_sample(const KArgs& a) {
       }
     }
   }
-  if (best <= 32u) {
+  if (best <= kSampleAlone) {
     bool back = false;
     for (uint32_t p = vs; p < ve && !back; p += 8) {
 #pragma unroll
       for (uint32_t k = 0; k < 8; ++k) back = back || (p + k < ve && static_cast<uint32_t>(a.cols[p + k]) == u);
     }
     if (!back) no = 1u;
+  }
+  if (__syncthreads_count(best <= kSampleAlone) < kBlock / 4) {
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t len = best > kSampleAlone ? best : kSampleLong + 1;
+    for (int r = 0; r < 2; ++r) {
+      const uint32_t key = static_cast<uint32_t>(-wave_max(-static_cast<int32_t>(len << 6 | lane)));
+      if (key >> 6 > kSampleLong) break;
+      const int who = static_cast<int>(key & 63);
+      const uint32_t wu = __shfl(u, who, 64), we = __shfl(ve, who, 64);
+      bool back = false;
+      for (uint32_t p = __shfl(vs, who, 64); p < we && !__any(back); p += 64 * 8) {
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) {
+          const uint32_t i = p + k * 64 + lane;
+          back = back || (i < we && static_cast<uint32_t>(a.cols[i]) == wu);
+        }
+      }
+      if (!__any(back)) no = 1u;
+      if (static_cast<int>(lane) == who) len = kSampleLong + 1;
+    }
   }
   __syncthreads();
   if (threadIdx.x == 0) a.ctl->sym_no = no;

@@ -147,3 +147,15 @@ def test_kernel(kernel, blocks, half):
     assert not kernel(n, s[drop], d[drop], blocks)
     one_way = STRUCTURED[4]
     assert not kernel(n, np.append(s, [a for a, _ in one_way]), np.append(d, [b for _, b in one_way]), blocks)
+
+
+@pytest.mark.parametrize("degree", [4, 31, 33, 100, 600])
+def test_sample(kernel, degree):
+    """The sample turns down a digraph of any degree up to its longest lists,
+    and no symmetric graph."""
+    rng = np.random.default_rng(degree)
+    n = 5000
+    u, v = np.repeat(np.arange(n), degree), rng.integers(0, n, n * degree)
+    assert not kernel(n, u, v, 0)
+    u, v = u[: u.size // 2], v[: v.size // 2]
+    assert kernel(n, np.concatenate([u, v]), np.concatenate([v, u]), 0)
