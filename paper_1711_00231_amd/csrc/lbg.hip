@@ -296,6 +296,11 @@ class TeamPlace {
 // enqueues that many, so a typical solve needs one read-back and few empty
 // launches.
 thread_local uint32_t g_big_hint[2] = {0u, 0u};
+// Whether this thread's previous SSSP solve that might have deferred nodes did
+// (near_far_init decides on the device; 0: there was none): the next one's
+// first submission holds the one-level launches for the same.
+enum { kFarUnknown = 0, kFarDid, kFarDidNot };
+thread_local int g_far_hint = kFarUnknown;
 // Likewise, levels of the thread's previous BFS / SSSP solve by another
 // strategy: its first submission holds that many and one more (an empty level
 // of hierarchical processing with 256-arc windows is 640 launches: R-MAT 22
@@ -446,7 +451,7 @@ int check_common(const Problem& P) {
   return LBG_OK;
 }
 
-// Whether an SSSP solve defers nodes beyond a threshold (near_far_init).  Not
+// Whether an SSSP solve may defer nodes beyond a threshold (near_far_init).  Not
 // above 16 arcs per node: skewed graphs lose more to the extra iterations than
 // they save (R-MAT, thresholds from a quarter of a mean list's weight to all
 // of it: scale 18, 0.48 -> 0.60 - 0.68 ms; scale 22 ordered, 2.50 -> 2.66 -
@@ -638,6 +643,7 @@ int solve(const Problem& P) {
   }
   HIP_TRY(hipGetLastError());
 
+  bool defer = a.far && g_far_hint != kFarDidNot;  // near-far one-level kernels (as expected, then as it is)
   bool merge = true;  // the next launch is the first after a team launch (or of the solve)
   uint32_t nth = 0;   // one-level launches since then
   auto launch = [&](uint32_t L) {
@@ -661,7 +667,7 @@ int solve(const Problem& P) {
           else hipLaunchKernelGGL((lbg::k_expand_balanced<true, false, false, false, true>), dim3(GR.bal_s[sv][nw]), dim3(lbg::kBlock), 0, st, a, L);
           break;
         default:
-          if (a.far) {
+          if (defer) {
             const dim3 fg(GR.far[packed ? 1 : 0][nw]), fb(lbg::kBlock);
             if (packed) {
               if (narrow) hipLaunchKernelGGL((lbg::k_expand_balanced<true, true, false, true, false, true>), fg, fb, 0, st, a, L);
@@ -756,6 +762,9 @@ int solve(const Problem& P) {
   const int64_t most_big = !small_ok ? 64 : !P.is_sssp ? P.m / (int64_t{team_limit} + 1)
                            : P.m > (P.m > 16 * static_cast<int64_t>(P.n) ? int64_t{4} * team_limit : kSmallGraph) ? 64 : 0;
   if (small_ok && !P.is_sssp) batch = static_cast<uint32_t>(std::clamp<int64_t>(most_big, 1, batch));
+  // levels that outgrow the team are expected, and which kernels will run them
+  const bool expect_big = most_big > 0 && (!a.far || g_far_hint != kFarUnknown);
+  bool counted = false;  // g_big_hint is this solve's
   bool first = true, alone = false;
   uint64_t ef = 1;
   size_t nev = 0;
@@ -822,9 +831,9 @@ int solve(const Problem& P) {
       a.min_arcs = team_limit;
       if (ef <= team_limit && (rc = team()) != LBG_OK) return rc;
       // near-far solves come back to big levels after each split
-      if (first ? most_big > 0 : ef > team_limit) {
-        for (int i = 0; i < (a.far ? 3 : 1); ++i) {
-          if ((rc = one_level(a.far ? 6 : batch)) != LBG_OK) return rc;
+      if (first ? expect_big : ef > team_limit) {
+        for (int i = 0; i < (defer ? 3 : 1); ++i) {
+          if ((rc = one_level(defer ? 6 : batch)) != LBG_OK) return rc;
           if ((rc = team()) != LBG_OK) return rc;
         }
       }
@@ -842,11 +851,19 @@ int solve(const Problem& P) {
     if (sl)  // the mixed list's tail (ctr) plus the 8 slice tails
       for (int x = 0; x < lbg::kXcds; ++x) ef += static_cast<uint32_t>(host->xstat[x][4 + L % 3]);
     if (a.team) {  // which of the submission's launches had work
-      if (first && ones) g_big_hint[kind] = 1u + static_cast<uint32_t>(__builtin_popcountll(host->worked & ones));
+      if (ones && !defer && !alone && !counted) {
+        g_big_hint[kind] = 1u + static_cast<uint32_t>(__builtin_popcountll(host->worked & ones));
+        counted = true;
+      }
       for (size_t j = 0; profiling && j < g_event_level.size(); ++j) {
         const int64_t q = g_event_level[j];
         if (q >= k_first) g_event_level[j] = (host->worked >> (q & 63)) & 1ull ? 0 : -2;
       }
+    }
+    if (a.far && first) {
+      defer = host->plain == 0u;
+      g_far_hint = defer ? kFarDid : kFarDidNot;
+      if (!defer) a.far = nullptr;
     }
     // near-far: done once a split has found the far set empty
     if (ef == 0u && (!a.far || (host->split_at == L && host->far_seen != L))) break;

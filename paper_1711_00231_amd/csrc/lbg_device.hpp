@@ -70,7 +70,7 @@ struct Ctl {
   unsigned int sym_run;       // BFS: 1 + the launch that went over the arcs (k_bfs_sym), 0: none did
   unsigned int solo_levels;   // batches: most levels of a query solved by one workgroup
   unsigned int solo_limit;    // batches: arcs of the largest instance whose queries one workgroup may solve
-  unsigned int pad1;
+  unsigned int plain;         // near-far SSSP: 1 when nothing is deferred (near_far_init)
   // [x][0] updates, [x][1] global atomics issued; [x][2], [x][3] the same for
   // levels run by the small-frontier kernel; [x][4 + L % 3] the packed tail
   // (nodes << 32 | edges) of slice x's worklist of level L (destination-

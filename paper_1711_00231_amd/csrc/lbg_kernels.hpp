@@ -339,27 +339,58 @@ __device__ __forceinline__ void init_state(const KArgs& a, int32_t src, uint32_t
 // 3.66 / 30.  While even the largest level of a step is a fraction of what
 // the chip takes in one round of latency the step doubles (the grid without
 // shortcuts: 4587 iterations at 4 x, 3560 with doubling).
+//
+// What it saves is the work of nodes reached over few heavy arcs before many
+// light ones.  Where the weights hardly differ there are none, and the extra
+// iterations only cost: decided by the spread of a sample of the weights
+// (standard deviation / mean; 0.33 for weights 1 - 2, 0.45 for 1 - 4, 0.52 for
+// 1 - 10, 0.58 for wide ranges), deferring against not, in ms.  Uniform graph
+// of 10^6 nodes and 8 arcs per node: equal 0.54 / 0.38, 50 - 100 0.63 / 0.44,
+// 1 - 4 0.72 / 0.62, 1 - 10 0.78 / 0.86, 1 - 100 1.00 / 1.21.  Grid of 1500 x
+// 1500, 3.6 arcs per node: 1 - 2 1.03 / 1.00, 1 - 4 1.17 / 1.27.  And graphs of
+// few arcs per node lose as the dense ones do (solve() in lbg.hip) when most
+// of their nodes have next to none: directed R-MAT of 2^21 nodes, 8 arcs per
+// node, 1.05 / 0.93 ms (half of its nodes have less than a 20th of the mean;
+// a power-law tail over nodes of ordinary degree, 10^6 nodes, gains: 1.08 /
+// 1.11 to 1.17 / 1.63).
+constexpr double kFarSpread = 0.4, kFarSpreadDense = 0.485;  // the second from kFarDense arcs per node on
+constexpr uint32_t kFarDense = 6;
 constexpr uint32_t kFarIdle = 16384;  // arcs of a level that latency hides
 constexpr uint32_t kFarSample = 4096;
 
-// One workgroup: the first threshold from a sample of the weights, then the
-// other words of the team's control block.
+// One workgroup: whether to defer and the first threshold, from samples of the
+// weights and the out-degrees, then the other words of the team's control
+// block.
 __device__ __forceinline__ void near_far_init(const KArgs& a) {
-  __shared__ unsigned long long sum;
-  if (threadIdx.x == 0) sum = 0ull;
-  __syncthreads();
-  unsigned long long x = 0;
+  constexpr int kN = 3;
+  __shared__ double red[kN][kBlock];  // weights, their squares, nodes below a quarter of the mean degree
+  double x[kN] = {0.0, 0.0, 0.0};
   for (uint32_t k = threadIdx.x; k < kFarSample; k += kBlock) {
     const uint32_t e = static_cast<uint32_t>(static_cast<unsigned long long>(k) * a.m / kFarSample);
-    x += a.arcs ? a.arcs[e] & ((1u << a.wbits) - 1u) : a.weights[e];
+    const double w = static_cast<double>(a.arcs ? a.arcs[e] & ((1u << a.wbits) - 1u) : a.weights[e]);
+    const uint32_t v = static_cast<uint32_t>(static_cast<unsigned long long>(k) * a.n / kFarSample);
+    const double d = static_cast<double>(a.offsets[v + 1]) - static_cast<double>(a.offsets[v]);
+    x[0] += w;
+    x[1] += w * w;
+    x[2] += 4.0 * d * a.n < a.m ? 1.0 : 0.0;
   }
-  atomicAdd(&sum, x);
+  for (int i = 0; i < kN; ++i) red[i][threadIdx.x] = x[i];
   __syncthreads();
+  for (uint32_t h = kBlock / 2; h > 0; h /= 2) {
+    if (threadIdx.x < h)
+      for (int i = 0; i < kN; ++i) red[i][threadIdx.x] += red[i][threadIdx.x + h];
+    __syncthreads();
+  }
   if (threadIdx.x == 0) {
+    const double sum = red[0][0];
+    const double spread = a.m >= static_cast<unsigned long long>(kFarDense) * a.n ? kFarSpreadDense : kFarSpread;
+    const bool narrow = red[1][0] * kFarSample <= (1.0 + spread * spread) * sum * sum;
+    const bool skewed = 2.0 * red[2][0] >= kFarSample;
+    a.ctl->plain = narrow || skewed ? 1u : 0u;
     TeamCtl* t = a.team;
     for (int k = 0; k < 4; ++k) t->join[k] = t->size[k] = 0u;
     t->epoch = 0u;
-    const double step = 16.0 * static_cast<double>(sum) / kFarSample * a.n / a.m;
+    const double step = 16.0 * sum / kFarSample * a.n / a.m;
     t->delta0 = static_cast<uint32_t>(step < 1.0 ? 1.0 : (step > 1e9 ? 1e9 : step));
     t->thr[0] = t->delta[0] = t->delta0;
     t->at[0] = 0u;
@@ -591,7 +622,7 @@ __global__ __launch_bounds__(kBlock) void k_sssp_finish(KArgs a) {
   const unsigned long long c = __hip_atomic_load(&a.ctl->ctr[L % 3], __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
   if (static_cast<uint32_t>(c) != 0u) return;
-  if (a.far && !(a.ctl->split_at == L && a.ctl->far_seen != L)) return;  // the far set may hold nodes
+  if (a.far && a.ctl->plain == 0u && !(a.ctl->split_at == L && a.ctl->far_seen != L)) return;  // the far set may hold nodes
   if (a.sliced) {  // and the 8 slice lists
     for (int x = 0; x < kXcds; ++x)
       if (static_cast<uint32_t>(__hip_atomic_load(&a.ctl->xstat[x][4 + L % 3], __ATOMIC_RELAXED,
@@ -1180,7 +1211,8 @@ __device__ __forceinline__ void balanced_level(const KArgs& a, uint32_t k) {
   const uint32_t L = level_of(a, k);
   if (a.team) {
     const uint32_t Ef = static_cast<uint32_t>(ld_agent(&a.ctl->ctr[L % 3]));
-    const bool idle = Ef <= a.min_arcs && !(Ef == 0u && kFar && a.min_arcs == 0u);
+    const bool idle = (Ef <= a.min_arcs && !(Ef == 0u && kFar && a.min_arcs == 0u)) ||
+                      (kSssp && a.far && kFar != (a.ctl->plain == 0u));  // launched before that was known
     if (blockIdx.x == 0 && threadIdx.x == 0) level_next(a, k, idle ? L : L + 1, !idle);
     if (idle) return;
   }

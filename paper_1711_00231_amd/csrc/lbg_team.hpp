@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
   const uint32_t L0 = level_of(a, launch);
   const unsigned long long c0 = ld_agent(&a.ctl->ctr[L0 % 3]);
   uint32_t nf = static_cast<uint32_t>(c0 >> 32), E = static_cast<uint32_t>(c0);
-  const bool far = kSssp && a.far;
+  const bool far = kSssp && a.far && a.ctl->plain == 0u;
   if ((E == 0u && !far) || E > min(limit, kTeamE) || nf > a.node_cap) {
     // Nothing for a team to do, if nobody has joined one: a workgroup that
     // starts late (other streams hold the CUs) may find the counter as a team

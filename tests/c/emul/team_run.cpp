@@ -6,7 +6,8 @@
 // usage: team_run GRAPH OUT key=value...   (tests/test_team_emulation_cpu.py)
 //   GRAPH  int32 n, m, then n + 1 offsets, m columns, m weights
 //   OUT    int64 error, levels, next, arcs and entries of the next worklist,
-//          team launches, one-level launches with work, then the n results
+//          team launches, one-level launches with work, 1 if nothing was deferred,
+//          then the n results
 //   sssp=0|1 src=.. far=0|1 limit=.. blocks=.. grid=..
 //   extra=K    K more arcs to node 0, weight 0, after the graph's own: the
 //              last node's (their arrays are zero pages)
@@ -140,6 +141,7 @@ int main(int argc, char** argv) {
     a.min_arcs = alone ? 0u : limit;
     if (!alone) team();
     if (get("stop", 0) || opt.count("error")) break;
+    if (a.ctl->plain && step) a.far = nullptr;  // known once a submission has ended
     for (int i = 0; i < 3; ++i) one();
     if (!alone) team();
     if (sssp) emu::launch(2, kBlock, [=] { k_sssp_finish(a); });
@@ -152,11 +154,12 @@ int main(int argc, char** argv) {
     L_prev = L;
   }
   const unsigned long long c = a.ctl->ctr[a.ctl->next % 3];
-  const int64_t head[7] = {a.ctl->error, a.ctl->levels, a.ctl->next, static_cast<uint32_t>(c),
-                           static_cast<int64_t>(c >> 32), seq, ones};
+  const int64_t head[8] = {a.ctl->error, a.ctl->levels, a.ctl->next, static_cast<uint32_t>(c),
+                           static_cast<int64_t>(c >> 32), seq, ones,
+                           a.tblocks && sssp ? a.ctl->plain : 0};
   f = fopen(argv[2], "wb");
   if (!f) emu::die("output");
-  fwrite(head, 8, 7, f);
+  fwrite(head, 8, 8, f);
   fwrite(out, 4, n, f);
   const Frontier& fr = a.fr[a.ctl->next & 1];
   const uint32_t e = static_cast<uint32_t>(std::min<unsigned long long>(c >> 32, n));

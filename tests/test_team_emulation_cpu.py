@@ -42,9 +42,9 @@ def emu(tmp_path_factory):
                            timeout=300)
         assert r.returncode == 0, (r.returncode, r.stderr[-500:])
         raw = open(of, "rb").read()
-        head = np.frombuffer(raw, np.int64, 7)
-        st = dict(zip(("error", "levels", "next", "arcs", "entries", "teams", "ones"), (int(x) for x in head)))
-        rest = np.frombuffer(raw, np.uint32, offset=56)
+        head = np.frombuffer(raw, np.int64, 8)
+        st = dict(zip(("error", "levels", "next", "arcs", "entries", "teams", "ones", "plain"), (int(x) for x in head)))
+        rest = np.frombuffer(raw, np.uint32, offset=64)
         st["worklist"] = rest[g.n:].reshape(2, -1)  # edge prefixes, first arcs
         return rest[: g.n], st
 
@@ -137,3 +137,19 @@ def test_nothing_runs_after_an_error(emu):
         out, st = emu(g, src=5, far=far, blocks=4, error=128, fill=0x5A)
         assert (st["error"], st["levels"], st["next"]) == (128, 0, 0)
         assert st["arcs"] == g.degrees[5]
+
+
+@pytest.mark.parametrize("weights,plain", [((1, 100), 0), ((1, 10), 0), ((1, 4), 1), ((50, 100), 1), ((7, 7), 1), ((0, 0), 1)])
+def test_what_defers_nodes(emu, weights, plain):
+    """Weights that hardly differ, and graphs most of whose nodes have next to
+    no arcs, defer nothing."""
+    g = graphgen.uniform(n=1500, k=8, wlo=weights[0], whi=weights[1], salt=3)
+    got, st = emu(g, src=5, far=1, blocks=4, limit=4000)
+    assert (st["error"], st["plain"]) == (0, plain)
+    assert np.array_equal(got, O.dijkstra(g.offsets, g.cols, g.weights, 5))
+    if weights == (1, 100):
+        arcs = [(v, (3 * v + k) % 1500, 1 + (7 * k) % 100) for v in range(1500) for k in range(900 if v % 100 == 0 else 1)]
+        g = _graph(1500, arcs)
+        got, st = emu(g, src=5, far=1, blocks=4, limit=4000)
+        assert (st["error"], st["plain"]) == (0, 1)
+        assert np.array_equal(got, O.dijkstra(g.offsets, g.cols, g.weights, 5))
