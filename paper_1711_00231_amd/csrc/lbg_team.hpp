@@ -349,15 +349,19 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
   auto spill = [&](bool last) {
     const Frontier out = a.fr[L & 1];
     const uint32_t nb = sm.segn[me], eb = sm.sege[me];
-    for (uint32_t k = tid; k < cnt; k += kTeamBlock) {
-      const uint32_t p = sm.list[cur].pre[k];
-      const int32_t v = kSssp ? sm.list[cur].node[k] : 0;
+    for (uint32_t k0 = 0; k0 < cnt; k0 += kTeamBlock) {  // convergent
+      const uint32_t k = k0 + tid;
+      const bool act = k < cnt;
+      const uint32_t p = act ? sm.list[cur].pre[k] : 0u;
+      const int32_t v = kSssp && act ? sm.list[cur].node[k] : 0, st = act ? sm.list[cur].st[k] : 0;
       if (last) {
         const uint32_t pn = k + 1 < cnt ? sm.list[cur].pre[k + 1] : end;
-        write_entry<kPay, T, kNarrow>(a, out, nb + k, eb + p, v, 0, sm.list[cur].st[k], static_cast<int32_t>(pn - p));
+        write_entry_wave<kPay, T, kNarrow>(a, out, act, nb + k, eb + p, v, st, static_cast<int32_t>(pn - p));
+      } else if (!act) {
+        continue;
       } else if (nb + k < a.node_cap) {
         st_agent(at<kNarrow>(out.eprefix, nb + k), eb + p);
-        st_agent(at<kNarrow>(out.estart, nb + k), sm.list[cur].st[k]);
+        st_agent(at<kNarrow>(out.estart, nb + k), st);
         if (kSssp) st_agent(at<kNarrow>(out.node, nb + k), v);
       } else {
         bad = true;

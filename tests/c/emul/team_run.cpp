@@ -163,6 +163,12 @@ int main(int argc, char** argv) {
   fwrite(out, 4, n, f);
   const Frontier& fr = a.fr[a.ctl->next & 1];
   const uint32_t e = static_cast<uint32_t>(std::min<unsigned long long>(c >> 32, n));
+  // every tile of the next worklist names the entry that holds its first arc
+  const uint32_t T = sssp ? TileCfg<true>::kEdges : TileCfg<false>::kEdges;
+  for (uint32_t t = 0; get("stop", 0) && static_cast<uint64_t>(t) * T < static_cast<uint32_t>(c); ++t) {
+    const uint32_t i = static_cast<uint32_t>(fr.tile_node[t]);
+    if (i >= e || fr.eprefix[i] > t * T || (i + 1 < e && fr.eprefix[i + 1] <= t * T)) emu::die("tile marks");
+  }
   fwrite(fr.eprefix, 4, e, f);
   fwrite(fr.estart, 4, e, f);
   fclose(f);

@@ -153,3 +153,15 @@ def test_what_defers_nodes(emu, weights, plain):
         got, st = emu(g, src=5, far=1, blocks=4, limit=4000)
         assert (st["error"], st["plain"]) == (0, 1)
         assert np.array_equal(got, O.dijkstra(g.offsets, g.cols, g.weights, 5))
+
+
+@pytest.mark.parametrize("sssp", [0, 1])
+def test_tile_marks_of_long_and_short_lists(emu, sssp):
+    """A level that leaves the team: entries of one arc up to many tiles."""
+    degrees = [1, 2, 511, 512, 513, 1024, 4095, 4096, 4097, 8 * 512, 8 * 512 + 1, 9 * 1024, 70 * 1024 + 5, 3, 1]
+    n = 2000
+    arcs = [(1, 10 + i, 1) for i in range(len(degrees))]
+    arcs += [(10 + i, 100 + k % 1800, 1) for i, d in enumerate(degrees) for k in range(d)]
+    g = _graph(n, arcs)
+    _, st = emu(g, sssp=sssp, src=1, limit=1000, blocks=3, stop=1)
+    assert (st["error"], st["arcs"], st["entries"]) == (0, sum(degrees), len(degrees))
