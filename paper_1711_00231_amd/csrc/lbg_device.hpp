@@ -107,7 +107,7 @@ struct TeamCtl {
   uint32_t delta[3];  // the last step of the threshold
   uint32_t most[3];   // arcs of the largest level since the last split
   uint32_t at[2];     // the level that launch number k of a solve finds (k % 2)
-  uint32_t pad;
+  uint32_t level[2];  // BFS: the level a workgroup that ran ahead has reached, before exchange e (e % 2)
   unsigned long long flag[2 * kTeamFew];
 };
 static_assert(sizeof(TeamCtl) <= 128 && sizeof(Ctl) + 128 <= 1280, "fits between the control block and 1280");

@@ -47,6 +47,7 @@ constexpr uint32_t kTeamEager = 16384;
 constexpr uint32_t kTeamOwnBfs = 512, kTeamOwnSssp = 1024;
 constexpr uint32_t kTeamRounds = 16;   // SSSP rounds between exchanges while the frontier is small,
 constexpr uint32_t kTeamCalm = 512;    //   at most so many arcs per workgroup
+constexpr uint32_t kTeamAhead = 1024;  // BFS levels a workgroup runs while it holds the whole frontier
 constexpr unsigned long long kTeamWait = 1000;               // 10 us of the 100 MHz clock
 constexpr unsigned long long kTeamPatience = 1000000000ull;  // 10 s
 
@@ -105,7 +106,7 @@ struct TeamLds {
   uint32_t segn[kTeamMax + 1];  // entries before workgroup q's
   uint32_t sege[kTeamMax + 1];  // arcs before workgroup q's
   unsigned long long flag[kTeamSlots / 64];  // bit s: an entry starts at slot s
-  unsigned long long push;      // (entries << 48) | arcs pushed so far
+  unsigned long long push;      // (entries << 32) | arcs pushed so far
   uint32_t me, size, ok;
   uint32_t found;               // split: this workgroup found nodes in the far set
   uint32_t any_found;           //   or some other one did
@@ -136,6 +137,7 @@ __device__ __forceinline__ bool team_exchange(const KArgs& a, TeamLds<kSssp>& sm
         here = here && (q >= size || static_cast<uint32_t>(v[h] >> 34) == (e & 0x3fffffffu));
       }
       ok = __all(here);
+      if (!ok && spin > 64u) __builtin_amdgcn_s_sleep(2);
       if (!ok && (spin & 1023u) == 0u && wall_clock64() - t0 > kTeamPatience) break;
     }
     uint32_t cn = 0, ce = 0, most = 0;
@@ -186,11 +188,16 @@ __device__ __forceinline__ bool team_exchange(const KArgs& a, TeamLds<kSssp>& sm
 // leaves a workgroup with more than kTeamOwn* arcs and twice the mean (or
 // more than it can hold), the level is written out and cut again.
 //
-// BFS exchanges flags before every level (levels are hop counts).  SSSP runs
-// kTeamRounds rounds between exchanges: distances only fall, so the order of
-// relaxations is free (and L counts exchanges).  Since a node may improve again after a workgroup has
-// expanded it, every improvement is pushed, with its distance, and an entry
-// whose node has a smaller one by then is passed over.
+// BFS exchanges flags before every level (levels are hop counts), except where
+// one workgroup holds the whole frontier: it runs level after level, up to
+// kTeamAhead of them, until it has nothing left or more than kTeamOwnBfs arcs,
+// and leaves the level it has reached for the others (a path of 20,000 nodes:
+// 61 -> 37 ms; 53 with the frontier in one workgroup's LDS and no team).  SSSP
+// runs kTeamRounds rounds between exchanges: distances only fall, so the order
+// of relaxations is free (and L counts exchanges).  Since a node may improve
+// again after a workgroup has expanded it, every improvement is pushed, with
+// its distance, and an entry whose node has a smaller one by then is passed
+// over.
 template <bool kSssp, bool kNarrow, bool kPacked = false>
 __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t launch, uint32_t seq, uint32_t limit,
                                                             uint32_t max_levels) {
@@ -202,10 +209,10 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
   __shared__ uint32_t red[2][kTeamWaves];
   const uint32_t tid = threadIdx.x, lane = tid & 63;
 
-  // an earlier launch of the solve failed: what it left is not to be built on
-  if (ld_agent(&a.ctl->error) != 0u) return;
+  const uint32_t failed = ld_agent(&a.ctl->error);
   const uint32_t L0 = level_of(a, launch);
   const unsigned long long c0 = ld_agent(&a.ctl->ctr[L0 % 3]);
+  if (failed) return;  // in an earlier launch: what it left is not to be built on
   uint32_t nf = static_cast<uint32_t>(c0 >> 32), E = static_cast<uint32_t>(c0);
   const bool far = kSssp && a.far && a.ctl->plain == 0u;
   if ((E == 0u && !far) || E > min(limit, kTeamE) || nf > a.node_cap) {
@@ -249,31 +256,31 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
   unsigned long long tot_f = 0, tot_e = 0;  // this workgroup's share
   bool bad = false, alive = true, done = false;
   uint32_t cur = 0;            // the list of this level
-  uint32_t cnt = 0, arcs = 0;  // its size (arcs: at most 2^32 - 1)
-  uint32_t end = 0;            // its arcs mod 2^32, as pre[] counts them
+  uint32_t cnt = 0, arcs = 0;  // its size
   uint32_t L = L0;
 
   bool staged = E > 0u;                  // the lists are an equal cut of level L: nothing to ask the others
   bool known = false;                    // the others' counts are known
   uint32_t rounds = 1;                   // until the next exchange
+  bool ahead = false;                    // BFS: one workgroup runs ahead,
+  bool leads = false;                    //   this one
   uint32_t part = 0;                     // stage() took an entry whose first arc is another workgroup's
 
   // Adds (per wavefront, convergent) the lanes with `put` to list `to`.  SSSP
   // lists a node once for every improvement, with all of its arcs each time,
-  // so their sum is bounded by no graph size: 4096 entries of less than 2^31
-  // arcs take 43 bits.
+  // so their sum is bounded by no graph size.  An entry counts kMostArcs at
+  // most: with one such the level has more than `limit` and leaves the team,
+  // and the nodes' arcs are looked up again then; 4096 of them are below 2^32.
+  constexpr uint32_t kMostArcs = kTeamE + 1;
   auto put_all = [&](uint32_t to, bool put, int32_t v, int32_t s0, int32_t d, uint32_t du) {
     const uint64_t mask = __ballot(put);
     if (mask == 0) return;
-    const uint32_t x = put ? static_cast<uint32_t>(d) : 0u;
-    const uint32_t inc = wave_incl_scan(x);  // mod 2^32
-    unsigned long long sum = inc;            // lane 63: of the wavefront
-    if (__any(x >> 20)) sum = (static_cast<unsigned long long>(wave_sum(x >> 16)) << 16) + wave_sum(x & 0xffffu);
+    const uint32_t inc = wave_incl_scan(put ? static_cast<uint32_t>(d) : 0u);
     unsigned long long b = 0;
-    if (lane == 63) b = atomicAdd(&sm.push, (static_cast<unsigned long long>(__popcll(mask)) << 48) + sum);
+    if (lane == 63) b = atomicAdd(&sm.push, (static_cast<unsigned long long>(__popcll(mask)) << 32) | inc);
     b = bcast64(b, 63);
     if (put) {
-      const uint32_t k = static_cast<uint32_t>(b >> 48) + lane_rank(mask);
+      const uint32_t k = static_cast<uint32_t>(b >> 32) + lane_rank(mask);
       if (k < kTeamSlots) {
         sm.list[to].pre[k] = static_cast<uint32_t>(b) + inc - static_cast<uint32_t>(d);
         sm.list[to].st[k] = s0;
@@ -291,9 +298,8 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
     __syncthreads();
     const unsigned long long p = sm.push;
     cur ^= 1u;
-    cnt = min(static_cast<uint32_t>(p >> 48), kTeamSlots);
-    end = static_cast<uint32_t>(p);
-    arcs = (p & 0xffff00000000ull) ? 0xffffffffu : end;
+    cnt = min(static_cast<uint32_t>(p >> 32), kTeamSlots);
+    arcs = static_cast<uint32_t>(p);
     __syncthreads();
     if (tid == 0) sm.push = 0ull;
   };
@@ -318,7 +324,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
       i1 = min(i1, i0 + step);
     }
     cnt = 0;
-    arcs = end = hi - lo;
+    arcs = hi - lo;
     part = lo < hi && ld_agent(at<kNarrow>(f.eprefix, i0)) < lo ? 1u : 0u;
     if (lo < hi) {
       for (uint32_t k0 = 0;; k0 += kTeamBlock) {  // at least one arc of every entry taken lies in [lo, hi)
@@ -355,7 +361,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
       const uint32_t p = act ? sm.list[cur].pre[k] : 0u;
       const int32_t v = kSssp && act ? sm.list[cur].node[k] : 0, st = act ? sm.list[cur].st[k] : 0;
       if (last) {
-        const uint32_t pn = k + 1 < cnt ? sm.list[cur].pre[k + 1] : end;
+        const uint32_t pn = k + 1 < cnt ? sm.list[cur].pre[k + 1] : arcs;
         write_entry_wave<kPay, T, kNarrow>(a, out, act, nb + k, eb + p, v, st, static_cast<int32_t>(pn - p));
       } else if (!act) {
         continue;
@@ -498,7 +504,8 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
       if (from + r * kTeamBlock >= len) continue;
       const int32_t d = s1[r] - s0[r];
       // a node without out-arcs has nothing to expand
-      put_all(cur ^ 1u, win[r] && d > 0, vv[r], s0[r], d, du[r] + ww[r]);
+      put_all(cur ^ 1u, win[r] && d > 0, vv[r], s0[r], kSssp ? min(d, static_cast<int32_t>(kMostArcs)) : d,
+              du[r] + ww[r]);
     }
   };
 
@@ -509,16 +516,25 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
     if (fits)
       for (uint32_t k = tid; k < cnt; k += kTeamBlock) {
         const uint32_t s = sm.list[cur].pre[k];
-        atomicOr(&sm.flag[s >> 6], 1ull << (s & 63));
+        if (kSssp || s < kTeamSlots) atomicOr(&sm.flag[s >> 6], 1ull << (s & 63));  // BFS: malformed offsets
       }
     __syncthreads();
     load(0u);
-    if (known || (!staged && (rounds == 0u || !fits))) {
+    if (known || (!staged && (rounds == 0u || !fits || (leads && (arcs == 0u || arcs > kTeamOwnBfs))))) {
       if (!known) {
         ++e;
+        if (leads && tid == 0) {  // the thread that raises the flag
+          st_agent(&a.team->level[e & 1], L);
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
         alive = team_exchange<kSssp, false>(a, sm, e, me, P, payload());
         if (!alive) break;
         if (kSssp) ++L;
+        if (ahead) {
+          const uint32_t now = ld_agent(&a.team->level[e & 1]);
+          levels += now - L;
+          L = now;
+        }
       }
       known = false;
       nf = sm.segn[P];
@@ -526,6 +542,9 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
       // small and steady: else some workgroups' lists grow while others idle
       rounds = kSssp && sm.sege[P] <= P * kTeamCalm && sm.sege[P] <= 2 * E ? kTeamRounds : 1u;
       E = sm.sege[P];
+      ahead = !kSssp && sm.most == E && E <= kTeamOwnBfs;
+      leads = ahead && arcs > 0u;
+      if (leads) rounds = kTeamAhead;
       if (E == 0u) {
         if (!far) {
           done = true;
@@ -572,10 +591,11 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
 #pragma unroll
               for (int b = 0; b < kB; ++b) {
                 // room for this push and one in flight of every wavefront
-                const bool room = __any((sm.push >> 48) + kTeamBlock <= kTeamSlots);
+                const bool room = __any((sm.push >> 32) + kTeamBlock <= kTeamSlots);
                 const bool go = v[b] >= 0 && d[b] <= thr && room;
                 if (v[b] >= 0 && !go) kept |= 1u << (v[b] & 31);
-                put_all(cur ^ 1u, go && s1[b] > s0[b], v[b], s0[b], s1[b] - s0[b], d[b]);
+                put_all(cur ^ 1u, go && s1[b] > s0[b], v[b], s0[b],
+                        min(s1[b] - s0[b], static_cast<int32_t>(kMostArcs)), d[b]);
               }
             }
             if (kept != had) st_agent(at<kNarrow>(a.far, k), kept);
@@ -617,9 +637,10 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
               v = sm.list[cur].node[k];
               x = sm.list[cur].du[k];
               s0 = sm.list[cur].st[k];
-              d = static_cast<int32_t>((k + 1 < cnt ? sm.list[cur].pre[k + 1] : end) - sm.list[cur].pre[k]);
-              keep = static_cast<uint32_t>(v) < a.n &&
-                     static_cast<uint32_t>(ld_agent(at<kNarrow>(a.dstate, static_cast<uint32_t>(v))) >> 32) == x;
+              if (static_cast<uint32_t>(v) < a.n) {
+                d = *at<kNarrow>(a.offsets, v + 1) - s0;
+                keep = static_cast<uint32_t>(ld_agent(at<kNarrow>(a.dstate, static_cast<uint32_t>(v))) >> 32) == x;
+              }
             }
             put_all(cur ^ 1u, keep, v, s0, d, x);
           }
@@ -645,7 +666,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_expand_team(KArgs a, uint32_t la
         alive = team_exchange<kSssp, false>(a, sm, e, me, P, 0ull);
         if (!alive) break;
         if (E > 0u) stage();
-        else cnt = arcs = end = 0u;
+        else cnt = arcs = 0u;
         staged = true;
         rounds = 1u;
         continue;

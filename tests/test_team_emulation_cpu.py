@@ -165,3 +165,20 @@ def test_tile_marks_of_long_and_short_lists(emu, sssp):
     g = _graph(n, arcs)
     _, st = emu(g, sssp=sssp, src=1, limit=1000, blocks=3, stop=1)
     assert (st["error"], st["arcs"], st["entries"]) == (0, sum(degrees), len(degrees))
+
+
+@pytest.mark.parametrize("first", [0, 1])
+@pytest.mark.parametrize("tail", [1, 3, 700, 1500])
+def test_bfs_levels_of_one_workgroup(emu, first, tail):
+    """A path into a fan of `tail` nodes, which meet again in a second path:
+    while one workgroup holds the frontier it runs ahead of the others."""
+    n = 2 * 1300 + tail
+    arcs = [(v, v + 1, 1) for v in range(1299)] + [(v + 1, v, 1) for v in range(1299)]
+    arcs += [(1299, 1300 + k, 1) for k in range(tail)] + [(1300 + k, 1300 + tail, 1) for k in range(tail)]
+    arcs += [(v, v + 1, 1) for v in range(1300 + tail, n - 1)]
+    g = _graph(n, arcs)
+    for limit in (1 << 20, 900):
+        got, st = emu(g, sssp=0, src=3, first=first, limit=limit, blocks=6)
+        exp = O.bfs(g.offsets, g.cols, 3)
+        assert st["error"] == 0 and np.array_equal(got.view(np.int32), exp)
+        assert st["levels"] == int(exp[g.degrees > 0].max()) + 1
