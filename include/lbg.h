@@ -506,7 +506,7 @@ void lbg_profile_read(int32_t which, lbg_profile* out);
  * and SSSP queries mix freely in one batch: a BFS query claims each node of
  * its row once, with a bit in a per-row bitmap, and an SSSP query relaxes
  * with the atomic minimum of the single-query path.  lbg_batch_solve gives
- * the small queries of a large batch (instances of 2^28 arcs and more in all,
+ * the small queries of a large batch (instances of 2^29 arcs and more in all,
  * counted on the device when total_arcs, the caller's bound, allows as many)
  * to one workgroup each instead (state in LDS); results are the same.
  * ------------------------------------------------------------------------ */

@@ -1872,14 +1872,15 @@ __device__ __forceinline__ int solo_class(const KArgs& a, const QInfo& qi) {
 }
 
 // One workgroup gets through 0.6 to 1.2 G arcs/s, the chip through about 200
-// when it has several for every CU: batches of 2^28 arcs and more take their
+// when it has several for every CU: batches of 2^29 arcs and more take their
 // small queries that way (2,048 queries over 2.6 G arcs: the 1,024 BFS queries
 // 20 -> 6.8 ms), except those with more than a 256th of the batch, which would
-// hold it up.  Smaller batches are done sooner in the shared worklist (28
-// queries, 8 M arcs: 1.1 against 2.5 ms).  The arcs are those of the batch's
-// instances (one pass over the query table, 1,024 threads); the caller's bound
-// on them only says whether it is worth asking.
-constexpr unsigned long long kSoloBatch = 1ull << 28;
+// hold it up.  Smaller batches are done sooner in the shared worklist; shared
+// against alone, in ms: 2^25.2 arcs 1.53 / 2.38, 2^27.3 5.38 / 7.03, 2^28.2
+// 11.6 / 13.1, 2^29.7 25.2 / 23.5, 2^31.1 65.3 / 53.9.  The arcs are those of
+// the batch's instances (one pass over the query table, 1,024 threads); the
+// caller's bound on them only says whether it is worth asking.
+constexpr unsigned long long kSoloBatch = 1ull << 29;
 __global__ __launch_bounds__(1024) void k_solo_limit(KArgs a) {
   __shared__ unsigned long long total;
   if (threadIdx.x == 0) total = 0ull;

@@ -86,14 +86,15 @@ def test_solo_rejects_arc_leaving_instance():
 
 @pytest.mark.parametrize("wide", [0, 1])
 def test_solo_batches_of_as_many_arcs(wide):
-    """The same instances in batches whose queries hold 2^28 arcs and more, by
-    repetition.  One workgroup's atomics are in LDS and not counted: a BFS batch
-    without the large instance counts none."""
+    """The same instances in batches whose queries hold 2^29 arcs and more, by
+    repetition, and one beyond the limit, a 256th of that.  One workgroup's
+    atomics are in LDS and not counted: a BFS batch without the large instance
+    counts none."""
     lbg.set_addressing(wide)
-    gs = _instances()
+    gs = _instances() + [graphgen.uniform(n=300_000, k=8, salt=9)]
     u, nb, _ = graphgen.pack(gs)
     dg = lbg.DeviceGraph.from_numpy(u.offsets, u.cols, u.weights)
-    for kinds, largest in (((lbg.KIND_BFS, lbg.KIND_SSSP), 1 << 30), ((lbg.KIND_BFS,), 1 << 20)):
+    for kinds, largest in (((lbg.KIND_BFS, lbg.KIND_SSSP), 1 << 30), ((lbg.KIND_BFS,), 1 << 21)):
         once, expect, arcs = [], [], 0
         for i, g in enumerate(gs):
             for kind in kinds if g.m <= largest else ():
@@ -102,7 +103,7 @@ def test_solo_batches_of_as_many_arcs(wide):
                               else O.dijkstra(g.offsets, g.cols, g.weights, g.n - 1).view(np.int32))
                 arcs += g.m
         exp = torch.from_numpy(np.concatenate(expect)).cuda()
-        times = -(-BOUND // arcs)
+        times = -(-(1 << 29) // arcs)
         out, st = lbg.batch_solve(dg, once * times, stats=True)
         assert bool((out.view(times, -1) == exp).all())
         assert (st["atomics"] == 0) == (len(kinds) == 1)
