@@ -63,10 +63,13 @@
  *     tensors), except `stats` and the batched query table (host).  The
  *     caller owns every buffer; the library allocates no device memory.  It
  *     keeps, between calls: process-wide profiling counters, degree-bin
- *     parameters and the hash key of the symmetry check, per-device launch
- *     sizes, and per host thread one pinned control-block copy, its event
- *     pool, the last batch graph and how many large levels the thread's last
- *     BFS and SSSP had (which sizes the next solve's first submission).
+ *     parameters, the start of the symmetry check's random points and how
+ *     many were drawn, per-device launch sizes and whether a solve has the
+ *     device's team, and per host thread one pinned control-block copy, its
+ *     event pool, the last batch graph, how many large levels the thread's
+ *     last BFS and SSSP had and whether that SSSP deferred far nodes (which
+ *     size the next solve's first submission and choose its kernels; a wrong
+ *     guess costs launches that find no work).
  *   - `stream` is a hipStream_t passed as void* (NULL = default stream).  All
  *     work is ordered on it.  The call returns after the solve has finished
  *     on the stream (the level loop reads the frontier size back to decide
@@ -77,6 +80,8 @@
  *     CSR is O(n + m) and therefore opt-in: lbg_validate_csr().
  *   - Thread safety: concurrent calls are safe on distinct workspaces (and
  *     output buffers); lbg_set_bins affects binned solves that start later.
+ *     Of the balanced solves that run on a device at a time one has a team of
+ *     several workgroups for its small levels; the others run theirs in one.
  */
 #ifndef LBG_H
 #define LBG_H
@@ -115,7 +120,8 @@ typedef enum {
  * levels: number of frontiers holding at least one out-arc (BFS: 1 + the
  *         largest level of a reached node with out-arcs, which is the
  *         eccentricity of src + 1 unless every farthest node is a sink;
- *         SSSP: Bellman-Ford iterations).
+ *         SSSP: Bellman-Ford iterations, and of the small-frontier kernel
+ *         its rounds, which are run in runs of up to 16).
  * frontier_entries: total worklist entries processed (nodes; LBG_EDGE: edges;
  *         LBG_SLICED: (node, slice) pairs; LBG_SPLIT: pieces).
  * edges_scanned: total arcs of the worklist entries processed (BFS: the

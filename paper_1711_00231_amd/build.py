@@ -11,7 +11,8 @@ LIB_PATH = os.path.join(HERE, "liblbg.so")
 SOURCES = [os.path.join(HERE, "csrc", "lbg.hip")]
 DEPS = SOURCES + [os.path.join(HERE, "csrc", f) for f in ("lbg_device.hpp", "lbg_kernels.hpp", "lbg_sliced.hpp",
                                                                     "lbg_split.hpp", "lbg_order.hpp",
-                                                                    "lbg_team.hpp", "lbg_pull.hpp", "lbg_solo.hpp")] + \
+                                                                    "lbg_team.hpp", "lbg_pull.hpp", "lbg_solo.hpp",
+                                                                    "lbg_sym.hpp")] + \
     [os.path.join(ROOT, "include", "lbg.h")]
 
 HIPCC_FLAGS = [

@@ -306,7 +306,10 @@ thread_local int g_far_hint = kFarUnknown;
 // of hierarchical processing with 256-arc windows is 640 launches: R-MAT 22
 // SSSP 51 - 56 ms, 84 with submissions of 8, 16, ... levels).
 thread_local uint32_t g_level_hint[2] = {0u, 0u};
-// BFS solves of graphs of at least this many arcs may pull levels.
+// BFS solves of graphs of at least this many arcs may pull levels.  Below, the
+// pass and the extra launches cost as much as they save (without against with,
+// us: R-MAT 17 to 19, 3.7 to 15.5 M arcs, 138 / 143, 169 / 175, 208 / 213;
+// R-MAT 20, 31 M, 276 / 227).
 constexpr int64_t kPullGraph = int64_t{1} << 24;
 // The points of k_bfs_sym for one solve: uniform in the field, from a start
 // drawn at random when the first solve asks and moved on with each one, so a
@@ -545,17 +548,18 @@ int solve(const Problem& P) {
   // a level can only run in scan mode if the graph has that many arcs
   const bool scan_possible = static_cast<int64_t>(a.scan_min) <= P.m;
   // Every level that reaches the one-level launches scans (the default on
-  // graphs of up to 2^24 nodes; an `alone` submission aside): then a compaction leaves the filters as the
-  // next level needs them, and only the first launch after a team launch is
-  // preceded by the filter merge.
+  // graphs of up to 2^24 nodes with a full team; an `alone` submission aside):
+  // then a compaction leaves the filters as the next level needs them, and
+  // only the first launch after a team launch is preceded by the filter merge.
   const bool scan_all = scan_possible && a.scan_min <= team_limit + 1u;
   // Pull levels (lbg_pull.hpp): a pass over all arcs establishes symmetry, so
-  // the level must hold a good part of them (a quarter of what it costs to
-  // expand m / 16 arcs), and the graph enough for the extra launches to pay.
+  // the level must hold a good part of them (from m / 4, m / 16 or m / 64 arcs
+  // on, us: R-MAT 20 229, 226, 282; 22 548, 469, 506; 24 1946, 1605, 1574),
+  // and the graph enough for the extra launches to pay.
   // Whether smaller levels scan does not matter: where one may not have, the
   // filter merge precedes every launch and takes the snapshot, too.
   // The pass tells the pairs of kSymNodes nodes apart, and its workgroups leave
-  // their products (12 words each) in a worklist's node array, of n words.
+  // their products (8 words each) in a worklist's node array, of n words.
   constexpr int kPartWords = 2 * 2 * lbg::kSymPoints;
   int sym_blocks = 0;
   if (scan_possible && P.m >= kPullGraph && std::max(a.scan_min, team_limit + 1u) <= P.m / 16 &&

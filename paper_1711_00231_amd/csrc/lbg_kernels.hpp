@@ -333,8 +333,8 @@ __device__ __forceinline__ void init_state(const KArgs& a, int32_t src, uint32_t
 //
 // The step: 16 x the mean weight / the mean out-degree, i.e. about 16 arcs
 // of a node's share of weight.  Smaller steps relax fewer arcs in more
-// iterations.  Counted on the host emulation, arcs relaxed / iterations: grid
-// with shortcuts, 1 x mean weight 1.12 / 189, 4 x (this rule) 1.38 / 119,
+// iterations.  Counted with a host model of the rule, arcs relaxed /
+// iterations: grid with shortcuts, 1 x mean weight 1.12 / 189, 4 x (this rule) 1.38 / 119,
 // 8 x 1.72 / 105; uniform 2^20, 1 x 1.27 / 41, 2 x (this rule) 1.33 / 35, 4 x
 // 3.66 / 30.  While even the largest level of a step is a fraction of what
 // the chip takes in one round of latency the step doubles (the grid without
@@ -1231,31 +1231,8 @@ __global__ __launch_bounds__(kBlock) void k_expand_balanced(KArgs a, uint32_t k)
   balanced_level<kSssp, kNarrow, kMulti, kPacked, kSplit, kFar>(a, k);
 }
 
-// BFS scan levels.  A level of at least a.scan_min arcs is expanded without
-// claims or pushes (expand_level, scan mode): every newly reached node gets
-// level L + 1 in the levels array.  This kernel, launched after each
-// balanced BFS level, then builds worklist L + 1 from the nodes whose level
-// is L + 1 (the worklist of Section II-B, made by a scan of the node states
-// instead of by atomic claims; at R-MAT scale 22 a big level issues ~8 M
-// claim atomics, at a memory-side rate of ~25 G/s).  Each workgroup takes
-// chunks of 1024 x kPer nodes: coalesced loads of the chunk's levels and
-// offsets into LDS, then thread t handles nodes kPer t .. kPer (t + 1) - 1 of
-// the chunk, so a block scan gives every new node with out-arcs its place in
-// node order and one packed atomic reserves the chunk's entries: the next
-// level reads the CSR in order.  `visited`, next level's `seen` snapshot and
-// every XCD's filter are rewritten from the levels (each 32-node word by one
-// thread, plain stores), so a following scan level needs no k_bfs_prep.
-// What bounds it: 8 bytes per node read, and the reservations, which all hit
-// one address (about 12 ns each).  kPer = 16 where that still gives a chunk to
-// every CU (n >= 2^22), else 4.  Against 256 threads and 4096 nodes with a
-// k_bfs_prep before every scan level: R-MAT 22, 42 -> 31 us between two big
-// levels; 2048 x 2048 grid, 33 -> 17 us.
-// Returns at once after a push-mode level, whose pushes already built
-// worklist L + 1.  The host launches it only after levels it allows to scan
-// (it passes scan_min = UINT32_MAX to the expansion of any other level), so
-// a scan level is always followed by its compaction.
-// Before a level that may scan: every XCD's filter absorbs `visited`, which
-// is exact (push levels set it with claim atomics, the small-frontier kernel
+// BFS, before a level that may scan: every XCD's filter absorbs `visited`,
+// which is exact (push levels set it with claim atomics, the small-frontier kernel
 // too, scan levels by k_bfs_compact's whole-word stores), so in scan mode a
 // clear filter bit proves the node unreached before the level and the
 // expansion needs no read of the node's level (measured: BFS 2.6 % faster
@@ -1282,6 +1259,27 @@ constexpr int kCompactBlock = 1024;
 template <uint32_t kPer>
 __device__ __forceinline__ uint32_t compact_slot(uint32_t j) { return j + j / kPer; }
 
+// BFS scan levels.  A level of at least a.scan_min arcs is expanded without
+// claims or pushes (expand_level, scan mode): every newly reached node gets
+// level L + 1 in the levels array.  This kernel, launched behind it, then
+// builds worklist L + 1 from the nodes whose level is L + 1 (the worklist of
+// Section II-B, made by a scan of the node states instead of by atomic claims; at R-MAT scale 22 a big level issues ~8 M
+// claim atomics, at a memory-side rate of ~25 G/s).  Each workgroup takes
+// chunks of 1024 x kPer nodes: coalesced loads of the chunk's levels and
+// offsets into LDS, then thread t handles nodes kPer t .. kPer (t + 1) - 1 of
+// the chunk, so a block scan gives every new node with out-arcs its place in
+// node order and one packed atomic reserves the chunk's entries: the next
+// level reads the CSR in order.  `visited`, next level's `seen` snapshot and
+// every XCD's filter are rewritten from the levels (each 32-node word by one
+// thread, plain stores), so a following scan level needs no k_bfs_prep.
+// What bounds it: 8 bytes per node read, and the reservations, which all hit
+// one address (about 12 ns each).  kPer = 16 where that still gives a chunk to
+// every CU (n >= 2^22), else 4.  Against 256 threads and 4096 nodes with a
+// k_bfs_prep before every scan level: R-MAT 22, 42 -> 31 us between two big
+// levels; 2048 x 2048 grid, 33 -> 17 us.
+// Returns at once after a level that pushed, whose pushes already built
+// worklist L + 1, after a pulled one and after a launch that had no work.  The
+// host launches it behind every expansion of a solve whose levels may scan.
 template <bool kNarrow, uint32_t kPer>
 __global__ __launch_bounds__(kCompactBlock) void k_bfs_compact(KArgs a, uint32_t launch) {
   const uint32_t L = level_of(a, launch);

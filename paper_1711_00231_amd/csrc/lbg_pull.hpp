@@ -11,8 +11,8 @@
 //
 // The caller's CSR is any directed graph, so symmetry is established in the
 // solve, and only when a level is about to be pulled:
-//  * k_init samples arcs between low-degree nodes; one without its reverse
-//    settles the matter (directed graphs of low degree stop here);
+//  * k_init samples arcs to nodes of few arcs; one without its reverse settles
+//    the matter (almost all directed graphs stop here);
 //  * k_bfs_sym then reads every arc once, in order (a streaming pass, 4 bytes
 //    per arc), and compares the products of lbg_sym.hpp at two random points.
 //    A graph that does not pass is expanded as before.

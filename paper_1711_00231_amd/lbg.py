@@ -356,7 +356,8 @@ def get_slice_min() -> int:
 
 def set_bfs_scan_min(arcs: int) -> None:
     """Frontier arcs from which a balanced BFS level runs in scan mode
-    (< 0: n / 4, 0: every level, >= 2**32: never; see lbg_set_bfs_scan_min)."""
+    (< 0: n / 32, of the levels too large for the small-frontier kernel;
+    0: every level, >= 2**32: never; see lbg_set_bfs_scan_min)."""
     _check(lib.lbg_set_bfs_scan_min(int(arcs)))
 
 
