@@ -334,9 +334,9 @@ __device__ __forceinline__ void init_state(const KArgs& a, int32_t src, uint32_t
 // The step: 16 x the mean weight / the mean out-degree, i.e. about 16 arcs
 // of a node's share of weight.  Smaller steps relax fewer arcs in more
 // iterations.  Counted with a host model of the rule, arcs relaxed /
-// iterations: grid with shortcuts, 1 x mean weight 1.12 / 189, 4 x (this rule) 1.38 / 119,
-// 8 x 1.72 / 105; uniform 2^20, 1 x 1.27 / 41, 2 x (this rule) 1.33 / 35, 4 x
-// 3.66 / 30.  While even the largest level of a step is a fraction of what
+// iterations: grid with shortcuts, 1 x mean weight 1.12 / 189, 4 x (this rule)
+// 1.38 / 119, 8 x 1.72 / 105; uniform 2^20, 1 x 1.27 / 41, 2 x (this rule)
+// 1.33 / 35, 4 x 3.66 / 30.  While even the largest level of a step is a fraction of what
 // the chip takes in one round of latency the step doubles (the grid without
 // shortcuts: 4587 iterations at 4 x, 3560 with doubling).
 //

@@ -16,9 +16,12 @@
 //  * k_bfs_sym then reads every arc once, in order (a streaming pass, 4 bytes
 //    per arc), and compares the products of lbg_sym.hpp at two random points.
 //    A graph that does not pass is expanded as before.
-// R-MAT 22: 0.98 -> 0.48 ms for the solve, of which the pass over 513 MB of
-// arcs takes 174 us (2.9 TB/s) and the two pulled levels 112 + 38 us, where
-// expansion and compaction took 265 + 582 us; R-MAT 24: 4.28 -> 1.38 ms.
+// R-MAT 22: 0.98 -> 0.47 ms for the solve, of which the pass over 513 MB of
+// arcs takes 187 us (2.7 TB/s; 163 - 176 us when it summed a 64-bit hash, which
+// a family of directed graphs could make zero) and the two pulled levels
+// 75 + 37 us, where expansion and compaction took 265 + 582 us; R-MAT 24:
+// 4.28 -> 1.41 ms.  A graph that is symmetric but for a few arcs pays for the
+// pass and has no pulled level (R-MAT 22 less three arcs: 1.07 -> 1.21 ms).
 #pragma once
 
 #include <type_traits>
