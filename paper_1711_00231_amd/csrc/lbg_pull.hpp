@@ -17,9 +17,9 @@
 //    per arc), and compares the products of lbg_sym.hpp at two random points.
 //    A graph that does not pass is expanded as before.
 // R-MAT 22: 0.98 -> 0.47 ms for the solve, of which the pass over 513 MB of
-// arcs takes 187 us (2.7 TB/s; 163 - 176 us when it summed a 64-bit hash, which
-// a family of directed graphs could make zero) and the two pulled levels
-// 75 + 37 us, where expansion and compaction took 265 + 582 us; R-MAT 24:
+// arcs takes about 185 us (2.8 TB/s; 163 - 176 us when it summed a 64-bit hash,
+// which a family of directed graphs could make zero) and the two pulled levels
+// about 74 + 35 us, where expansion and compaction took 265 + 582 us; R-MAT 24:
 // 4.28 -> 1.41 ms.  A graph that is symmetric but for a few arcs pays for the
 // pass and has no pulled level (R-MAT 22 less three arcs: 1.07 -> 1.21 ms).
 #pragma once
