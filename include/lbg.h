@@ -80,8 +80,9 @@
  *     CSR is O(n + m) and therefore opt-in: lbg_validate_csr().
  *   - Thread safety: concurrent calls are safe on distinct workspaces (and
  *     output buffers); lbg_set_bins affects binned solves that start later.
- *     Of the balanced solves that run on a device at a time one has a team of
- *     several workgroups for its small levels; the others run theirs in one.
+ *     Of the balanced solves that a process runs on a device at a time one has
+ *     a team of several workgroups for its small levels; the others run theirs
+ *     in one.
  */
 #ifndef LBG_H
 #define LBG_H
